@@ -176,8 +176,8 @@ size_t fq_act_workspace_bytes(int K, int Kpad);
  * Limit: fq_act_workspace_bytes(K, Kpad) <= FQ_NOALLOC_SCRATCH_BYTES (e.g. K = 32768 with Kpad = 65536),
  * else FQ_ERR_WORKSPACE and nothing is enqueued.  The first call on a device looks the array's address up
  * (hipGetSymbolAddress; FQ_ERR_HIP if that fails).
- * All calls on one GPU share that GPU's array and it keeps the previous call's contents; what has to start
- * at zero is cleared by a kernel inside every call (no memset node, so the call may be captured).  Calls
+ * All calls on one GPU share that GPU's array and it keeps the previous call's contents; no part of it has to
+ * hold a value on entry (and nothing is cleared with a memset node, so the call may be captured).  Calls
  * that overlap on one GPU (different streams, or threads without ordering) race on the array: order them.
  * ------------------------------------------------------------------------------------------- */
 #define FQ_NOALLOC_SCRATCH_BYTES (1u << 20)

@@ -369,7 +369,7 @@ int fq_flatten_quant_act_noalloc(const void* X, int x_dtype, int M, int K, int l
     void* base = nullptr;
     rc = scratch_of_current_device(&base);
     if (rc) return rc;
-    // cmax, the part of the scratch that must start at zero, is cleared by a fill kernel inside the launch
+    // no part of the scratch has to hold anything on entry
     ActWorkspace ws = carve_act_workspace(base, K, Kpad);
     return launch_flatten_quant(X, x_dtype, M, K, ldx, src_idx, rep, Kpad, bits, absmax_in ? 1 : 0, absmax_in,
                                 Xq_out, s_x_out, ws, static_cast<hipStream_t>(stream));

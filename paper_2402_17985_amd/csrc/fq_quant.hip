@@ -5,11 +5,14 @@
 // s = max|.| / qmax, round, here round-half-even, then clamp).
 //
 // The kernels, all bandwidth or latency bound:
-//   colabsmax           per input channel max|x| over the rows (64-wide wave reads 1 KiB of a row per
-//                       instruction; per-thread running max; one atomic max per column per block;
+//   colabsmax           per input channel max|x| over the rows for calibration (64-wide wave reads 1 KiB of a
+//                       row per instruction; per-thread running max; one atomic max per column per block;
 //                       the max of non-negative floats is taken on their bit patterns, so the
 //                       result does not depend on the order of the updates)
-//   scale               per-tensor absmax a' by wavefront reductions, the scale s, the per-slot
+//   tensor_absmax       the same pass over X, reduced to one candidate for the per-tensor absmax a' per workgroup
+//   flatten_quant_direct  few rows: map, a', multipliers and the quantizer in one kernel (with tensor_absmax before
+//                       it when the scale is dynamic and X more than a few rows)
+//   scale               many rows: a' from the candidates, the scale s, the per-slot
 //                       multiplier m_p = fl32(qmax / (n_p * a')) (float64 quotient), and two flags
 //                       per group of 16 slots that tell the quantizer which path a group may take
 //   flatten_quant_rows  the quantizer of the equal split: a workgroup owns a strip of rows, reads the
@@ -18,6 +21,7 @@
 //   flatten_quant       the general form (one thread per 16 slots and strip of rows, every slot
 //                       gathered from global memory): the peel split of Eq. 3 as printed, and layers
 //                       too wide for the row-strip kernel's LDS budget
+#include <algorithm>
 #include <atomic>
 
 #include "fq_internal.h"
@@ -109,23 +113,17 @@ __global__ void fill_u32_kernel(uint32_t* p, int count, uint32_t v)
 // of a column meet in LDS and one lane issues the atomic max, and only if its value exceeds what the
 // column already holds (the stored value only grows, so a stale read can only cause a redundant
 // atomic, never a missed one).
+// Running maxima of |X| over the rows r0 + wave, r0 + wave + 4, ... < r1 of the VEC columns from col0 on.
 template <int DT>
-__global__ __launch_bounds__(256) void colabsmax_kernel(const void* __restrict__ Xv, int M, int K, int ld,
-                                                        int rows_per_block, uint32_t* __restrict__ cmax)
+__device__ __forceinline__ void strip_colmax(const typename Elem<DT>::type* __restrict__ X, int K, int ld, int r0, int r1,
+                                             int col0, int wave, float (&mx)[Elem<DT>::VEC])
 {
     typedef typename Elem<DT>::type T;
     constexpr int VEC = Elem<DT>::VEC;
-    __shared__ float part[4][64 * VEC];
-    const T* X = static_cast<const T*>(Xv);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col0 = (blockIdx.x * 64 + lane) * VEC;
-    const int r0 = blockIdx.y * rows_per_block;
-    const int r1 = min(M, r0 + rows_per_block);
-    float mx[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) mx[v] = 0.0f;
     if (col0 + VEC <= K) {
-        // wave w takes rows r0 + w, r0 + w + 4, ...; sixteen 16-byte loads in flight per lane
+        // sixteen 16-byte loads in flight per lane
         const T* p = X + (size_t)(r0 + wave) * ld + col0;
         const size_t step = (size_t)4 * ld;
         int r = r0 + wave;
@@ -164,6 +162,19 @@ __global__ __launch_bounds__(256) void colabsmax_kernel(const void* __restrict__
             for (int r = r0 + wave; r < r1; r += 4)
                 mx[v] = fmaxf(mx[v], fabsf(Elem<DT>::widen(X[(size_t)r * ld + col0 + v])));
     }
+}
+
+template <int DT>
+__global__ __launch_bounds__(256) void colabsmax_kernel(const void* __restrict__ Xv, int M, int K, int ld,
+                                                        int rows_per_block, uint32_t* __restrict__ cmax)
+{
+    constexpr int VEC = Elem<DT>::VEC;
+    __shared__ float part[4][64 * VEC];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r0 = blockIdx.y * rows_per_block;
+    float mx[VEC];
+    strip_colmax<DT>(static_cast<const typename Elem<DT>::type*>(Xv), K, ld, r0, min(M, r0 + rows_per_block),
+                     (blockIdx.x * 64 + lane) * VEC, wave, mx);
 #pragma unroll
     for (int v = 0; v < VEC; ++v) part[wave][lane * VEC + v] = mx[v];
     __syncthreads();
@@ -179,70 +190,113 @@ __global__ __launch_bounds__(256) void colabsmax_kernel(const void* __restrict__
 }
 
 // ---------------------------------------------------------------------------------------------
-// per-tensor absmax, scale and per-slot multipliers (one workgroup)
+// absmax of the flattened tensor, one candidate per workgroup
 // ---------------------------------------------------------------------------------------------
-// The per-tensor absmax of the flattened tensor is max_p fl32(c_p / n_p) with c_p the channel
-// maximum behind slot p and n_p its copy count.  Rounding is monotonic, so it equals
-// fl32(c* / n*) for the pair with the largest exact quotient; pairs are compared exactly by cross
-// multiplication in float64 (24-bit x n products, exact for n < 2^29), leaving a single division at
-// the end.
-struct Quot {
-    float c;
-    int n;
-};
-__device__ __forceinline__ Quot quot_max(Quot a, Quot b)
+// a' = max_p fl32(c_p / n_p) with c_p = max_i |X[i, src p]|.  The rounded quotient is monotonic in c, so the maximum
+// over rows may be taken after it: a workgroup that has seen the columns [c0, c0 + 64 VEC) of some rows contributes
+// max_j fl32(c_j / n_j), n_j = the smallest copy count of the valid slots that read channel j (channels that no slot reads
+// contribute nothing).  Four waves stream X; four more scan the map for n_j meanwhile.  The candidate goes to
+// cand[workgroup], and whoever needs a' takes the maximum of the candidates.
+// What this replaces: a kernel that cleared K channel maxima, atomic maxima on them, and a gather of all channel maxima
+// over the map in every workgroup of the kernel that forms the multipliers.
+// ALL: a' = max |X| over all channels, whatever the map (weights, peel split).
+template <int DT, bool ALL>
+__global__ __launch_bounds__(ALL ? 256 : 512) void tensor_absmax_kernel(const void* __restrict__ Xv, int M, int K, int ld,
+                                                                        int rows_per_block, const int32_t* __restrict__ src,
+                                                                        const int32_t* __restrict__ rep, int Kpad,
+                                                                        float* __restrict__ cand)
 {
-    return ((double)b.c * (double)a.n > (double)a.c * (double)b.n) ? b : a;
-}
-__device__ __forceinline__ Quot wave_quot_max(Quot q)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        Quot o;
-        o.c = __shfl_xor(q.c, off, 64);
-        o.n = __shfl_xor(q.n, off, 64);
-        q = quot_max(q, o);
+    constexpr int VEC = Elem<DT>::VEC, COLS = 64 * VEC, NONE = 0x7fffffff, NTHR = ALL ? 256 : 512;
+    __shared__ float part[4][COLS];
+    __shared__ int copies[COLS];
+    __shared__ float red[NTHR / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c0 = blockIdx.x * COLS;
+    const int r0 = blockIdx.y * rows_per_block;
+    if constexpr (!ALL) {
+        for (int c = tid; c < COLS; c += NTHR) copies[c] = NONE;
+        __syncthreads();
     }
-    return q;
+    float best = 0.0f;
+    if (wave < 4) {
+        float mx[VEC];
+        strip_colmax<DT>(static_cast<const typename Elem<DT>::type*>(Xv), K, ld, r0, min(M, r0 + rows_per_block),
+                         c0 + lane * VEC, wave, mx);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            if constexpr (ALL) best = fmaxf(best, mx[v]);
+            else part[wave][lane * VEC + v] = mx[v];
+        }
+    } else if constexpr (!ALL) {
+#pragma unroll 4
+        for (int p = (tid - 256) * 4; p < Kpad; p += 1024) {
+            const v4i s = *reinterpret_cast<const v4i*>(src + p);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int c = s[i] - c0;
+                if ((unsigned)s[i] < (unsigned)K && (unsigned)c < (unsigned)COLS) {
+                    const int n = rep[p + i];
+                    if (n > 0) atomicMin(&copies[c], n);
+                }
+            }
+        }
+    }
+    if constexpr (!ALL) {
+        __syncthreads();
+        for (int c = tid; c < COLS; c += NTHR) {
+            const float m = fmaxf(fmaxf(part[0][c], part[1][c]), fmaxf(part[2][c], part[3][c]));
+            const int n = copies[c];
+            // the float64 quotient rounded to fp32 is the correctly rounded fp32 quotient
+            if (n == 1) best = fmaxf(best, m);
+            else if (n != NONE) best = fmaxf(best, (float)((double)m / (double)n));
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
+    if (lane == 0) red[wave] = best;
+    __syncthreads();
+    if (tid == 0) {
+#pragma unroll
+        for (int w = 1; w < NTHR / 64; ++w) best = fmaxf(best, red[w]);
+        cand[blockIdx.y * gridDim.x + blockIdx.x] = best;
+    }
 }
 
-// Every workgroup recomputes the absmax a' (a cheap reduction over the map), tabulates the
-// multipliers m(n) = fl32(qmax / (n * a')) for n < 1024 in LDS (one float64 division per thread),
-// and fills its own 1024 slots of mslot.  Workgroup 0 also writes the scale.
-__global__ __launch_bounds__(1024) void scale_kernel(const uint32_t* __restrict__ cmax, int K,
+// ---------------------------------------------------------------------------------------------
+// per-tensor absmax, scale and per-slot multipliers (one workgroup)
+// ---------------------------------------------------------------------------------------------
+// Every workgroup takes the maximum of the candidates of tensor_absmax_kernel (at most 1024: one load per thread; none
+// when the bound is static), tabulates the multipliers m(n) = fl32(qmax / (n * a')) for n < 1024 in LDS (one float64
+// division per thread), and fills its own 1024 slots of mslot.  Workgroup 0 also writes the scale.
+__global__ __launch_bounds__(1024) void scale_kernel(const float* __restrict__ cand, int ncand, int K,
                                                      const int32_t* __restrict__ src,
                                                      const int32_t* __restrict__ rep, int Kpad, int qmax,
                                                      int mode, const float* __restrict__ absmax_in, float T,
                                                      float* __restrict__ mslot, float* __restrict__ scale_out,
                                                      float* __restrict__ scalars, uint8_t* __restrict__ gflag)
 {
+    __shared__ float red[16];
+    __shared__ float table[1024];
+    const int tid = threadIdx.x;
+    float a;
+    if (absmax_in) {
+        a = *absmax_in;
+        if (!(a >= 0.0f) || a > 3.0e38f) a = 0.0f;     // negative / NaN / Inf static bound: treated as 0
+    } else {
+        float best = (tid < ncand) ? cand[tid] : 0.0f;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
+        if ((tid & 63) == 0) red[tid >> 6] = best;
+        __syncthreads();
+        a = red[0];
+#pragma unroll
+        for (int w = 1; w < 16; ++w) a = fmaxf(a, red[w]);
+        if (mode == 3) a = fminf(a, T);
+    }
     // Peel split (modes 3 dynamic / 4 static): `rep` carries the slot ordinals e; mslot[p] receives the
     // offset fl32(e * T) that the slot subtracts from |x| (+inf in padding, which clamps to 0), and the
-    // single multiplier m = fl32(qmax / a') goes to scalars[2].  a' = min(T, max_j cmax[j]) when dynamic.
+    // single multiplier m = fl32(qmax / a') goes to scalars[2].  a' = min(T, max |X|) when dynamic.
     if (mode >= 3) {
-        __shared__ float redf[16];
-        __shared__ float a_peel;
-        const int tid = threadIdx.x;
-        float a;
-        if (mode == 3) {
-            float best = 0.0f;
-#pragma unroll 8
-            for (int j = tid; j < K; j += 1024) best = fmaxf(best, __uint_as_float(cmax[j]));
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
-            if ((tid & 63) == 0) redf[tid >> 6] = best;
-            __syncthreads();
-            if (tid == 0) {
-                float t = 0.0f;
-                for (int w = 0; w < 16; ++w) t = fmaxf(t, redf[w]);
-                a_peel = fminf(t, T);
-            }
-            __syncthreads();
-            a = a_peel;
-        } else {
-            a = *absmax_in;
-            if (!(a >= 0.0f) || a > 3.0e38f) a = 0.0f;
-        }
         if (blockIdx.x == 0 && tid == 0) {
             *scale_out = (a == 0.0f) ? 1.0f : (float)((double)a / (double)qmax);
             scalars[0] = a;
@@ -255,53 +309,6 @@ __global__ __launch_bounds__(1024) void scale_kernel(const uint32_t* __restrict_
             mslot[p] = valid ? (float)e * T : __builtin_inff();
         }
         return;
-    }
-    __shared__ Quot red[16];
-    __shared__ float a_shared;
-    __shared__ float table[1024];
-    const int tid = threadIdx.x;
-    float a;
-    if (mode != 1) {
-        Quot best = {0.0f, 1};
-        if (mode == 0) {
-            // eight slots per thread at a time: all map loads, then all gathers of the channel maxima, so
-            // that a pass costs two memory latencies instead of two per slot
-            for (int base = tid; base < Kpad; base += 8 * 1024) {
-                int s[8], n[8];
-                float c[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int p = base + u * 1024;
-                    s[u] = (p < Kpad) ? src[p] : -1;
-                    n[u] = (p < Kpad) ? rep[p] : 0;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const bool ok = (unsigned)s[u] < (unsigned)K && n[u] > 0;
-                    c[u] = ok ? __uint_as_float(cmax[s[u]]) : 0.0f;
-                    if (!ok) n[u] = 1;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) best = quot_max(best, Quot{c[u], n[u]});
-            }
-        } else {
-#pragma unroll 8
-            for (int j = tid; j < K; j += 1024) best = quot_max(best, Quot{__uint_as_float(cmax[j]), 1});
-        }
-        best = wave_quot_max(best);
-        if ((tid & 63) == 0) red[tid >> 6] = best;
-        __syncthreads();
-        if (tid < 64) {
-            Quot t = (tid < 16) ? red[tid] : Quot{0.0f, 1};
-            t = wave_quot_max(t);
-            // the float64 quotient rounded to fp32 is the correctly rounded fp32 quotient
-            if (tid == 0) a_shared = (float)((double)t.c / (double)t.n);
-        }
-        __syncthreads();
-        a = a_shared;
-    } else {
-        a = *absmax_in;
-        if (!(a >= 0.0f) || a > 3.0e38f) a = 0.0f;     // negative / NaN / Inf static bound: treated as 0
     }
     const double ad = (double)a;
     if (blockIdx.x == 0 && tid == 0) {
@@ -351,6 +358,24 @@ __global__ __launch_bounds__(1024) void scale_kernel(const uint32_t* __restrict_
 // ---------------------------------------------------------------------------------------------
 // flatten + quantize
 // ---------------------------------------------------------------------------------------------
+// LDS of flatten_quant_direct_kernel before the strip itself: the table of multipliers and the wave maxima.  Copy counts
+// below DIRECT_TABLE fit a byte.
+constexpr int DIRECT_TABLE = 256, DIRECT_RED = 16;
+constexpr int DIRECT_LDS_FIXED = (DIRECT_TABLE + DIRECT_RED) * 4;
+
+// Eight consecutive map entries.  The entry points ask for 16-byte alignment of src only: a 4-byte aligned vector type
+// keeps the loads wide for any rep (global memory needs no more than dword alignment).
+// Workgroup barrier that orders LDS only: global loads and stores stay in flight across it.
+__device__ __forceinline__ void strip_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+struct __attribute__((packed, aligned(4))) i4a4 { int v[4]; };
+__device__ __forceinline__ void load8(const int32_t* p, int* out)
+{
+    const i4a4 a = *reinterpret_cast<const i4a4*>(p), b = *reinterpret_cast<const i4a4*>(p + 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { out[i] = a.v[i]; out[4 + i] = b.v[i]; }
+}
+
 // BITS = 8, 4, or 6 = the 4-bit quantizer with its values stored as 6-bit E3M2 codes (k-blocked layout);
 // for 6 the result is the code itself, which is also what the row strip keeps in LDS
 template <int BITS> __device__ __forceinline__ int quant1(float x, float m)
@@ -679,6 +704,335 @@ __global__ __launch_bounds__(BITS == 6 ? 512 : 256) void flatten_quant_rows_kern
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// flatten + quantize of an activation of few rows (the equal split)
+// ---------------------------------------------------------------------------------------------
+// The same two phases as the row-strip kernel, but nothing is prepared in kernels of their own: at these sizes a call is
+// bound by its launches (each 4-8 us) and not by bytes.  A workgroup owns a run of rows, which it walks in strips of R,
+// and has one thread per P head groups, so that a strip is one round of loads.
+//   the map    thread t reads the sources and copy counts of its groups t, t + blockDim, ... of the head.  A group is
+//              plain when its slots are the channels at the same indices with tabulated copy counts; the counts of plain
+//              groups are left in LDS, and from them follows which appended groups only repeat their values.
+//   a'         the static bound; or the maximum of the candidates that tensor_absmax_kernel left; or (few rows) taken
+//              from all of X by every workgroup, which costs M * K reads from L2 against a launch.
+//   strips     phase 1 quantizes the plain head groups from registers, phase 2 copies appended slots out of LDS; any
+//              other group is gathered slot by slot.  The next strip is read before phase 2.
+template <int DT, int BITS, int P, int R>
+__global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* __restrict__ Xv, int M, int K, int ld,
+                                                                    const int32_t* __restrict__ src,
+                                                                    const int32_t* __restrict__ rep, int Kpad,
+                                                                    const float* __restrict__ absmax_in,
+                                                                    const float* __restrict__ cand, int ncand,
+                                                                    float* __restrict__ scale_out,
+                                                                    float* __restrict__ scalars, uint8_t* __restrict__ out)
+{
+    typedef typename Elem<DT>::type T;
+    constexpr int VEC = Elem<DT>::VEC, NV = 16 / VEC;
+    constexpr int QMAX = (BITS == 8) ? 127 : 7;
+    const int nthr = blockDim.x, tid = threadIdx.x;
+    extern __shared__ __align__(16) uint8_t lds[];
+    const T* X = static_cast<const T*>(Xv);
+    const int NH = K >> 4;                                     // groups of the head
+    const int KQ = NH << 4;
+    const int G = Kpad >> 4;
+    const int NT = G - NH;                                     // groups of phase 2
+    float* table = reinterpret_cast<float*>(lds);              // [DIRECT_TABLE] m(n) = fl32(qmax / (n a'))
+    float* red = table + DIRECT_TABLE;                         // [DIRECT_RED]
+    uint8_t* qs = lds + DIRECT_LDS_FIXED;                      // [R][KQ] int8
+    uint16_t* ts = reinterpret_cast<uint16_t*>(qs + (size_t)R * KQ);    // sources of the phase-2 slots
+    uint8_t* tf = qs + (size_t)R * KQ + (size_t)NT * 32;                // copy flags of the phase-2 groups
+    const int row_begin = (int)((long long)M * blockIdx.x / gridDim.x);
+    const int row_end = (int)((long long)M * (blockIdx.x + 1) / gridDim.x);
+
+    // the head groups of a strip of X; every row index is below row_end, every group inside the row
+    v4u raw[P][R][NV];
+    auto load_strip = [&](int rs) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const int g = tid + p * nthr;
+            if (g < NH) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (rs + r < row_end) {
+                        const v4u* vp = reinterpret_cast<const v4u*>(X + (size_t)(rs + r) * ld + (g << 4));
+#pragma unroll
+                        for (int i = 0; i < NV; ++i) raw[p][r][i] = vp[i];
+                    }
+            }
+        }
+    };
+    load_strip(row_begin);
+
+    // bytes of an output row and of one group of 16 slots: 16 (INT8), 8 (INT4 nibbles), 12 (E3M2 codes)
+    constexpr int GB = (BITS == 8) ? 16 : (BITS == 4 ? 8 : 12);
+    // INT8 / INT4 rows are dense (E3M2 output has its own addressing, see store_e3m2)
+    const size_t orow_bytes = (size_t)(Kpad >> 4) * GB;
+    auto group_ofs = [&](int g) -> size_t { return (size_t)g * GB; };
+
+    // copy counts of eight slots (weights: no counts, every slot a plain copy)
+    const int32_t* counts = rep ? rep : src;
+    const bool counted = rep != nullptr;
+    auto load_counts = [&](int p, int* n) {
+        load8(counts + p, n);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) n[i] = counted ? n[i] : 1;
+    };
+    // sources and copy counts of a group's 16 slots
+    auto load_slots = [&](int p0, int (&sv)[16], int (&nv)[16]) {
+        load8(src + p0, sv);
+        load8(src + p0 + 8, sv + 8);
+        load_counts(p0, nv);
+        load_counts(p0 + 8, nv + 8);
+    };
+
+    // ---- the map ----
+    uint32_t nb[P][4];                                         // copy counts of this thread's plain groups, as bytes
+    int plain = 0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int g = tid + p * nthr;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) nb[p][i] = 0;
+        if (g < NH) {
+            int sv[16], nv[16];
+            load_slots(g << 4, sv, nv);
+            bool ok = true;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) ok = ok && sv[i] == (g << 4) + i && (unsigned)(nv[i] - 1) < DIRECT_TABLE - 1;
+            if (ok) {
+                plain |= 1 << p;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) nb[p][i >> 2] |= (uint32_t)nv[i] << (8 * (i & 3));
+            }
+            *reinterpret_cast<v4u*>(qs + (g << 4)) = v4u{nb[p][0], nb[p][1], nb[p][2], nb[p][3]};
+        }
+    }
+    __syncthreads();
+    // Sources of the phase-2 slots as 16-bit channel numbers (0xffff: the slot holds 0) and, per group, whether every
+    // slot holds 0 whatever the input or repeats a channel of a plain group with that channel's own copy count.  Eight
+    // slots per thread and pass; the two threads of a group sit in adjacent lanes.
+    for (int t = tid * 8; t < NT * 16; t += nthr * 8) {
+        int j[8], n[8];
+        load8(src + KQ + t, j);
+        load_counts(KQ + t, n);
+        bool copyable = true;
+        uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const bool in = (unsigned)j[i] < (unsigned)KQ;
+            const int own = in ? qs[j[i]] : 0;
+            if ((unsigned)j[i] < (unsigned)K) copyable = copyable && own != 0 && n[i] == own;
+            w[i >> 1] |= (in ? (uint32_t)j[i] : 0xffffu) << (16 * (i & 1));
+        }
+        *reinterpret_cast<v4u*>(ts + t) = v4u{w[0], w[1], w[2], w[3]};
+        const int mine = copyable ? 1 : 0, other = __shfl_xor(mine, 1, 64);
+        if ((tid & 1) == 0) tf[t >> 4] = (uint8_t)(mine & other);
+    }
+    __syncthreads();
+
+    // ---- a' and the table of multipliers ----
+    float a;
+    if (absmax_in) {
+        a = *absmax_in;
+        if (!(a >= 0.0f) || a > 3.0e38f) a = 0.0f;             // negative / NaN / Inf static bound: treated as 0
+    } else {
+        float best = 0.0f;
+        // the float64 quotient rounded to fp32 is the correctly rounded fp32 quotient
+        auto quotient = [&](float c, int n) { best = fmaxf(best, n == 1 ? c : (float)((double)c / (double)n)); };
+        if (cand) {
+            for (int c = tid; c < ncand; c += nthr) best = fmaxf(best, cand[c]);
+        } else {
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                const int g = tid + p * nthr;
+                if ((plain >> p) & 1) {
+                    float mx[16];
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) mx[i] = 0.0f;
+                    const T* xp = X + (g << 4);
+#pragma unroll 4
+                    for (int r = 0; r < M; ++r, xp += ld) {
+                        float x[16];
+#pragma unroll
+                        for (int i = 0; i < NV; ++i) widen16<DT>(reinterpret_cast<const v4u*>(xp)[i], x + i * VEC);
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) mx[i] = fmaxf(mx[i], fabsf(x[i]));
+                    }
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) quotient(mx[i], (nb[p][i >> 2] >> (8 * (i & 3))) & 0xff);
+                }
+            }
+            // the slots of every other group (head groups that are not plain, appended groups that do not repeat plain
+            // ones); plain groups and their copies have been seen above
+            for (int q = tid; q < G * 16; q += nthr) {
+                const int g = q >> 4;
+                bool seen;
+                if (g < NH) seen = qs[g << 4] != 0;
+                else seen = tf[g - NH] != 0;
+                if (seen) continue;
+                const int j = src[q], n = counted ? rep[q] : 1;
+                if ((unsigned)j >= (unsigned)K || n <= 0) continue;
+                float mx = 0.0f;
+#pragma unroll 8
+                for (int r = 0; r < M; ++r) mx = fmaxf(mx, fabsf(Elem<DT>::widen(X[(size_t)r * ld + j])));
+                quotient(mx, n);
+            }
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
+        if ((tid & 63) == 0) red[tid >> 6] = best;
+        __syncthreads();
+        a = red[0];
+#pragma unroll
+        for (int w = 1; w < DIRECT_RED; ++w) a = (w < (nthr >> 6)) ? fmaxf(a, red[w]) : a;
+    }
+    const double ad = (double)a;
+    auto multiplier = [&](int n) -> float { return (float)((double)QMAX / ((double)n * ad)); };
+    for (int n = tid; n < DIRECT_TABLE; n += nthr) table[n] = (n > 0 && a != 0.0f) ? multiplier(n) : 0.0f;
+    if (blockIdx.x == 0 && tid == 0) {
+        *scale_out = (a == 0.0f) ? 1.0f : (float)(ad / (double)QMAX);
+        scalars[0] = a;
+    }
+    __syncthreads();
+    float m[P][16];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) m[p][i] = table[(nb[p][i >> 2] >> (8 * (i & 3))) & 0xff];
+
+    auto pack_store = [&](const int (&q)[16], uint8_t* o) {
+        if (BITS == 8) {
+            v4u w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                w[i] = (uint32_t)(q[4 * i] & 0xff) | ((uint32_t)(q[4 * i + 1] & 0xff) << 8) |
+                       ((uint32_t)(q[4 * i + 2] & 0xff) << 16) | ((uint32_t)(q[4 * i + 3] & 0xff) << 24);
+            *reinterpret_cast<v4u*>(o) = w;
+        } else if (BITS == 6) {
+            (void)o;                                // E3M2 output goes through store_e3m2
+        } else {
+            v2u w;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                uint32_t acc = 0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc |= (uint32_t)(q[8 * i + j] & 0xf) << (4 * j);
+                w[i] = acc;
+            }
+            *reinterpret_cast<v2u*>(o) = w;
+        }
+    };
+    // E3M2 output, blocked along k: block t (codes 128 t .. 128 t + 127) holds 96 bytes of every row in turn.
+    // A row's 96 bytes are two 48-byte groups of 64 codes; the 24-byte bit stream of each 32-code unit a is
+    // split into its first 16 bytes X_a and last 8 bytes Y_a, and the group is stored X_a Y_a Y_b X_b with
+    // (a, b) = (0, 1) in rows whose index has bit 4 clear and (1, 0) in the others (what the GEMM's LDS reads
+    // want).  A thread's 16 codes are half a unit: stream bytes 0..11 (e = 0) or 12..23 (e = 1).
+    auto store_e3m2 = [&](const int (&q)[16], int row, int g) {
+        const u3 v = pack16_e3m2(q);
+        const int gi = g & 7, e = gi & 1;
+        uint8_t* grp = out + ((size_t)(g >> 3) * (size_t)M + (size_t)row) * 96 + 48 * (gi >> 2);
+        const bool mirrored = (((gi >> 1) ^ (row >> 4)) & 1) != 0;
+        if (!mirrored) {
+            *reinterpret_cast<u3*>(grp + 12 * e) = v;                 // X at 0, Y at 16: the plain stream
+        } else if (e == 0) {
+            *reinterpret_cast<u3*>(grp + 32) = v;                     // X at 32
+        } else {
+            *reinterpret_cast<uint32_t*>(grp + 44) = v.a;             // the last 4 bytes of X
+            *reinterpret_cast<v2u*>(grp + 24) = v2u{v.b, v.c};        // Y at 24
+        }
+    };
+    // one group of one row in its general form: every slot's source element gathered from global memory
+    auto gather_group = [&](int g, int row) {
+        const T* xr = X + (size_t)row * ld;
+        int s[16], n[16], q[16];
+        load_slots(g << 4, s, n);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const bool valid = (unsigned)s[i] < (unsigned)K && n[i] > 0;
+            const float x = Elem<DT>::widen(xr[(unsigned)s[i] < (unsigned)K ? s[i] : 0]);
+            float mult = 0.0f;
+            if (valid) mult = n[i] < DIRECT_TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
+            q[i] = quant1<BITS>(x, mult);
+        }
+        if constexpr (BITS == 6) store_e3m2(q, row, g);
+        else pack_store(q, out + (size_t)row * orow_bytes + group_ofs(g));
+    };
+
+    // head groups of this thread that are not plain
+    int slow = 0;
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        if (tid + p * nthr < NH && !((plain >> p) & 1)) slow |= 1 << p;
+
+    for (int rs = row_begin; rs < row_end; rs += R) {
+        const int nr = min(row_end - rs, R);
+        // ---- phase 1: the head ----
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const int g = tid + p * nthr;
+            if ((plain >> p) & 1) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (r < nr) {
+                        float x[16];
+#pragma unroll
+                        for (int i = 0; i < NV; ++i) widen16<DT>(raw[p][r][i], x + i * VEC);
+                        int q[16];
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) q[i] = quant1<BITS>(x[i], m[p][i]);
+                        if constexpr (BITS == 6) store_e3m2(q, rs + r, g);
+                        else pack_store(q, out + (size_t)(rs + r) * orow_bytes + group_ofs(g));
+                        v4u w;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            w[i] = (uint32_t)(q[4 * i] & 0xff) | ((uint32_t)(q[4 * i + 1] & 0xff) << 8) |
+                                   ((uint32_t)(q[4 * i + 2] & 0xff) << 16) | ((uint32_t)(q[4 * i + 3] & 0xff) << 24);
+                        *reinterpret_cast<v4u*>(qs + (size_t)r * KQ + (g << 4)) = w;
+                    }
+            }
+        }
+        load_strip(rs + R);
+        strip_barrier();
+
+        // ---- phase 2: appended copies and padding, (group, row) items over all threads; before them, this thread's
+        //      own head groups that are not plain ----
+        const int items = NT * nr, own = slow ? P * nr : 0;
+        for (int it = tid, k = 0; k < own || it < items;) {
+            int g, rr, gt = 0;
+            bool copy = false;
+            if (k < own) {
+                const int p = k / nr;
+                rr = k++ - p * nr;
+                if (!((slow >> p) & 1)) continue;
+                g = tid + p * nthr;
+            } else {
+                gt = it % NT;
+                rr = it / NT;
+                it += nthr;
+                g = NH + gt;
+                copy = tf[gt] != 0;
+            }
+            if (!copy) {
+                gather_group(g, rs + rr);
+                continue;
+            }
+            const v4u* tp = reinterpret_cast<const v4u*>(ts + gt * 16);
+            const v4u t0 = tp[0], t1 = tp[1];
+            const int8_t* ql = reinterpret_cast<const int8_t*>(qs) + (size_t)rr * KQ;
+            int q[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const uint32_t word = (i < 8) ? t0[i >> 1] : t1[(i - 8) >> 1];
+                const uint32_t j = (i & 1) ? (word >> 16) : (word & 0xffffu);
+                q[i] = (j == 0xffffu) ? 0 : (int)ql[j];
+            }
+            if constexpr (BITS == 6) store_e3m2(q, rs + rr, g);
+            else pack_store(q, out + (size_t)(rs + rr) * orow_bytes + group_ofs(g));
+        }
+        strip_barrier();
+    }
+}
+
 // Per input channel max|x| into cmax (fp32 bit patterns, which order like the non-negative floats
 // they hold); accumulate keeps what cmax holds on entry as the starting value.
 template <int DT>
@@ -705,6 +1059,57 @@ void launch_colabsmax(const void* X, int M, int K, int ld, bool accumulate, uint
     colabsmax_kernel<DT><<<grid, 256, 0, stream>>>(X, M, K, ld, (int)rpb, cmax);
 }
 
+// Raises a kernel's dynamic LDS limit once per device (`done` belongs to that kernel).
+int raise_lds_limit(const void* kern, int bytes, std::atomic<unsigned long long>& done)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return fail(FQ_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
+    const unsigned long long bit = 1ull << (dev & 63);
+    if (done.load(std::memory_order_acquire) & bit) return FQ_OK;
+    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) return fail(FQ_ERR_HIP, "hipFuncSetAttribute(%d bytes LDS): %s", bytes, hipGetErrorString(e));
+    done.fetch_or(bit, std::memory_order_release);
+    return FQ_OK;
+}
+
+// Candidates for a' of the flattened tensor (or, all_channels, of the whole array) into cand; returns their number, at
+// most 1024 and at most what the K floats of the workspace hold.
+template <int DT>
+int launch_tensor_absmax(const void* X, int M, int K, int ld, const int32_t* src, const int32_t* rep, int Kpad,
+                         bool all_channels, float* cand, hipStream_t stream)
+{
+    constexpr int VEC = Elem<DT>::VEC;
+    const int bx = (K + 64 * VEC - 1) / (64 * VEC);
+    const int cap = std::min(1024, (int)(round_up((size_t)K * 4, 256) / 4));
+    // Strips of 64 rows (16 loads in flight for each of the four waves) while that gives at most 512 workgroups, then
+    // higher ones.  Odd multiples of 64: with a power-of-two row stride, strips that start a power-of-two number of rows
+    // apart hit the same memory channels (16384 x 8192 bf16: 54 us at 576 rows, 59 us at 512).
+    long long rpb = ((long long)M * bx + 511) / 512;
+    rpb = std::max(64LL, (rpb + 63) / 64 * 64);
+    if (rpb > 64 && (rpb / 64) % 2 == 0) rpb += 64;
+    while ((M + rpb - 1) / rpb * bx > cap) rpb *= 2;
+    const int strips = (int)((M + rpb - 1) / rpb);
+    const dim3 grid(bx, (unsigned)strips);
+    if (all_channels) tensor_absmax_kernel<DT, true><<<grid, 256, 0, stream>>>(X, M, K, ld, (int)rpb, src, rep, Kpad, cand);
+    else tensor_absmax_kernel<DT, false><<<grid, 512, 0, stream>>>(X, M, K, ld, (int)rpb, src, rep, Kpad, cand);
+    return strips * bx;
+}
+
+typedef void (*direct_kernel_t)(const void*, int, int, int, const int32_t*, const int32_t*, int, const float*, const float*, int,
+                                float*, float*, uint8_t*);
+
+// Rows per strip of flatten_quant_direct_kernel: what the registers hold in flight (fp32 takes twice as many).
+template <int DT, int P> constexpr int direct_rows() { return DT == FQ_F32 ? (P == 1 ? 2 : 1) : (P == 1 ? 4 : 2); }
+
+template <int DT, int BITS, int P>
+int direct_kernel(direct_kernel_t* kern)
+{
+    static std::atomic<unsigned long long> raised{0};
+    *kern = flatten_quant_direct_kernel<DT, BITS, P, direct_rows<DT, P>()>;
+    return raise_lds_limit(reinterpret_cast<const void*>(*kern), 144 * 1024, raised);
+}
+
 template <int DT>
 int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx, const int32_t* rep,
                      int Kpad, int bits, int mode, const float* absmax_in, float T, void* out, float* scale_out,
@@ -712,27 +1117,52 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
 {
     const int qmax = (bits == 6) ? 7 : (1 << (bits - 1)) - 1;       // 6: the 4-bit quantizer, E3M2 storage
     const bool peel = mode >= 3;
-    if (bits == 6) {
-        // E3M2 storage exists in the row-strip kernel only: refuse before anything is enqueued
-        const size_t kq1 = (size_t)(K & ~15), tail1 = 2 * ((size_t)Kpad - kq1) + ((size_t)Kpad - kq1) / 16;
-        if (peel || K < 16 || kq1 + tail1 > 64u * 1024u)
-            return fail(FQ_ERR_DTYPE, "E3M2 storage (bits = 6) needs K >= 16 and a layer narrow enough for the "
-                                      "row-strip kernel, and is not available for the peel split");
-        // very wide layers launch this kernel with up to 128 KiB of LDS: raise its limit once per device
-        static std::atomic<unsigned long long> raised{0};
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return fail(FQ_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
-        const unsigned long long bit = 1ull << (dev & 63);
-        if (!(raised.load(std::memory_order_acquire) & bit)) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(flatten_quant_rows_kernel<DT, 6>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-            if (e != hipSuccess) return fail(FQ_ERR_HIP, "hipFuncSetAttribute(128 KiB LDS): %s", hipGetErrorString(e));
-            raised.fetch_or(bit, std::memory_order_release);
-        }
+    uint8_t* o8 = static_cast<uint8_t*>(out);
+    float* cand = ws.cmax;
+    const bool dynamic = mode != 1 && mode != 4, all_channels = mode >= 2;
+    // bytes of LDS per row of a strip, and per appended slot 2 (its source) and per appended group 1 (its flag)
+    const size_t kq = (size_t)(K & ~15), tail_src = 2 * ((size_t)Kpad - kq) + ((size_t)Kpad - kq) / 16;
+    const bool narrow = K >= 16 && kq + tail_src <= 64u * 1024u;
+    if (bits == 6 && (peel || !narrow))                             // E3M2 storage exists in the strip kernels only
+        return fail(FQ_ERR_DTYPE, "E3M2 storage (bits = 6) needs K >= 16 and a layer narrow enough for the "
+                                  "row-strip kernel, and is not available for the peel split");
+    const int NH = K >> 4, P = NH <= 1024 ? 1 : 2;
+    // Up to 12 Mi elements the direct kernel, beyond it scale_kernel and the row-strip kernel (three or, static, two
+    // launches, but no map work per workgroup).  Whole call, bf16, dynamic, direct against prepared: 16 x 4096 10.2 / 14.2
+    // us, 500 x 11008 18.9 / 21.6, 2048 x 4096 18.4 / 18.7, 1024 x 11008 (11.3 M) 23.4 / 23.7; at 4096 x 4096 (16.8 M)
+    // 25.5 / 24.7, 1024 x 20480 36.5 / 32.4, 8192 x 11008 98.9 / 87.0.
+    if (out && !peel && narrow && NH <= 2048 && (long long)M * K <= (12ll << 20)) {
+        const int R = P == 1 ? direct_rows<DT, 1>() : direct_rows<DT, 2>();
+        const int nthr = (int)round_up((size_t)(NH + P - 1) / P, 64);
+        const size_t lds = DIRECT_LDS_FIXED + (size_t)R * kq + tail_src;
+        // what the CUs hold at once: 1024 threads (128 registers each) and 160 KiB of LDS
+        const int occ = std::max(1, std::min((int)(160u * 1024u / lds), 1024 / nthr));
+        // a row each while there are CUs for them, then strips of R rows
+        const int nblk = std::min(std::max((M + R - 1) / R, std::min(M, 256)), 256 * occ);
+        direct_kernel_t kern = nullptr;
+        int rc;
+        if (P == 1) rc = bits == 8 ? direct_kernel<DT, 8, 1>(&kern) : bits == 6 ? direct_kernel<DT, 6, 1>(&kern) : direct_kernel<DT, 4, 1>(&kern);
+        else rc = bits == 8 ? direct_kernel<DT, 8, 2>(&kern) : bits == 6 ? direct_kernel<DT, 6, 2>(&kern) : direct_kernel<DT, 4, 2>(&kern);
+        if (rc) return rc;
+        // A few rows: every workgroup reads all of X for a' rather than a launch that does (16 x 4096 bf16: 10.2 against
+        // 12.4 us for the call); at most 64 rows, since a slot that repeats no plain group walks them one by one.
+        const bool self = mode == 0 && M <= 64 && (size_t)M * K * sizeof(typename Elem<DT>::type) <= 256u * 1024u;
+        int ncand = 0;
+        if (dynamic && !self) ncand = launch_tensor_absmax<DT>(X, M, K, ld, src_idx, rep, Kpad, all_channels, cand, stream);
+        kern<<<(unsigned)nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, mode == 2 ? nullptr : rep, Kpad, absmax_in,
+                                                    ncand ? cand : nullptr, ncand, scale_out, ws.scalars, o8);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return fail(FQ_ERR_HIP, "flatten-quantize launch failed: %s", hipGetErrorString(e));
+        return FQ_OK;
     }
-    if (mode != 1 && mode != 4) launch_colabsmax<DT>(X, M, K, ld, /*accumulate=*/false, ws.cmax, stream);
-    scale_kernel<<<(Kpad + 1023) / 1024, 1024, 0, stream>>>(ws.cmax, K, src_idx, rep, Kpad, qmax, mode, absmax_in, T,
+    if (bits == 6) {
+        // very wide layers launch the row-strip kernel with up to 128 KiB of LDS: raise its limit once per device
+        static std::atomic<unsigned long long> raised{0};
+        if (int rc = raise_lds_limit(reinterpret_cast<const void*>(flatten_quant_rows_kernel<DT, 6>), 128 * 1024, raised)) return rc;
+    }
+    int ncand = 0;
+    if (dynamic) ncand = launch_tensor_absmax<DT>(X, M, K, ld, src_idx, rep, Kpad, all_channels, cand, stream);
+    scale_kernel<<<(Kpad + 1023) / 1024, 1024, 0, stream>>>(cand, ncand, K, src_idx, rep, Kpad, qmax, mode, absmax_in, T,
                                                             ws.mslot, scale_out, ws.scalars, ws.gflag);
     if (!out) {
         // scales only: the caller quantizes elsewhere (the GEMM that converts its A operand on the way into LDS)
@@ -740,43 +1170,38 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
         if (e != hipSuccess) return fail(FQ_ERR_HIP, "activation scale launch failed: %s", hipGetErrorString(e));
         return FQ_OK;
     }
-    uint8_t* o8 = static_cast<uint8_t*>(out);
-    if (!peel && K >= 16) {
+    if (!peel && narrow) {
         // row-strip kernel: R rows per workgroup with R * K bytes of LDS plus 2 bytes per appended slot
         // (at most 64 KiB, so that two workgroups fit a CU); wider layers use the general kernel below
-        // per appended slot 2 bytes (its source) and per appended group 1 byte (its flag)
-        const size_t kq = (size_t)(K & ~15), tail_src = 2 * ((size_t)Kpad - kq) + ((size_t)Kpad - kq) / 16;
         int R = 8;
         while (R > 1 && (size_t)R * kq + tail_src > 64u * 1024u) R >>= 1;
         const size_t lds = (size_t)R * kq + tail_src;
-        if (lds <= 64u * 1024u) {
-            const unsigned nblk = (unsigned)((M + R - 1) / R);
-            // 256 threads walk the strip's groups (larger workgroups, one thread per head group, measured slower)
-            const int nthr = 256;
-            if (bits == 8)
-                flatten_quant_rows_kernel<DT, 8><<<nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad, R, o8);
-            else if (bits == 6) {
-                // Very wide layers (strips cut to two rows or one): the blocked E3M2 layout then gets runs of only
-                // 192 or 96 bytes per block.  A strip twice as high in a 512-thread workgroup with up to 128 KiB of
-                // LDS (one workgroup per CU) measured 11 % faster at K = 22016; at K = 11008 (four rows -> eight)
-                // the same change was 16 % slower, so it stops there.
-                int R6 = R;
-                size_t lds6 = lds;
-                int nthr6 = nthr;
-                if (R <= 2 && (size_t)(2 * R) * kq + tail_src <= 128u * 1024u) {
-                    R6 = 2 * R;
-                    lds6 = (size_t)R6 * kq + tail_src;
-                    nthr6 = 512;
-                    // (the kernel's LDS limit was raised above, before anything of this call was enqueued)
-                }
-                flatten_quant_rows_kernel<DT, 6><<<(unsigned)((M + R6 - 1) / R6), nthr6, lds6, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad, R6, o8);
+        const unsigned nblk = (unsigned)((M + R - 1) / R);
+        // 256 threads walk the strip's groups (larger workgroups, one thread per head group, measured slower)
+        const int nthr = 256;
+        if (bits == 8)
+            flatten_quant_rows_kernel<DT, 8><<<nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad, R, o8);
+        else if (bits == 6) {
+            // Very wide layers (strips cut to two rows or one): the blocked E3M2 layout then gets runs of only
+            // 192 or 96 bytes per block.  A strip twice as high in a 512-thread workgroup with up to 128 KiB of
+            // LDS (one workgroup per CU) measured 11 % faster at K = 22016; at K = 11008 (four rows -> eight)
+            // the same change was 16 % slower, so it stops there.
+            int R6 = R;
+            size_t lds6 = lds;
+            int nthr6 = nthr;
+            if (R <= 2 && (size_t)(2 * R) * kq + tail_src <= 128u * 1024u) {
+                R6 = 2 * R;
+                lds6 = (size_t)R6 * kq + tail_src;
+                nthr6 = 512;
+                // (the kernel's LDS limit was raised above, before anything of this call was enqueued)
             }
-            else
-                flatten_quant_rows_kernel<DT, 4><<<nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad, R, o8);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return fail(FQ_ERR_HIP, "flatten-quantize launch failed: %s", hipGetErrorString(e));
-            return FQ_OK;
+            flatten_quant_rows_kernel<DT, 6><<<(unsigned)((M + R6 - 1) / R6), nthr6, lds6, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad, R6, o8);
         }
+        else
+            flatten_quant_rows_kernel<DT, 4><<<nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad, R, o8);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return fail(FQ_ERR_HIP, "flatten-quantize launch failed: %s", hipGetErrorString(e));
+        return FQ_OK;
     }
     const int G = Kpad / 16;
     // rows per thread: as many as 8 while the launch still has >= 2048 waves
@@ -804,7 +1229,7 @@ ActWorkspace carve_act_workspace(void* base, int K, int Kpad)
     ActWorkspace ws;
     uint8_t* p = static_cast<uint8_t*>(base);
     size_t off = 0;
-    ws.cmax = reinterpret_cast<uint32_t*>(p + off);
+    ws.cmax = reinterpret_cast<float*>(p + off);
     off += round_up((size_t)K * 4, 256);
     ws.mslot = reinterpret_cast<float*>(p + off);
     off += round_up((size_t)Kpad * 4, 256);

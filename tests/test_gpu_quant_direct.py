@@ -1,0 +1,111 @@
+"""The flatten-quantize call on both sides of its dispatch rules, against the CPU oracle, byte for byte: the one-kernel
+form for few rows (one or two head groups per thread; a' static, read by every workgroup, or from the candidates of the
+absmax kernel) and the prepared form, with maps from the planner and maps that are not."""
+import numpy as np
+import pytest
+import torch
+
+import fq_workloads as WL
+import paper_2402_17985_amd as fq
+from oracle import fq_oracle as O
+from tests.gpu_util import DEV, bytes_ws, dev_i32, scalar, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _packed(q, bits):
+    return q.view(np.uint8) if bits == 8 else O.pack_i4(q) if bits == 4 else O.pack_e3m2_blocked(q)
+
+
+def _padded(X, dtype):
+    """Device tensor whose rows start on 16-byte boundaries, and the values it holds."""
+    store, Xf = WL.round_to_dtype(X, dtype)
+    M, K = X.shape
+    buf = to_dev(np.pad(store, ((0, 0), (0, -K % 16))), dtype)
+    return buf[:, :K], Xf
+
+
+def _check(X, dtype, src, rep, bits, static, rep_offset=0):
+    Xd, Xf = _padded(X, dtype)
+    M, K = X.shape
+    Kpad = len(src)
+    valid = (src >= 0) & (src < K) & (rep > 0)                            # every other slot holds 0: padding to the oracle
+    osrc, orep = np.where(valid, src, -1).astype(np.int32), np.where(valid, rep, 0).astype(np.int32)
+    a = np.float32(static) if static else O.act_absmax_dynamic(Xf, osrc, orep)
+    want, s_ref = O.flatten_quant_act(Xf, osrc, orep, bits if bits == 8 else 4, a)
+    shape = (Kpad // 128, M, 96) if bits == 6 else (M, Kpad if bits == 8 else Kpad // 2)
+    out = torch.full(shape, 0x55, dtype=torch.uint8, device=DEV)
+    s_x = torch.zeros(1, dtype=torch.float32, device=DEV)
+    rep_d = dev_i32(np.concatenate([np.zeros(rep_offset, np.int32), rep]))[rep_offset:]
+    fq.fq_flatten_quant_act(Xd, dev_i32(src), rep_d, bits, out, s_x, bytes_ws(fq.fq_act_workspace_bytes(K, Kpad)),
+                            absmax_in=scalar(static) if static else None)
+    torch.cuda.synchronize()
+    assert np.float32(s_x.item()) == s_ref
+    np.testing.assert_array_equal(out.cpu().numpy().reshape(-1), _packed(want, bits).reshape(-1))
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("dtype,M,K,bits", [
+    ("f32", 1, 16, 8), ("bf16", 3, 20, 4), ("f32", 5, 257, 6),            # narrow and ragged
+    ("bf16", 64, 1000, 8), ("bf16", 65, 1000, 8),                         # a' read by every workgroup / candidates
+    ("f16", 33, 4104, 4), ("bf16", 31, 4096, 6), ("f32", 16, 4096, 8),
+    ("bf16", 1, 16384, 8), ("bf16", 5, 16400, 4), ("f32", 3, 22016, 6),   # one head group per thread, and two
+    ("bf16", 768, 16384, 4), ("bf16", 769, 16384, 4),                     # last of the direct form, first of the other
+    ("bf16", 700, 1024, 8), ("f32", 1500, 272, 4), ("bf16", 2, 33000, 8), # strips of several rows; too wide for it
+])
+def test_planned_maps(dtype, M, K, bits, static):
+    rng = np.random.default_rng(K + M)
+    X = rng.standard_normal((M, K), dtype=np.float32)
+    out = rng.choice(K, max(1, K // 100), replace=False)
+    X[:, out] *= np.float32(40.0)
+    X[:, out[0]] *= np.float32(30.0)                                      # one channel with several hundred copies
+    chmax = np.abs(WL.round_to_dtype(X, dtype)[1]).max(axis=0).astype(np.float32)
+    T = float(np.float32(3.0 * np.median(chmax)))
+    src, rep, _, _ = fq.fq_flatten_plan(chmax, T, 128 if bits == 6 else 32)
+    _check(X, dtype, src, rep, bits, T if static else None)
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("M,K", [(9, 200), (40, 4000), (200, 1200)])
+def test_maps_that_are_not_the_planners(M, K, bits, static):
+    rng = np.random.default_rng(M)
+    X = (rng.standard_normal((M, K)) * rng.choice([1, 1, 10], K)).astype(np.float32)
+    Kpad = (K + 512 + 127) // 128 * 128
+    src = np.full(Kpad, -1, dtype=np.int32)
+    rep = np.zeros(Kpad, dtype=np.int32)
+    src[:K] = np.arange(K)
+    rep[:K] = rng.integers(1, 4, K)
+    src[16:32] = src[16:32][::-1]                                         # a head group that is a permutation
+    src[50] = -1                                                          # a hole in the head
+    rep[70] = 0                                                           # a head slot without copies
+    rep[100] = 256                                                        # copy counts beyond a byte
+    rep[101] = 100000
+    tail = np.arange(K + 3, Kpad - 20)
+    src[tail] = rng.integers(0, K, tail.size)
+    rep[tail] = rep[src[tail]]
+    rep[tail[::5]] += 1                                                   # not the channel's own copy count
+    src[tail[7]] = K + 5                                                  # out of range
+    _check(X, "f32", src, rep, bits, 3.0 if static else None, rep_offset=1)   # rep 4-byte aligned only
+    _check(np.zeros_like(X), "f32", src, rep, bits, None)
+
+
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("N,K", [(1, 16), (40, 1000), (300, 16400), (769, 16384)])
+def test_weights(N, K, bits):
+    """a' of the weights is their absmax over all channels, also those the map does not read."""
+    rng = np.random.default_rng(N)
+    W, Wf = _padded(rng.standard_normal((N, K), dtype=np.float32), "bf16")
+    Kpad = (K + 200 + 127) // 128 * 128
+    src = np.full(Kpad, -1, dtype=np.int32)
+    src[:K] = np.arange(K)
+    j = int(np.abs(Wf).max(axis=0).argmax())
+    src[j] = -1                                                           # the largest channel is not read
+    src[K:K + 150] = rng.integers(0, K, 150)
+    want, s_ref = O.flatten_weights(Wf, src, bits if bits == 8 else 4)
+    out = torch.full(((Kpad // 128, N, 96) if bits == 6 else (N, Kpad if bits == 8 else Kpad // 2)), 0x55, dtype=torch.uint8, device=DEV)
+    s_w = torch.zeros(1, dtype=torch.float32, device=DEV)
+    fq.fq_flatten_weights(W, dev_i32(src), bits, out, s_w, bytes_ws(fq.fq_weights_workspace_bytes(K, Kpad)))
+    torch.cuda.synchronize()
+    assert np.float32(s_w.item()) == s_ref
+    np.testing.assert_array_equal(out.cpu().numpy().reshape(-1), _packed(want, bits).reshape(-1))
