@@ -378,7 +378,9 @@ int fq_gemm_bf16(const void* X, const void* W, int M, int N, int K, void* Y, int
  *       bf16) or 10 (INT4).
  *   6:  128x128 tile, 4 waves, direct global->LDS copies (small problems, narrow outputs).
  *   2:  128x128 tile, 64-byte k-stages, 4 waves, operands staged through registers.
- * fq_gemm_i4_e3m2 has a single kernel and ignores the hook.
+ * fq_gemm_i4_e3m2 has a single kernel of this kind: any of these values selects it.
+ * With -1, products of at most 4 rows (4-bit values: 16) and outputs that one small tile per CU covers go to kernels of
+ * their own (weights streamed into registers; the reduction split over a workgroup's waves; a deep ring of stages).
  * Every variant computes the same values.  Returns FQ_ERR_RANGE for an unknown variant.
  * ------------------------------------------------------------------------------------------- */
 int fq_gemm_select(int variant);

@@ -26,6 +26,36 @@ int set_gemm_variant(int v)
     return FQ_OK;
 }
 
+// Raises a kernel's dynamic-LDS limit once per device.  `done` holds one bit per device ordinal (mod 64); a race
+// between two threads only repeats the idempotent call.
+int set_lds_limit(const void* kern, int smem, std::atomic<unsigned long long>& done)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return fail(FQ_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
+    const unsigned long long bit = 1ull << (dev & 63);
+    if (done.load(std::memory_order_acquire) & bit) return FQ_OK;
+    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (e != hipSuccess) return fail(FQ_ERR_HIP, "hipFuncSetAttribute(%d bytes LDS): %s", smem, hipGetErrorString(e));
+    done.fetch_or(bit, std::memory_order_release);
+    return FQ_OK;
+}
+
+// Compute units of the current device (cached per device ordinal).
+int compute_units()
+{
+    static std::atomic<int> cus[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    std::atomic<int>& slot = cus[dev & 63];
+    int n = slot.load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+        slot.store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
 // What a forced variant cannot run, checked before anything is enqueued (rowbytes = bytes of a quantized row).
 int check_forced_variant(int bits, int rowbytes)
 {
@@ -36,10 +66,56 @@ int check_forced_variant(int bits, int rowbytes)
     return FQ_OK;
 }
 
+namespace {
+// Products of few output tiles.  `done` says whether a kernel for them was chosen (and its launch attempted).
+//   - At most 4 rows, or 4-bit values and at most 16: the weights go straight into registers (gemm_skinny; INT8 at 8 and 16
+//     rows, 6400 x 15360: 23.0, 24.3 us against 20.9, 21.0 for the stream kernel; nibbles 10.2, 10.4 against 11.6, 11.6).
+//   - Otherwise the smallest tile with which one round of workgroups, one per CU, covers the output: a larger one leaves CUs
+//     idle, a smaller one takes a second round and reads the operands more often (INT8 12544 x 4096, 256 rows: 32 x 64 30.6,
+//     64 x 64 21.7, 96 x 64 25.2 us).  Up to 96 x 64 the reduction is split over the waves.  Beyond it INT8 goes through the
+//     ring (4608 x 11008, 128 rows, 128 x 64: 16.3 us, by split waves 18.5), 4-bit values stay with split waves (12544 x 4096, 500
+//     rows: nibbles 29.5 us, ring 37.6, 128 x 128 kernel 36.3; E3M2 27.3, its 256 x 256 kernel 46.2) up to 128 x 64; 128 x 128 tiles
+//     through the ring for INT8 and nibbles (4608 x 11008, 200 rows: 19.4 and 20.7 us against 26.0 and 21.9).
+//   - Batched products with a reduction of under four stages stay with the tiled kernels: there is nothing to split.
+int launch_few_tiles(const void* A, const void* B, int M, int N, int Kpad, int bits, const float* s_x, const float* s_w, void* Y,
+                     int y_dtype, int ldy, const Batch& bt, hipStream_t stream, bool& done)
+{
+    done = false;
+    const int rowbytes = bits == 8 ? Kpad : bits == 4 ? Kpad / 2 : Kpad / 4 * 3;
+    if (g_variant >= 0 || (bt.count > 1 && rowbytes < 512)) return FQ_OK;
+    if (M <= 4 || (bits != 8 && M <= 16 && N <= 16384)) {
+        done = true;
+        return launch_gemm_skinny(bits, A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+    }
+    const long long cus = compute_units();
+    auto one_round = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * bt.count <= cus; };
+    auto stream_tile = [&](StreamTile t) {
+        done = true;
+        return launch_gemm_stream(t, bits, A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+    };
+    auto ring_tile = [&](RingTile t) {
+        done = true;
+        return launch_gemm_ring(t, bits, A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+    };
+    if (one_round(32, 32)) return stream_tile(STREAM_32x32);
+    if (one_round(32, 64)) return stream_tile(STREAM_32x64);
+    if (one_round(64, 64)) return stream_tile(STREAM_64x64);
+    if (one_round(32, 128)) return stream_tile(STREAM_32x128);
+    if (one_round(96, 64)) return stream_tile(STREAM_96x64);
+    if (one_round(128, 64)) return bits == 8 ? ring_tile(RING_128x64) : stream_tile(STREAM_128x64);
+    if (one_round(64, 128)) return bits == 8 ? ring_tile(RING_64x128) : stream_tile(STREAM_64x128);
+    if (one_round(128, 128) && bits != FQ_BITS_I4_E3M2) return ring_tile(RING_128x128);
+    return FQ_OK;
+}
+}  // namespace
+
 int launch_gemm_int(const void* Xq, const void* Wq, int M, int N, int Kpad, int bits, const float* s_x,
                     const float* s_w, void* Y, int y_dtype, int ldy, hipStream_t stream, const float* bias)
 {
     const Batch one = {1, 0, 0, 0, bias, g_ticks};
+    bool done = false;
+    const int rc = launch_few_tiles(Xq, Wq, M, N, Kpad, bits, s_x, s_w, Y, y_dtype, ldy, one, stream, done);
+    if (done) return rc;
     if (bits == 8) return gemm_dispatch_i8(Xq, Wq, M, N, Kpad, s_x, s_w, Y, y_dtype, ldy, one, stream);
     if (bits == FQ_BITS_I4_E3M2) return gemm_dispatch_f6(Xq, Wq, M, N, Kpad / 4 * 3, s_x, s_w, Y, y_dtype, ldy, one, stream);
     return gemm_dispatch_i4(Xq, Wq, M, N, Kpad / 2, s_x, s_w, Y, y_dtype, ldy, one, stream);
@@ -50,6 +126,9 @@ int launch_bmm_int(const void* Aq, const void* Bq, int batch, int M, int N, int 
                    size_t stride_y_bytes, hipStream_t stream)
 {
     const Batch bt = {batch, stride_a, stride_b, stride_y_bytes, nullptr, g_ticks};
+    bool done = false;
+    const int rc = launch_few_tiles(Aq, Bq, M, N, Kpad, bits, s_a, s_b, Y, y_dtype, ldy, bt, stream, done);
+    if (done) return rc;
     if (bits == 8) return gemm_dispatch_i8(Aq, Bq, M, N, Kpad, s_a, s_b, Y, y_dtype, ldy, bt, stream);
     return gemm_dispatch_i4(Aq, Bq, M, N, Kpad / 2, s_a, s_b, Y, y_dtype, ldy, bt, stream);
 }

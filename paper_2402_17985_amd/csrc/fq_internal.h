@@ -1,6 +1,7 @@
 // Internal declarations shared by the translation units of libfq (GPU library only).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <atomic>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -71,6 +72,20 @@ int gemm_dispatch_bf16(const void* A, const void* B, int M, int N, int rowbytes,
                        void* Y, int y_dtype, int ldy, Batch bt, hipStream_t stream);
 int gemm_dispatch_f6(const void* A, const void* B, int M, int N, int rowbytes, const float* s_x, const float* s_w,
                        void* Y, int y_dtype, int ldy, Batch bt, hipStream_t stream);
+// The kernels for few output tiles (any output type and batch; rowbytes = bytes of a quantized row).  Skinny: at most 16
+// rows, weights streamed into registers.  Stream: the reduction split over the waves (the last two tiles for 4-bit values only).
+// Ring: one tile per CU through a deep ring of stages (INT8; nibbles 128 x 128 only).
+enum StreamTile { STREAM_32x32, STREAM_32x64, STREAM_64x64, STREAM_32x128, STREAM_96x64, STREAM_128x64, STREAM_64x128 };
+enum RingTile { RING_128x64, RING_64x128, RING_128x128 };
+int launch_gemm_skinny(int bits, const void* A, const void* B, int M, int N, int rowbytes, const float* s_x, const float* s_w,
+                       void* Y, int y_dtype, int ldy, Batch bt, hipStream_t stream);
+int launch_gemm_stream(int tile, int bits, const void* A, const void* B, int M, int N, int rowbytes, const float* s_x,
+                       const float* s_w, void* Y, int y_dtype, int ldy, Batch bt, hipStream_t stream);
+int launch_gemm_ring(int tile, int bits, const void* A, const void* B, int M, int N, int rowbytes, const float* s_x,
+                     const float* s_w, void* Y, int y_dtype, int ldy, Batch bt, hipStream_t stream);
+// Raises a kernel's dynamic-LDS limit once per device; `done` (one bit per device ordinal, mod 64) belongs to the kernel
+int set_lds_limit(const void* kern, int smem, std::atomic<unsigned long long>& done);
+int compute_units();         // of the current device
 int forced_gemm_variant();   // -1 = choose from the shape
 int set_gemm_variant(int v);
 int check_forced_variant(int bits, int rowbytes);   // FQ_OK unless the forced variant cannot run this operand

@@ -1059,20 +1059,6 @@ void launch_colabsmax(const void* X, int M, int K, int ld, bool accumulate, uint
     colabsmax_kernel<DT><<<grid, 256, 0, stream>>>(X, M, K, ld, (int)rpb, cmax);
 }
 
-// Raises a kernel's dynamic LDS limit once per device (`done` belongs to that kernel).
-int raise_lds_limit(const void* kern, int bytes, std::atomic<unsigned long long>& done)
-{
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return fail(FQ_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
-    const unsigned long long bit = 1ull << (dev & 63);
-    if (done.load(std::memory_order_acquire) & bit) return FQ_OK;
-    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e != hipSuccess) return fail(FQ_ERR_HIP, "hipFuncSetAttribute(%d bytes LDS): %s", bytes, hipGetErrorString(e));
-    done.fetch_or(bit, std::memory_order_release);
-    return FQ_OK;
-}
-
 // Candidates for a' of the flattened tensor (or, all_channels, of the whole array) into cand; returns their number, at
 // most 1024 and at most what the K floats of the workspace hold.
 template <int DT>
@@ -1107,7 +1093,7 @@ int direct_kernel(direct_kernel_t* kern)
 {
     static std::atomic<unsigned long long> raised{0};
     *kern = flatten_quant_direct_kernel<DT, BITS, P, direct_rows<DT, P>()>;
-    return raise_lds_limit(reinterpret_cast<const void*>(*kern), 144 * 1024, raised);
+    return set_lds_limit(reinterpret_cast<const void*>(*kern), 144 * 1024, raised);
 }
 
 template <int DT>
@@ -1158,7 +1144,7 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
     if (bits == 6) {
         // very wide layers launch the row-strip kernel with up to 128 KiB of LDS: raise its limit once per device
         static std::atomic<unsigned long long> raised{0};
-        if (int rc = raise_lds_limit(reinterpret_cast<const void*>(flatten_quant_rows_kernel<DT, 6>), 128 * 1024, raised)) return rc;
+        if (int rc = set_lds_limit(reinterpret_cast<const void*>(flatten_quant_rows_kernel<DT, 6>), 128 * 1024, raised)) return rc;
     }
     int ncand = 0;
     if (dynamic) ncand = launch_tensor_absmax<DT>(X, M, K, ld, src_idx, rep, Kpad, all_channels, cand, stream);

@@ -1,0 +1,87 @@
+"""The GEMM kernels for few rows and few output tiles: every kernel and tile of the dispatch, at the edges of its rows,
+columns, k-steps and waves.  Accumulators against the exact product; every output type bit for bit against the tiled
+kernels, which the other tests hold to the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2402_17985_amd as fq
+from oracle import fq_oracle as O
+from tests.gpu_util import DEV, scalar
+
+pytestmark = pytest.mark.gpu
+
+
+def _operand(rng, rows, K, bits):
+    """(integer values, the same in storage) on the device."""
+    lo, hi = (-128, 128) if bits == 8 else (-8, 8)
+    q = rng.integers(lo, hi, (rows, K), dtype=np.int8)
+    store = q if bits == 8 else O.pack_i4(q) if bits == 4 else O.pack_e3m2_blocked(q)
+    return torch.from_numpy(q).to(DEV), torch.from_numpy(np.ascontiguousarray(store)).to(DEV)
+
+
+def _gemm(bits, X, W, s_x, s_w, bias, Y):
+    if bits == 8:
+        fq.fq_gemm_i8_bias(X, W, s_x, s_w, bias, Y)
+    elif bits == 4:
+        fq.fq_gemm_i4_bias(X, W, s_x, s_w, bias, Y)
+    else:
+        fq.fq_gemm_i4_e3m2(X, W, s_x, s_w, bias, Y)
+
+
+# (M, N): what 256 CUs make of it
+SHAPES = [
+    (1, 40), (3, 4100), (4, 9001), (16, 300), (16, 9000), (16, 16380),     # rows streamed into registers (16: 4-bit values)
+    (5, 37), (33, 1000), (64, 4096),                                       # 32 x 32
+    (32, 11008), (100, 2001),                                              # 32 x 64
+    (130, 4000), (63, 16384), (8200, 20),                                  # 64 x 64
+    (20, 20000),                                                           # 32 x 128
+    (96, 16000), (90, 16001),                                              # 96 x 64
+    (128, 16000), (125, 15999),                                            # 128 x 64
+    (60, 30000),                                                           # 64 x 128
+    (300, 10000), (257, 9999),                                             # 128 x 128
+]
+
+
+@pytest.mark.parametrize("bits,K", [(8, 32), (8, 128), (8, 1056), (8, 2080), (4, 32), (4, 256), (4, 2144), (6, 128), (6, 1152)])
+@pytest.mark.parametrize("M,N", SHAPES)
+def test_accumulators(M, N, bits, K):
+    rng = np.random.default_rng(M + N + K)
+    xq, X = _operand(rng, M, K, bits)
+    wq, W = _operand(rng, N, K, bits)
+    Y = torch.full((M, N), 0x55555555, dtype=torch.int32, device=DEV)
+    _gemm(bits, X, W, None, None, None, Y)
+    assert torch.equal(Y.double(), xq.double() @ wq.double().t().contiguous())
+
+
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("ydt", [torch.float32, torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("M,N,pad", [(2, 130, 0), (2, 131, 2), (16, 9002, 6), (40, 333, 3), (70, 4096, 0), (128, 16000, 0), (300, 9999, 1)])
+def test_output_types_and_strides(M, N, pad, ydt, bits):
+    rng = np.random.default_rng(N)
+    _, X = _operand(rng, M, 1152, bits)
+    _, W = _operand(rng, N, 1152, bits)
+    bias = torch.from_numpy(rng.standard_normal(N, dtype=np.float32)).to(DEV)
+    for b in (None, bias):
+        got = torch.full((M, N + pad), 7.0, dtype=ydt, device=DEV)
+        want = got.clone()
+        _gemm(bits, X, W, scalar(0.013), scalar(0.0021), b, got[:, :N])
+        fq.fq_gemm_select(2)
+        try:
+            _gemm(bits, X, W, scalar(0.013), scalar(0.0021), b, want[:, :N])
+        finally:
+            fq.fq_gemm_select(-1)
+        kind = torch.int32 if ydt == torch.float32 else torch.int16
+        assert torch.equal(got.view(kind), want.view(kind))          # the padding columns stay untouched as well
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("batch,M,N,K", [(3, 40, 70, 1024), (160, 1, 128, 2048), (7, 4, 33, 1056), (12, 65, 130, 1024), (2, 1000, 1000, 1024)])
+def test_batched(batch, M, N, K, bits):
+    rng = np.random.default_rng(batch)
+    xq, X = _operand(rng, batch * M, K, bits)
+    wq, W = _operand(rng, batch * N, K, bits)
+    Y = torch.full((batch, M, N), -1, dtype=torch.int32, device=DEV)
+    (fq.fq_bmm_i8 if bits == 8 else fq.fq_bmm_i4)(X.view(batch, M, -1), W.view(batch, N, -1), None, None, Y)
+    want = torch.bmm(xq.view(batch, M, K).double(), wq.view(batch, N, K).double().transpose(1, 2).contiguous())
+    assert torch.equal(Y.double(), want)
