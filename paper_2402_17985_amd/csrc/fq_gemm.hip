@@ -459,19 +459,31 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const uint8_t* __
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const ClockProbe probe(bt.ticks);
-    // batched launches: blockIdx.y selects the problem
-    A += (size_t)blockIdx.y * bt.stride_a;
-    B += (size_t)blockIdx.y * bt.stride_b;
-    Y = static_cast<uint8_t*>(Y) + (size_t)blockIdx.y * bt.stride_y;
+    // Batched launches: the grid's y dimension counts the problems.  Ids are dealt round-robin to the XCDs over the whole
+    // grid, so each XCD gets a contiguous band of (problem, tile) pairs: a problem's operands then pass through one L2, not
+    // through all eight.
+    int problem = blockIdx.y, first = blockIdx.x;
+    const bool banded = gridDim.y > 1 && (unsigned long long)gridDim.x * gridDim.y < (1ull << 31);
+    if (banded) {
+        const unsigned total = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x;
+        const unsigned q = total >> 3, rem = total & 7, xcd = id & 7, idx = id >> 3;
+        const unsigned logical = (xcd < rem) ? xcd * (q + 1) + idx : rem * (q + 1) + (xcd - rem) * q + idx;
+        problem = __builtin_amdgcn_readfirstlane((int)(logical / gridDim.x));
+        first = __builtin_amdgcn_readfirstlane((int)(logical - (unsigned)problem * gridDim.x));
+    }
+    A += (size_t)problem * bt.stride_a;
+    B += (size_t)problem * bt.stride_b;
+    Y = static_cast<uint8_t*>(Y) + (size_t)problem * bt.stride_y;
     // Workgroup w walks the virtual workgroup ids w, w + gridDim.x, ...: ids below n_main are full
     // tiles, the rest half tiles.  (With gridDim.x >= n_main + 2 n_tail each workgroup has one id.)
     constexpr bool CAN_PREFETCH = PIPE == 2 && NSTAGE == 2;     // see gemm_dma_tile
     const int n_ids = n_main + 2 * n_tail;
     int tile_m, tile_n;
     bool prefetched = false;
-    for (int v = blockIdx.x; v < n_ids; v += gridDim.x) {
+    for (int v = first; v < n_ids; v += gridDim.x) {
         if (v < n_main) {
-            tile_of_workgroup(v, n_main, tiles_m, tiles_n, tile_m, tile_n);
+            if (banded) tile_of_logical(v, tiles_m, tiles_n, tile_m, tile_n);
+            else tile_of_workgroup(v, n_main, tiles_m, tiles_n, tile_m, tile_n);
             const int vn = v + gridDim.x;
             const bool has_next = vn < n_main;
             int next_m = 0, next_n = 0;
@@ -1357,7 +1369,10 @@ int launch_dma(const void* A, const void* B, int M, int N, int rowbytes, const f
     constexpr bool PERSISTENT = PIPE == 2 && NSTAGE == 2;
     int grid_x = n_main + 2 * n_tail;
     if (PERSISTENT && bt.count == 1 && grid_x > cus) grid_x = cus;
-    kern<<<dim3((unsigned)grid_x, (unsigned)bt.count), dim3(WM * WN * 64), smem, stream>>>(
+    // a reduction of one stage needs one stage buffer (the output is staged in it as well): twice the workgroups per CU
+    constexpr bool ONE_OK = PIPE == 1 && BM * BN * 2 <= (BM + BN) * BKB;
+    const int lds = (ONE_OK && rowbytes <= BKB) ? smem / NSTAGE : smem;
+    kern<<<dim3((unsigned)grid_x, (unsigned)bt.count), dim3(WM * WN * 64), lds, stream>>>(
         static_cast<const uint8_t*>(A), static_cast<const uint8_t*>(B), M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy,
         tiles_m, tiles_n, n_main, n_tail, bt);
     hipError_t e = hipGetLastError();
@@ -1448,8 +1463,15 @@ int dispatch(const void* A, const void* B, int M, int N, int rowbytes, const flo
         // keep two per phase, 7) from 144 / 112 tiles on; narrow outputs (N <= 128, the P V product of attention) and
         // small problems use the 128 x 128 tile (6).
         const bool deep_ok = MODE != MODE_F6 && rowbytes % 128 == 0 && bt.count == 1 && y_dtype == FQ_BF16 && !bt.bias;
+        // Batched products of one k-stage (the Q K^T of attention with heads of up to 128) are bound by their output; the
+        // 128 x 128 tile then has four workgroups per CU at work.  The ping-pong kernel is better where its tiles are whole
+        // and many: 160 x 2048 x 2048 277 against 303 us, but 12 x 2048 x 2048 28.7 / 26.5, 40 x 700 x 700 20.3 / 19.1, 96 x 333 x
+        // 1500 45.4 / 42.5; and no 256-row tile for at most 128 rows (160 x 1 x 2048 33.7 / 22.0).
+        const long long padded256 = (long long)((M + 255) / 256 * 256) * ((N + 255) / 256 * 256);
+        const long long padded128 = (long long)((M + 127) / 128 * 128) * ((N + 127) / 128 * 128);
+        const bool small_tiles = bt.count > 1 && (M <= 128 || (rowbytes <= 128 && (big_tiles < 2048 || 20 * padded256 > 21 * padded128)));
         v = 6;
-        if (N > 128) {
+        if (N > 128 && !small_tiles) {
             if (MODE == MODE_I4 && rowbytes >= 512) {
                 if (big_tiles >= 112) v = (big_tiles >= 176 && deep_ok) ? 12 : 10;
             } else if (MODE == MODE_I4) {

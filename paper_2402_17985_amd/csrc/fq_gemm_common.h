@@ -1,6 +1,8 @@
 // What the GEMM translation units share: vector types, operand modes, the clock probe, the direct global -> LDS copy, the
 // workgroup -> tile order and the epilogue (GPU code only; everything has internal linkage).
 #pragma once
+#include <type_traits>
+
 #include "fq_internal.h"
 
 namespace fq {
@@ -89,11 +91,17 @@ __device__ __forceinline__ auto convert_value(S acc, float scale, bool has_bias 
     }
 }
 
-// The four bias values of the columns col .. col + 3 (zeros when there is no bias).
-__device__ __forceinline__ v4f bias4(const float* __restrict__ bias, int col)
+// The four bias values of the columns col .. col + 3 (col a multiple of 4; zeros beyond column N).
+__device__ __forceinline__ v4f bias4(const float* __restrict__ bias, int col, int N)
 {
     v4f b = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (bias) b = *reinterpret_cast<const v4f*>(bias + col);
+    if (col + 3 < N) {
+        b = *reinterpret_cast<const v4f*>(bias + col);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (col + e < N) b[e] = bias[col + e];
+    }
     return b;
 }
 
@@ -200,7 +208,7 @@ __device__ __forceinline__ void store_tile_as(acc_t (&acc)[FM][FN], int row0, in
             for (int j = 0; j < FN; ++j)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const v4f b4 = bias4(hb ? bias : nullptr, col0 + 4 * fhalf + j * 32 + 8 * g);
+                    const v4f b4 = hb ? bias4(bias, col0 + 4 * fhalf + j * 32 + 8 * g, N) : v4f{0.0f, 0.0f, 0.0f, 0.0f};
                     vec_t v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = convert_out<MODE, YDT>(acc[i][j], 4 * g + e, scale, hb, b4[e]);
@@ -223,31 +231,38 @@ __device__ __forceinline__ void store_tile_as(acc_t (&acc)[FM][FN], int row0, in
     }
 }
 
-// 2-byte outputs of an interior tile go through a wave-private LDS staging area so that global
-// memory sees full 128-byte row segments: the wave writes its tile as [row][column] (16-byte units
-// XOR-swizzled with the row to spread banks), reads it back 16 bytes per lane, and stores 16 bytes
-// per lane with 64/UNITS complete rows per instruction.  `stage` must hold FM*32 x FN*32 x 2 bytes.
-template <int MODE, int YDT, int FM, int FN, bool hb = false, int CH = FM, typename acc_t>
-__device__ __forceinline__ void store_tile_via_lds(acc_t (&acc)[FM][FN], int row0, int col0, float scale,
+// 16 bytes of a row of 2- or 4-byte elements: the vector type of an unaligned store (global memory takes any alignment).
+struct __attribute__((packed, aligned(2))) Bytes16 { v4i v; };
+
+// A wave's tile goes out through a wave-private LDS staging area so that global memory sees row segments: the wave writes
+// its accumulators as [row][column] (16-byte units XOR-swizzled with the row to spread banks), reads them back 16 bytes
+// per lane, and stores 16 bytes per lane, 64/UNITS rows per instruction.  `stage` must hold CH*32 rows of FN*32
+// elements.  Tiles that reach beyond the matrix drop what lies outside; rows may start at any element.  (Stored straight
+// from the accumulator layout, a store instruction touches 32 rows: with an odd row length, element by element, an 8192
+// x 4095 bf16 output took 75 us longer than an 8192 x 4096 one.)
+template <int MODE, int YDT, int FM, int FN, bool hb, int CH, typename acc_t>
+__device__ __forceinline__ void store_tile_via_lds(acc_t (&acc)[FM][FN], int row0, int col0, int M, int N, float scale,
                                                    void* __restrict__ Y, int ldy, uint8_t* stage,
                                                    const float* __restrict__ bias = nullptr)
 {
     // CH = 32-row blocks staged at a time: `stage` holds CH*32 rows and is reused FM/CH times (the
     // LDS operations of one wave execute in order, so a chunk's reads precede the next chunk's writes)
-    typedef typename OutVec<YDT>::type vec_t;              // 4 x 2 bytes
-    constexpr int ROWB = FN * 32 * 2;                      // bytes per staged row
-    constexpr int UNITS = ROWB / 16;
+    typedef typename OutVec<YDT>::type vec_t;
+    constexpr int ES = sizeof(vec_t) / 4;                  // bytes per element
+    constexpr int ROWB = FN * 32 * ES;                     // bytes per staged row
+    constexpr int UNITS = ROWB / 16, PER = 16 / ES;        // 16-byte units per row, elements per unit
     constexpr int SW = (UNITS >= 8 ? 8 : UNITS) - 1;
-    // the swizzle advances once per 256 bytes of staged rows, so that the 8-byte writes of 32 lanes (one
+    // the swizzle advances once per 256 bytes of staged rows, so that the 8- or 16-byte writes of 32 lanes (one
     // row each) spread over all 16-byte units of the 64 banks
     constexpr int SWS = (ROWB >= 256) ? 0 : (ROWB == 128 ? 1 : 2);
     constexpr int ROWS_PER_INSTR = 64 / UNITS;
-    static_assert(sizeof(vec_t) == 8 && (CH * 32) % ROWS_PER_INSTR == 0 && FM % CH == 0, "staging layout");
+    static_assert(UNITS <= 64 && (CH * 32) % ROWS_PER_INSTR == 0 && FM % CH == 0, "staging layout");
     const int lane = epilogue_lane();
     const int frow = lane & 31, fhalf = lane >> 5;
     uint8_t* Yb = static_cast<uint8_t*>(Y);
     const int mr = lane / UNITS, us = lane % UNITS;
-    const bool whole_lines = (ldy & 63) == 0 && (col0 & 63) == 0 && (reinterpret_cast<uintptr_t>(Y) & 127) == 0;
+    const bool whole_lines = row0 + FM * 32 <= M && col0 + FN * 32 <= N && (ldy * ES & 127) == 0 && (col0 * ES & 127) == 0 &&
+                             (reinterpret_cast<uintptr_t>(Y) & 127) == 0;
 #pragma unroll
     for (int c = 0; c < FM / CH; ++c) {
 #pragma unroll
@@ -258,36 +273,45 @@ __device__ __forceinline__ void store_tile_via_lds(acc_t (&acc)[FM][FN], int row
             for (int j = 0; j < FN; ++j)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const v4f b4 = bias4(hb ? bias : nullptr, col0 + 4 * fhalf + j * 32 + 8 * g);
+                    const v4f b4 = hb ? bias4(bias, col0 + 4 * fhalf + j * 32 + 8 * g, N) : v4f{0.0f, 0.0f, 0.0f, 0.0f};
                     vec_t v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = convert_out<MODE, YDT>(acc[i][j], 4 * g + e, scale, hb, b4[e]);
-                    const int u = g + 4 * j;
-                    *reinterpret_cast<vec_t*>(stage + m * ROWB + ((u ^ ((m >> SWS) & SW)) << 4) + 8 * fhalf) = v;
+                    const int u = ES == 2 ? g + 4 * j : 8 * j + 2 * g + fhalf;
+                    *reinterpret_cast<vec_t*>(stage + m * ROWB + ((u ^ ((m >> SWS) & SW)) << 4) + (ES == 2 ? 8 * fhalf : 0)) = v;
                 }
         }
         // The output is written once and not read by this kernel: a streaming store keeps it from
         // displacing the operand panels in L2 -- but only when the 128-byte row segments are whole cache
         // lines; partial-line streaming stores are several times slower than ordinary ones.  (Two loops
         // kept apart: merged, they become one ordinary store.)
-        uint8_t* ybase = Yb + ((size_t)(row0 + c * CH * 32) * ldy + col0) * 2;
+        const int rbase = row0 + c * CH * 32;
         if (whole_lines) {
+            uint8_t* ybase = Yb + ((size_t)rbase * ldy + col0) * ES;
             asm volatile("; streaming stores begin");    // the markers keep the two arms from being merged
 #pragma unroll
             for (int t = 0; t < CH * 32 / ROWS_PER_INSTR; ++t) {
                 const int m = t * ROWS_PER_INSTR + mr;
                 const int u = us ^ ((m >> SWS) & SW);
                 const v4i d = *reinterpret_cast<const v4i*>(stage + m * ROWB + (us << 4));
-                __builtin_nontemporal_store(d, reinterpret_cast<v4i*>(ybase + (size_t)m * ldy * 2 + (u << 4)));
+                __builtin_nontemporal_store(d, reinterpret_cast<v4i*>(ybase + (size_t)m * ldy * ES + (u << 4)));
             }
             asm volatile("; streaming stores end");
         } else {
-#pragma unroll
+            typedef decltype(convert_out<MODE, YDT>(acc[0][0], 0, scale)) elem_t;
+#pragma unroll 4
             for (int t = 0; t < CH * 32 / ROWS_PER_INSTR; ++t) {
                 const int m = t * ROWS_PER_INSTR + mr;
-                const int u = us ^ ((m >> SWS) & SW);
-                const v4i d = *reinterpret_cast<const v4i*>(stage + m * ROWB + (us << 4));
-                *reinterpret_cast<v4i*>(ybase + (size_t)m * ldy * 2 + (u << 4)) = d;
+                const int row = rbase + m, col = col0 + (us ^ ((m >> SWS) & SW)) * PER;
+                const uint8_t* sp = stage + m * ROWB + (us << 4);
+                if (row < M && col < N) {
+                    elem_t* y = reinterpret_cast<elem_t*>(Yb) + (size_t)row * ldy + col;
+                    if (col + PER <= N) {
+                        reinterpret_cast<Bytes16*>(y)->v = *reinterpret_cast<const v4i*>(sp);
+                    } else {
+                        for (int e = 0; col + e < N; ++e) y[e] = reinterpret_cast<const elem_t*>(sp)[e];
+                    }
+                }
             }
         }
     }
@@ -300,36 +324,39 @@ __device__ __forceinline__ void store_tile(acc_t (&acc)[FM][FN], int row0, int c
                                            void* __restrict__ Y, int y_dtype, int ldy, uint8_t* stage = nullptr,
                                            const float* __restrict__ bias = nullptr)
 {
-    const bool fast = row0 + FM * 32 <= M && col0 + FN * 32 <= N && (ldy & 3) == 0 &&
-                      (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
-    const bool staged = fast && stage != nullptr && (ldy & 7) == 0 && (col0 & 7) == 0;
-    if constexpr (MODE == MODE_BF16) {
-        if (staged) store_tile_via_lds<MODE, FQ_BF16, FM, FN, false, CH>(acc, row0, col0, 1.0f, Y, ldy, stage);
-        else store_tile_as<MODE, FQ_BF16, FM, FN>(acc, row0, col0, M, N, 1.0f, Y, ldy, fast);
+    // 2-byte outputs are staged CH blocks at a time, 4-byte ones half as many; without room for that (or without a
+    // staging area) they leave straight from the accumulator layout
+    auto put = [&](auto ydt, auto has_bias) {
+        constexpr int YDT = decltype(ydt)::value;
+        constexpr bool HB = decltype(has_bias)::value;
+        constexpr int ES = sizeof(typename OutVec<YDT>::type) / 4, CHS = ES == 2 ? CH : CH / 2;
+        const float sc = (MODE == MODE_BF16 || YDT == FQ_I32) ? 1.0f : scale;
+        if constexpr (CHS >= 1) {
+            if (stage) {
+                store_tile_via_lds<MODE, YDT, FM, FN, HB, CHS>(acc, row0, col0, M, N, sc, Y, ldy, stage, bias);
+                return;
+            }
+        }
+        const bool fast = row0 + FM * 32 <= M && col0 + FN * 32 <= N && (ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
+        store_tile_as<MODE, YDT, FM, FN, HB>(acc, row0, col0, M, N, sc, Y, ldy, fast, bias);
+    };
+    typedef std::integral_constant<int, FQ_BF16> bf16_t;
+    typedef std::integral_constant<int, FQ_F16> f16_t;
+    typedef std::integral_constant<int, FQ_F32> f32_t;
+    typedef std::integral_constant<int, FQ_I32> i32_t;
+    if constexpr (MODE == MODE_BF16 || ONLY_BF16) {
+        put(bf16_t{}, std::false_type{});
+    } else if (y_dtype == FQ_I32) {
+        put(i32_t{}, std::false_type{});
+    } else if (bias) {
+        // the biased epilogue is a separate instantiation so that the plain one carries none of it
+        if (y_dtype == FQ_BF16) put(bf16_t{}, std::true_type{});
+        else if (y_dtype == FQ_F16) put(f16_t{}, std::true_type{});
+        else put(f32_t{}, std::true_type{});
     } else {
-        if constexpr (ONLY_BF16) {
-            if (staged) store_tile_via_lds<MODE, FQ_BF16, FM, FN, false, CH>(acc, row0, col0, scale, Y, ldy, stage);
-            else store_tile_as<MODE, FQ_BF16, FM, FN>(acc, row0, col0, M, N, scale, Y, ldy, fast);
-            return;
-        }
-        if (y_dtype == FQ_I32) {
-            store_tile_as<MODE, FQ_I32, FM, FN>(acc, row0, col0, M, N, 1.0f, Y, ldy, fast);
-            return;
-        }
-        if (bias) {
-            // the biased epilogue is a separate instantiation so that the plain one carries none of it
-            if (staged && y_dtype == FQ_BF16) store_tile_via_lds<MODE, FQ_BF16, FM, FN, true, CH>(acc, row0, col0, scale, Y, ldy, stage, bias);
-            else if (staged && y_dtype == FQ_F16) store_tile_via_lds<MODE, FQ_F16, FM, FN, true, CH>(acc, row0, col0, scale, Y, ldy, stage, bias);
-            else if (y_dtype == FQ_BF16) store_tile_as<MODE, FQ_BF16, FM, FN, true>(acc, row0, col0, M, N, scale, Y, ldy, fast, bias);
-            else if (y_dtype == FQ_F16) store_tile_as<MODE, FQ_F16, FM, FN, true>(acc, row0, col0, M, N, scale, Y, ldy, fast, bias);
-            else store_tile_as<MODE, FQ_F32, FM, FN, true>(acc, row0, col0, M, N, scale, Y, ldy, fast, bias);
-            return;
-        }
-        if (staged && y_dtype == FQ_BF16) store_tile_via_lds<MODE, FQ_BF16, FM, FN, false, CH>(acc, row0, col0, scale, Y, ldy, stage);
-        else if (staged && y_dtype == FQ_F16) store_tile_via_lds<MODE, FQ_F16, FM, FN, false, CH>(acc, row0, col0, scale, Y, ldy, stage);
-        else if (y_dtype == FQ_BF16) store_tile_as<MODE, FQ_BF16, FM, FN>(acc, row0, col0, M, N, scale, Y, ldy, fast);
-        else if (y_dtype == FQ_F16) store_tile_as<MODE, FQ_F16, FM, FN>(acc, row0, col0, M, N, scale, Y, ldy, fast);
-        else store_tile_as<MODE, FQ_F32, FM, FN>(acc, row0, col0, M, N, scale, Y, ldy, fast);
+        if (y_dtype == FQ_BF16) put(bf16_t{}, std::false_type{});
+        else if (y_dtype == FQ_F16) put(f16_t{}, std::false_type{});
+        else put(f32_t{}, std::false_type{});
     }
 }
 

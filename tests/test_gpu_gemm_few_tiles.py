@@ -85,3 +85,39 @@ def test_batched(batch, M, N, K, bits):
     (fq.fq_bmm_i8 if bits == 8 else fq.fq_bmm_i4)(X.view(batch, M, -1), W.view(batch, N, -1), None, None, Y)
     want = torch.bmm(xq.view(batch, M, K).double(), wq.view(batch, N, K).double().transpose(1, 2).contiguous())
     assert torch.equal(Y.double(), want)
+
+
+# Outputs of the tiled kernels whose rows start at any element or that end inside a tile.  (variant, storage): 2 stores from
+# the accumulator layout and is the reference; the others stage rows through LDS.
+@pytest.mark.parametrize("ydt", [torch.int32, torch.float32, torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("variant,bits,K", [(6, 8, 256), (6, 4, 96), (7, 8, 160), (10, 4, 1024), (11, 8, 256), (12, 8, 384), (12, 4, 512), (6, 6, 256)])
+@pytest.mark.parametrize("M,N,pad,shift", [(256, 256, 0, 0), (257, 255, 0, 0), (511, 513, 3, 0), (130, 1001, 0, 8), (300, 264, 8, 0), (128, 640, 64, 4)])
+def test_ragged_outputs_of_the_tiled_kernels(M, N, pad, shift, variant, bits, K, ydt):
+    rng = np.random.default_rng(M * N)
+    _, X = _operand(rng, M, K, bits)
+    _, W = _operand(rng, N, K, bits)
+    kind = torch.int16 if ydt in (torch.float16, torch.bfloat16) else torch.int32
+    for bias in (None,) if ydt == torch.int32 else (None, torch.from_numpy(rng.standard_normal(N, dtype=np.float32)).to(DEV)):
+        out = []
+        for v in (variant, 2 if bits != 6 else -1):
+            buf = torch.full((M * (N + pad) + 2 * shift,), 7, dtype=ydt, device=DEV)     # shift: Y not on a cache line
+            Y = buf[shift:shift + M * (N + pad)].view(M, N + pad)[:, :N]
+            fq.fq_gemm_select(v)
+            try:
+                _gemm(bits, X, W, scalar(0.013), scalar(0.0021), bias, Y)
+            finally:
+                fq.fq_gemm_select(-1)
+            out.append(buf)
+        assert torch.equal(out[0].view(kind), out[1].view(kind))                         # nothing outside Y is touched
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("batch,M,N,K", [(5, 333, 150, 64), (3, 700, 701, 96), (150, 1, 300, 128), (9, 256, 129, 1024)])
+def test_batched_tiles_and_their_order(batch, M, N, K, bits):
+    rng = np.random.default_rng(M)
+    xq, X = _operand(rng, batch * M, K, bits)
+    wq, W = _operand(rng, batch * N, K, bits)
+    Y = torch.full((batch, M, N), -1, dtype=torch.int32, device=DEV)
+    (fq.fq_bmm_i8 if bits == 8 else fq.fq_bmm_i4)(X.view(batch, M, -1), W.view(batch, N, -1), None, None, Y)
+    want = torch.bmm(xq.view(batch, M, K).double(), wq.view(batch, N, K).double().transpose(1, 2).contiguous())
+    assert torch.equal(Y.double(), want)
