@@ -525,6 +525,8 @@ int fq_linear_bias(const void* X, int x_dtype, int M, int K, int ldx, const int3
     rc = check_bias(bias, y_dtype);
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (forced_gemm_variant() < 0 && linear_decode_fits(M, N, K, Kpad, bits))
+        return launch_linear_decode(X, x_dtype, K, src_idx, rep, Kpad, bits, absmax_in, Wq, N, s_w, bias, Y, y_dtype, ldy, st);
     rc = launch_flatten_quant(X, x_dtype, M, K, ldx, src_idx, rep, Kpad, bits, absmax_in ? 1 : 0, absmax_in, Xq,
                               s_x, ws, st);
     if (rc) return rc;

@@ -47,6 +47,8 @@ int launch_flatten_quant(const void* X, int x_dtype, int M, int K, int ld,
                          int mode, const float* absmax_in, void* out, float* scale_out,
                          const ActWorkspace& ws, hipStream_t stream, float T = 0.0f);
 
+bool quantizer_takes_e3m2(int K, int Kpad);   // layers for which E3M2 storage exists (equal split, weights)
+
 // chmax[j] = max(start, max_i |X[i, j]|), start = 0 or (accumulate) the non-negative value held on entry
 int launch_channel_absmax(const void* X, int x_dtype, int M, int K, int ld, int accumulate, float* chmax,
                           hipStream_t stream);
@@ -94,6 +96,12 @@ int check_forced_variant(int bits, int rowbytes);   // FQ_OK unless the forced v
 int launch_gemm_int(const void* Xq, const void* Wq, int M, int N, int Kpad, int bits,
                     const float* s_x, const float* s_w, void* Y, int y_dtype, int ldy,
                     hipStream_t stream, const float* bias = nullptr);
+
+// The equal-split layer (fq_linear) for one row in one kernel; linear_decode_fits says which layers it takes
+bool linear_decode_fits(int M, int N, int K, int Kpad, int bits);
+int launch_linear_decode(const void* X, int x_dtype, int K, const int32_t* src, const int32_t* rep, int Kpad, int bits,
+                         const float* absmax_in, const void* W, int N, const float* s_w, const float* bias, void* Y, int y_dtype,
+                         int ldy, hipStream_t stream);
 
 // `batch` independent products; operand strides in bytes, stride_y_bytes in bytes
 int launch_bmm_int(const void* Aq, const void* Bq, int batch, int M, int N, int Kpad, int bits, size_t stride_a,
