@@ -668,6 +668,11 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
         }
     };
     load_strip(row_begin);
+    // the static bound, or this thread's share of the candidates: on their way while the map is worked out
+    float best = 0.0f;
+    if (absmax_in) best = *absmax_in;
+    else if (cand)
+        for (int c = tid; c < ncand; c += nthr) best = fmaxf(best, cand[c]);
 
     // bytes of an output row and of one group of 16 slots: 16 (INT8), 8 (INT4 nibbles), 12 (E3M2 codes)
     constexpr int GB = (BITS == 8) ? 16 : (BITS == 4 ? 8 : 12);
@@ -694,6 +699,7 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
     // ---- the map ----
     uint32_t nb[P][4];                                         // copy counts of this thread's plain groups, as bytes
     int plain = 0;
+    bool other = false;                                        // a group that is neither plain nor copies of plain ones
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const int g = tid + p * nthr;
@@ -711,6 +717,38 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
                 for (int i = 0; i < 16; ++i) nb[p][i >> 2] |= (uint32_t)nv[i] << (8 * (i & 3));
             }
             *reinterpret_cast<v4u*>(qs + (g << 4)) = v4u{nb[p][0], nb[p][1], nb[p][2], nb[p][3]};
+            other = other || !ok;
+        }
+    }
+    // a' from all of X (few rows): the plain groups' part, the largest exact quotient |x| / n compared by cross
+    // multiplication in float64 (exact for n < 2^29) and divided once; rounding is monotonic
+    const bool self = !absmax_in && !cand;
+    float bc = 0.0f;
+    int bn = 1;
+    auto consider = [&](float v, int n) {
+        if ((double)v * (double)bn > (double)bc * (double)n) {
+            bc = v;
+            bn = n;
+        }
+    };
+    if (self) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            if (!((plain >> p) & 1)) continue;
+            float mx[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) mx[i] = 0.0f;
+            const T* xp = X + ((tid + p * nthr) << 4);
+#pragma unroll 4
+            for (int r = 0; r < M; ++r, xp += ld) {
+                float x[16];
+#pragma unroll
+                for (int i = 0; i < NV; ++i) widen16<DT>(reinterpret_cast<const v4u*>(xp)[i], x + i * VEC);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) mx[i] = fmaxf(mx[i], fabsf(x[i]));
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) consider(mx[i], (nb[p][i >> 2] >> (8 * (i & 3))) & 0xff);
         }
     }
     __syncthreads();
@@ -731,58 +769,33 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
             w[i >> 1] |= (in ? (uint32_t)j[i] : 0xffffu) << (16 * (i & 1));
         }
         *reinterpret_cast<v4u*>(ts + t) = v4u{w[0], w[1], w[2], w[3]};
-        const int mine = copyable ? 1 : 0, other = __shfl_xor(mine, 1, 64);
-        if ((tid & 1) == 0) tf[t >> 4] = (uint8_t)(mine & other);
+        const int mine = copyable ? 1 : 0, both = mine & __shfl_xor(mine, 1, 64);
+        if ((tid & 1) == 0) tf[t >> 4] = (uint8_t)both;
+        other = other || !both;
     }
-    __syncthreads();
+    const bool others = __syncthreads_or(other ? 1 : 0) != 0;
 
     // ---- a' and the table of multipliers ----
     float a;
     if (absmax_in) {
-        a = *absmax_in;
+        a = best;
         if (!(a >= 0.0f) || a > 3.0e38f) a = 0.0f;             // negative / NaN / Inf static bound: treated as 0
     } else {
-        float best = 0.0f;
-        // the float64 quotient rounded to fp32 is the correctly rounded fp32 quotient
-        auto quotient = [&](float c, int n) { best = fmaxf(best, n == 1 ? c : (float)((double)c / (double)n)); };
-        if (cand) {
-            for (int c = tid; c < ncand; c += nthr) best = fmaxf(best, cand[c]);
-        } else {
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                const int g = tid + p * nthr;
-                if ((plain >> p) & 1) {
-                    float mx[16];
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) mx[i] = 0.0f;
-                    const T* xp = X + (g << 4);
-#pragma unroll 4
-                    for (int r = 0; r < M; ++r, xp += ld) {
-                        float x[16];
-#pragma unroll
-                        for (int i = 0; i < NV; ++i) widen16<DT>(reinterpret_cast<const v4u*>(xp)[i], x + i * VEC);
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) mx[i] = fmaxf(mx[i], fabsf(x[i]));
-                    }
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) quotient(mx[i], (nb[p][i >> 2] >> (8 * (i & 3))) & 0xff);
-                }
-            }
+        if (self) {
             // the slots of every other group (head groups that are not plain, appended groups that do not repeat plain
-            // ones); plain groups and their copies have been seen above
-            for (int q = tid; q < G * 16; q += nthr) {
+            // ones), one by one; plain groups and their copies have been seen above
+            for (int q = tid; others && q < G * 16; q += nthr) {
                 const int g = q >> 4;
-                bool seen;
-                if (g < NH) seen = qs[g << 4] != 0;
-                else seen = tf[g - NH] != 0;
+                const bool seen = g < NH ? qs[g << 4] != 0 : tf[g - NH] != 0;
                 if (seen) continue;
                 const int j = src[q], n = counted ? rep[q] : 1;
                 if ((unsigned)j >= (unsigned)K || n <= 0) continue;
                 float mx = 0.0f;
 #pragma unroll 8
                 for (int r = 0; r < M; ++r) mx = fmaxf(mx, fabsf(Elem<DT>::widen(X[(size_t)r * ld + j])));
-                quotient(mx, n);
+                consider(mx, n);
             }
+            best = (float)((double)bc / (double)bn);
         }
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
