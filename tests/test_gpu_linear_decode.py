@@ -75,3 +75,27 @@ def test_maps_that_are_not_the_planners(static, bits):
     rep[tail] = rng.integers(1, 5, tail.size)
     src[tail[7]] = K + 5
     _compare(X, src, rep, W, bits, scalar(3.0) if static else None, torch.float16, None)
+
+
+@pytest.mark.parametrize("M,N,bits", [(1, 300, 8), (1, 9000, 4), (16, 5000, 4), (70, 4000, 8), (500, 1000, 6)])
+def test_replayed_from_a_graph(M, N, bits):
+    """The kernels for few rows and few tiles inside a captured graph, replayed between eager work on other data."""
+    rng = np.random.default_rng(M)
+    K = 1024
+    X = _x(rng, M, K, "bf16").contiguous()
+    W = torch.from_numpy(rng.standard_normal((N, K), dtype=np.float32)).to(DEV).to(torch.bfloat16)
+    layer = fq.FqLinear(W, X.float().abs().amax(dim=0).cpu().numpy(), 4.0, bits, device=DEV)
+    Y = torch.zeros((M, N), dtype=torch.bfloat16, device=DEV)
+    layer.forward(X, Y)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        layer.forward(X, Y)
+    for _ in range(3):
+        X.copy_(_x(rng, M, K, "bf16"))
+        want = layer.forward(X).clone()
+        Y.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y.view(torch.int16), want.view(torch.int16))
