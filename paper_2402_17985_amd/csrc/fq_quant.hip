@@ -409,7 +409,7 @@ __global__ __launch_bounds__(256) void flatten_quant_kernel(const void* __restri
 // made of such slots and padding (cflag) is copied from LDS; any other group is gathered from global
 // memory and quantized with its own multipliers.
 template <int DT, int BITS>
-__global__ __launch_bounds__(BITS == 6 ? 512 : 256) void flatten_quant_rows_kernel(const void* __restrict__ Xv, int M, int K, int ld,
+__global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __restrict__ Xv, int M, int K, int ld,
                                                                  const int32_t* __restrict__ src,
                                                                  const float* __restrict__ mslot,
                                                                  const uint8_t* __restrict__ gflag, int Kpad, int R,
@@ -1090,8 +1090,12 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
         while (R > 1 && (size_t)R * kq + tail_src > 64u * 1024u) R >>= 1;
         const size_t lds = (size_t)R * kq + tail_src;
         const unsigned nblk = (unsigned)((M + R - 1) / R);
-        // 256 threads walk the strip's groups (larger workgroups, one thread per head group, measured slower)
-        const int nthr = 256;
+        // 256 threads walk the strip's groups while the LDS lets four such workgroups share a CU (16 waves to hide the
+        // loads).  Strips cut to two rows or one whose LDS admits only two or three get 512 threads (us, 256 -> 512):
+        // weight 5120 x 20480 to nibbles 105.0 -> 98.5, activation 8192 x 22016 to INT8 147 -> 133, 8192 x 28672
+        // 195 -> 163.  With four workgroups 512 threads lose: 8192 x 16384 99 -> 102, 8192 x 36000 230 -> 242, weight
+        // 8192 x 28672 255 -> 275; on higher strips they lose or gain little: 8192 x 11008 nibbles 78.5 -> 80.4.
+        const int nthr = (R <= 2 && lds > 160u * 1024u / 4) ? 512 : 256;
         if (bits == 8)
             flatten_quant_rows_kernel<DT, 8><<<nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad, R, o8);
         else if (bits == 6) {
@@ -1101,7 +1105,7 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
             // the same change was 16 % slower, so it stops there.
             int R6 = R;
             size_t lds6 = lds;
-            int nthr6 = nthr;
+            int nthr6 = 256;
             if (R <= 2 && (size_t)(2 * R) * kq + tail_src <= 128u * 1024u) {
                 R6 = 2 * R;
                 lds6 = (size_t)R6 * kq + tail_src;

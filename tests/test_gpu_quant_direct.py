@@ -65,6 +65,16 @@ def test_planned_maps(dtype, M, K, bits, static):
     _check(X, dtype, src, rep, bits, T if static else None)
 
 
+# More elements than the one-kernel form takes, the last strip short: strips of four rows, and of two rows and one on both
+# sides of the LDS size from which 512 threads walk them
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("dtype,M,K,bits", [
+    ("bf16", 1055, 12000, 8), ("bf16", 745, 17000, 4), ("bf16", 285, 45000, 8), ("bf16", 621, 20480, 4), ("bf16", 621, 20480, 8), ("f32", 603, 21000, 8), ("f16", 421, 30016, 4),
+])
+def test_wide_strips(dtype, M, K, bits, static):
+    test_planned_maps(dtype, M, K, bits, static)
+
+
 @pytest.mark.parametrize("static", [False, True])
 @pytest.mark.parametrize("bits", [8, 4, 6])
 @pytest.mark.parametrize("M,K", [(9, 200), (40, 4000), (200, 1200)])
