@@ -266,12 +266,13 @@ __global__ __launch_bounds__(1024) void scale_kernel(const float* __restrict__ c
     if (p < Kpad && (tid & 15) == 0) gflag[p >> 4] = (((bal >> (tid & 48)) & 0xffffull) == 0xffffull) ? 1 : 0;
     // cflag[g] = 1 when every slot of group g either holds 0 whatever the input (padding) or repeats a
     // channel j < 16 * (K / 16) whose own slot j is the identity slot with the same copy count: the
-    // slot's quantized value then equals slot j's and can be copied instead of recomputed
+    // slot's quantized value then equals slot j's and can be copied instead of recomputed.  (A map may have fewer slots
+    // than there are channels: channel j then has no slot j.)
     bool copyable = false;
     if (p < Kpad) {
         const int j = src[p];
         if ((unsigned)j >= (unsigned)K) copyable = true;
-        else if (j < ((K >> 4) << 4) && src[j] == j) copyable = (mode == 2) || (rep[p] > 0 && rep[j] == rep[p]);
+        else if (j < min((K >> 4) << 4, Kpad) && src[j] == j) copyable = (mode == 2) || (rep[p] > 0 && rep[j] == rep[p]);
     }
     const unsigned long long balc = __ballot(copyable);
     // ... and 2 when, in addition, all 16 slots repeat the same channel (the long runs of a large

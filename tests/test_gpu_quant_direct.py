@@ -119,3 +119,18 @@ def test_weights(N, K, bits):
     torch.cuda.synchronize()
     assert np.float32(s_w.item()) == s_ref
     np.testing.assert_array_equal(out.cpu().numpy().reshape(-1), _packed(want, bits).reshape(-1))
+
+
+# A map that drops channels has fewer slots than X has columns: no kernel may look a channel's own slot up beyond its end.
+# (Kpad, K): slots and columns, up to 4 MiB of map apart.
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("dtype,M,K,Kpad,bits", [("f32", 5, 40, 32, 8), ("bf16", 33, 5000, 64, 4), ("f16", 700, 20000, 96, 8), ("bf16", 3, 200000, 256, 8),
+                                                 ("f32", 2, 262144, 128, 4), ("bf16", 2, 524288, 256, 8)])
+def test_fewer_slots_than_channels(dtype, M, K, Kpad, bits, static):
+    rng = np.random.default_rng(K)
+    X = rng.standard_normal((M, K), dtype=np.float32)
+    src = rng.integers(0, K, Kpad).astype(np.int32)
+    src[:5] = [0, 1, K - 1, K - 2, K - 1]
+    src[-2:] = -1
+    rep = np.where(src >= 0, rng.integers(1, 4, Kpad), 0).astype(np.int32)
+    _check(X, dtype, src, rep, bits, 2.5 if static else None)
