@@ -39,7 +39,8 @@ def _newer(target, deps):
 
 def build(force: bool = True, verbose: bool = False) -> str:
     hdrs = [os.path.join(CSRC, "fq_internal.h"), os.path.join(CSRC, "fq_gemm_common.h"),
-            os.path.join(CSRC, "fq_gemm_skinny.h"), os.path.join(CSRC, "fq_quant_common.h"), os.path.join(HERE, "..", "include", "fq.h"),
+            os.path.join(CSRC, "fq_gemm_skinny.h"), os.path.join(CSRC, "fq_quant_common.h"), os.path.join(CSRC, "fq_rules.h"),
+            os.path.join(HERE, "..", "include", "fq.h"),
             os.path.join(HERE, "..", "include", "fq_peak.h")]
     srcs = [(os.path.join(CSRC, s), extra, obj) for s, extra, obj in SOURCES]
     if not force and _newer(OUT, [s for s, _, _ in srcs] + hdrs):

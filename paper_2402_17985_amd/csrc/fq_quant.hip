@@ -26,6 +26,7 @@
 
 #include "fq_internal.h"
 #include "fq_quant_common.h"
+#include "fq_rules.h"
 
 namespace fq {
 namespace {
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(256) void colabsmax_kernel(const void* __restrict__
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r0 = blockIdx.y * rows_per_block;
     float mx[VEC];
-    strip_colmax<DT>(static_cast<const typename Elem<DT>::type*>(Xv), K, ld, r0, min(M, r0 + rows_per_block),
+    strip_colmax<DT>(static_cast<const typename Elem<DT>::type*>(Xv), K, ld, r0, r0 + min(M - r0, rows_per_block),
                      (blockIdx.x * 64 + lane) * VEC, wave, mx);
 #pragma unroll
     for (int v = 0; v < VEC; ++v) part[wave][lane * VEC + v] = mx[v];
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(ALL ? 256 : 512) void tensor_absmax_kernel(const vo
     float best = 0.0f;
     if (wave < 4) {
         float mx[VEC];
-        strip_colmax<DT>(static_cast<const typename Elem<DT>::type*>(Xv), K, ld, r0, min(M, r0 + rows_per_block),
+        strip_colmax<DT>(static_cast<const typename Elem<DT>::type*>(Xv), K, ld, r0, r0 + min(M - r0, rows_per_block),
                          c0 + lane * VEC, wave, mx);
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
@@ -195,11 +196,11 @@ __global__ __launch_bounds__(ALL ? 256 : 512) void tensor_absmax_kernel(const vo
 }
 
 // ---------------------------------------------------------------------------------------------
-// per-tensor absmax, scale and per-slot multipliers (one workgroup)
+// per-tensor absmax, scale and per-slot multipliers (a workgroup per 1024 slots)
 // ---------------------------------------------------------------------------------------------
-// Every workgroup takes the maximum of the candidates of tensor_absmax_kernel (at most 1024: one load per thread; none
-// when the bound is static), tabulates the multipliers m(n) = fl32(qmax / (n * a')) for n < 1024 in LDS (one float64
-// division per thread), and fills its own 1024 slots of mslot.  Workgroup 0 also writes the scale.
+// Every workgroup takes the maximum of the candidates of tensor_absmax_kernel (one load per thread, unless the matrix has
+// more than 1024 column blocks; none when the bound is static), tabulates the multipliers m(n) = fl32(qmax / (n * a')) for
+// n < 1024 in LDS (one float64 division per thread), and fills its own 1024 slots of mslot.  Workgroup 0 also writes the scale.
 __global__ __launch_bounds__(1024) void scale_kernel(const float* __restrict__ cand, int ncand, int K,
                                                      const int32_t* __restrict__ src,
                                                      const int32_t* __restrict__ rep, int Kpad, int qmax,
@@ -215,7 +216,8 @@ __global__ __launch_bounds__(1024) void scale_kernel(const float* __restrict__ c
         a = *absmax_in;
         if (!(a >= 0.0f) || a > 3.0e38f) a = 0.0f;     // negative / NaN / Inf static bound: treated as 0
     } else {
-        float best = (tid < ncand) ? cand[tid] : 0.0f;
+        float best = 0.0f;
+        for (int c = tid; c < ncand; c += 1024) best = fmaxf(best, cand[c]);
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
         if ((tid & 63) == 0) red[tid >> 6] = best;
@@ -979,27 +981,20 @@ void launch_colabsmax(const void* X, int M, int K, int ld, bool accumulate, uint
     colabsmax_kernel<DT><<<grid, 256, 0, stream>>>(X, M, K, ld, (int)rpb, cmax);
 }
 
-// Candidates for a' of the flattened tensor (or, all_channels, of the whole array) into cand; returns their number, at
-// most 1024 and at most what the K floats of the workspace hold.
+// Candidates for a' of the flattened tensor (or, all_channels, of the whole array) into cand, which holds the K floats of
+// the workspace; their number goes to *ncand.
 template <int DT>
 int launch_tensor_absmax(const void* X, int M, int K, int ld, const int32_t* src, const int32_t* rep, int Kpad,
-                         bool all_channels, float* cand, hipStream_t stream)
+                         bool all_channels, float* cand, int* ncand, hipStream_t stream)
 {
-    constexpr int VEC = Elem<DT>::VEC;
-    const int bx = (K + 64 * VEC - 1) / (64 * VEC);
-    const int cap = std::min(1024, (int)(round_up((size_t)K * 4, 256) / 4));
-    // Strips of 64 rows (16 loads in flight for each of the four waves) while that gives at most 512 workgroups, then
-    // higher ones.  Odd multiples of 64: with a power-of-two row stride, strips that start a power-of-two number of rows
-    // apart hit the same memory channels (16384 x 8192 bf16: 54 us at 576 rows, 59 us at 512).
-    long long rpb = ((long long)M * bx + 511) / 512;
-    rpb = std::max(64LL, (rpb + 63) / 64 * 64);
-    if (rpb > 64 && (rpb / 64) % 2 == 0) rpb += 64;
-    while ((M + rpb - 1) / rpb * bx > cap) rpb *= 2;
-    const int strips = (int)((M + rpb - 1) / rpb);
-    const dim3 grid(bx, (unsigned)strips);
-    if (all_channels) tensor_absmax_kernel<DT, true><<<grid, 256, 0, stream>>>(X, M, K, ld, (int)rpb, src, rep, Kpad, cand);
-    else tensor_absmax_kernel<DT, false><<<grid, 512, 0, stream>>>(X, M, K, ld, (int)rpb, src, rep, Kpad, cand);
-    return strips * bx;
+    const AbsmaxGrid a = absmax_grid(M, K, Elem<DT>::VEC, (long long)(round_up((size_t)K * 4, 256) / 4));
+    const dim3 grid((unsigned)a.blocks, (unsigned)a.strips);
+    if (all_channels) tensor_absmax_kernel<DT, true><<<grid, 256, 0, stream>>>(X, M, K, ld, a.rows_per_strip, src, rep, Kpad, cand);
+    else tensor_absmax_kernel<DT, false><<<grid, 512, 0, stream>>>(X, M, K, ld, a.rows_per_strip, src, rep, Kpad, cand);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(FQ_ERR_HIP, "absmax launch failed: %s", hipGetErrorString(e));
+    *ncand = a.candidates();
+    return FQ_OK;
 }
 
 typedef void (*direct_kernel_t)(const void*, int, int, int, const int32_t*, const int32_t*, int, const float*, const float*, int,
@@ -1062,7 +1057,8 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
         // 12.4 us for the call); at most 64 rows, since a slot that repeats no plain group walks them one by one.
         const bool self = mode == 0 && M <= 64 && (size_t)M * K * sizeof(typename Elem<DT>::type) <= 256u * 1024u;
         int ncand = 0;
-        if (dynamic && !self) ncand = launch_tensor_absmax<DT>(X, M, K, ld, src_idx, rep, Kpad, all_channels, cand, stream);
+        if (dynamic && !self)
+            if ((rc = launch_tensor_absmax<DT>(X, M, K, ld, src_idx, rep, Kpad, all_channels, cand, &ncand, stream))) return rc;
         kern<<<(unsigned)nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, mode == 2 ? nullptr : rep, Kpad, absmax_in,
                                                     ncand ? cand : nullptr, ncand, scale_out, ws.scalars, o8);
         hipError_t e = hipGetLastError();
@@ -1075,7 +1071,8 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
         if (int rc = set_lds_limit(reinterpret_cast<const void*>(flatten_quant_rows_kernel<DT, 6>), 128 * 1024, raised)) return rc;
     }
     int ncand = 0;
-    if (dynamic) ncand = launch_tensor_absmax<DT>(X, M, K, ld, src_idx, rep, Kpad, all_channels, cand, stream);
+    if (dynamic)
+        if (int rc = launch_tensor_absmax<DT>(X, M, K, ld, src_idx, rep, Kpad, all_channels, cand, &ncand, stream)) return rc;
     scale_kernel<<<(Kpad + 1023) / 1024, 1024, 0, stream>>>(cand, ncand, K, src_idx, rep, Kpad, qmax, mode, absmax_in, T,
                                                             ws.mslot, scale_out, ws.scalars, ws.gflag);
     if (!out) {

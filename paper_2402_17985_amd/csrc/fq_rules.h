@@ -1,0 +1,30 @@
+// Launch rules that depend on sizes alone: plain host arithmetic without HIP, so that a test can compile it with the host
+// compiler and walk the sizes at which a rule changes or a launch limit lies.
+#pragma once
+#include <algorithm>
+
+namespace fq {
+
+// Grid of the absmax pass: `blocks` workgroups side by side cover the columns (64 * vec of them each), `strips` of
+// rows_per_strip rows each cover the rows.  Every workgroup leaves one candidate.
+struct AbsmaxGrid {
+    int blocks, strips, rows_per_strip;
+    int candidates() const { return blocks * strips; }
+};
+
+// Strips of 64 rows (16 loads in flight for each of the four waves) while that gives at most 512 workgroups, then higher
+// ones.  Odd multiples of 64: with a power-of-two row stride, strips that start a power-of-two number of rows apart hit
+// the same memory channels (16384 x 8192 bf16: 54 us at 576 rows, 59 us at 512).  At most 1024 candidates, and at most
+// `capacity`; one strip has always room (capacity >= K >= blocks), however many column blocks a wide matrix has.
+inline AbsmaxGrid absmax_grid(long long M, long long K, int vec, long long capacity)
+{
+    const long long bx = (K + 64 * vec - 1) / (64 * vec), cap = std::min(1024LL, capacity);
+    long long rpb = (M * bx + 511) / 512;
+    rpb = std::max(64LL, (rpb + 63) / 64 * 64);
+    if (rpb > 64 && (rpb / 64) % 2 == 0) rpb += 64;
+    while (rpb < M && (M + rpb - 1) / rpb * bx > cap) rpb *= 2;
+    rpb = std::min(rpb, M);
+    return AbsmaxGrid{(int)bx, (int)((M + rpb - 1) / rpb), (int)rpb};
+}
+
+}  // namespace fq

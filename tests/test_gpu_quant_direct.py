@@ -134,3 +134,34 @@ def test_fewer_slots_than_channels(dtype, M, K, Kpad, bits, static):
     src[-2:] = -1
     rep = np.where(src >= 0, rng.integers(1, 4, Kpad), 0).astype(np.int32)
     _check(X, dtype, src, rep, bits, 2.5 if static else None)
+
+
+# Inputs with more than 1024 column blocks for the absmax pass (K > 262144 in fp32, > 524288 in two bytes), read through a map
+# that drops most channels; the largest element lies in the last column block, in a channel that the map reads.
+@pytest.mark.parametrize("dtype,M,K", [("f32", 2, 262400), ("f32", 70, 262148), ("bf16", 3, 524800)])
+@pytest.mark.parametrize("bits", [8, 4])
+def test_more_column_blocks_than_candidates(dtype, M, K, bits):
+    rng = np.random.default_rng(K)
+    X = rng.standard_normal((M, K), dtype=np.float32)
+    X[M - 1, K - 2] = -77.0
+    Kpad = 256
+    src = np.full(Kpad, -1, dtype=np.int32)
+    src[:200] = rng.choice(K, 200, replace=False)
+    src[200:203] = K - 2
+    rep = np.where(src >= 0, 1, 0).astype(np.int32)
+    rep[200:203] = 3
+    _check(X, dtype, src, rep, bits, None)
+    _check(X, dtype, src, rep, bits, 2.0)
+    Xd, Xf = _padded(X, dtype)
+    for call, args in ((fq.fq_flatten_weights, ()), (fq.fq_flatten_quant_act_peel, (dev_i32(np.zeros(Kpad, np.int32)),))):
+        out = torch.full((M, Kpad if bits == 8 else Kpad // 2), 0x55, dtype=torch.uint8, device=DEV)
+        s = torch.zeros(1, dtype=torch.float32, device=DEV)
+        ws = bytes_ws(fq.fq_act_workspace_bytes(K, Kpad))
+        if args:
+            call(Xd, dev_i32(src), *args, bits, 5.0, out, s, ws)
+            want, s_ref = O.flatten_quant_act_peel(Xf, src, np.zeros(Kpad, np.int32), bits, 5.0, O.act_absmax_peel(Xf, 5.0))
+        else:
+            call(Xd, dev_i32(src), bits, out, s, ws)
+            want, s_ref = O.flatten_weights(Xf, src, bits)
+        assert np.float32(s.item()) == s_ref
+        np.testing.assert_array_equal(out.cpu().numpy().reshape(-1), _packed(want, bits).reshape(-1))

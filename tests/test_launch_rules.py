@@ -1,0 +1,47 @@
+"""The launch rules that depend on sizes alone (csrc/fq_rules.h), compiled with the host compiler and walked on the CPU."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2402_17985_amd", "csrc")
+
+DRIVER = """
+#include "fq_rules.h"
+extern "C" void absmax(long long M, long long K, int vec, long long cap, int* out)
+{
+    const fq::AbsmaxGrid a = fq::absmax_grid(M, K, vec, cap);
+    out[0] = a.blocks; out[1] = a.strips; out[2] = a.rows_per_strip;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++")
+    d = tmp_path_factory.mktemp("rules")
+    src, so = str(d / "rules.cpp"), str(d / "rules.so")
+    with open(src, "w") as f:
+        f.write(DRIVER)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-static-libubsan",
+                    "-shared", "-fPIC", "-I", CSRC, "-o", so, src], check=True)
+    return ctypes.CDLL(so)
+
+
+# (elements per 16 bytes, K): more column blocks than 1024 candidates from K = 262145 (fp32) and 524289 (2-byte types) on
+@pytest.mark.parametrize("vec,K", [(4, 16), (4, 1024), (8, 64), (8, 4096), (8, 22016), (4, 262144), (4, 262145), (4, 262400),
+                                   (8, 524288), (8, 524800), (4, 3000000), (8, 2**31 - 1)])
+@pytest.mark.parametrize("M", [1, 2, 16, 64, 65, 500, 8192, 131072, 2**31 - 1])
+def test_absmax_grid_covers_the_matrix_and_fits_the_candidates(rules, vec, K, M):
+    out = (ctypes.c_int * 3)()
+    capacity = (K * 4 + 255) // 256 * 256 // 4
+    rules.absmax(ctypes.c_longlong(M), ctypes.c_longlong(K), vec, ctypes.c_longlong(capacity), out)
+    blocks, strips, rows = out
+    assert rows > 0 and strips > 0 and (blocks - 1) * 64 * vec < K <= blocks * 64 * vec
+    assert (strips - 1) * rows < M <= strips * rows
+    assert blocks * strips <= capacity
+    assert blocks * strips <= 1024 or strips == 1
