@@ -2,8 +2,17 @@
 // compiler and walk the sizes at which a rule changes or a launch limit lies.
 #pragma once
 #include <algorithm>
+#include <stddef.h>
+#include <stdint.h>
 
 namespace fq {
+
+// Whether two ranges of memory share a byte.
+inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes)
+{
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return p < q + b_bytes && q < p + a_bytes;
+}
 
 // Grid of the absmax pass: `blocks` workgroups side by side cover the columns (64 * vec of them each), `strips` of
 // rows_per_strip rows each cover the rows.  Every workgroup leaves one candidate.

@@ -99,3 +99,26 @@ def test_replayed_from_a_graph(M, N, bits):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(Y.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("where", ["X", "second half of X", "map", "copy counts", "bound"])
+def test_output_in_the_memory_of_an_input(where, static, bits):
+    """Y may take the place of what only the quantizer reads (a row updated in place): the result is that of a Y apart."""
+    rng = np.random.default_rng(bits)
+    K = N = 5120
+    X = _x(rng, 1, K, "bf16").contiguous()
+    W = torch.from_numpy(rng.standard_normal((N, K), dtype=np.float32)).to(DEV).to(torch.bfloat16)
+    layer = fq.FqLinear(W, X.float().abs().amax(dim=0).cpu().numpy(), 4.0, bits, device=DEV)
+    bound = torch.full((N,), 4.0, dtype=torch.float32, device=DEV)
+    absmax = bound[:1] if static or where == "bound" else None
+    want = layer.forward(X, absmax_in=absmax)
+    room = {"X": X.view(-1), "second half of X": torch.cat([X.view(-1), X.view(-1)]), "map": layer.src.view(torch.bfloat16),
+            "copy counts": layer.rep.view(torch.bfloat16), "bound": bound.view(torch.bfloat16)}[where]
+    if where == "second half of X":
+        X, Y = room[:K].view(1, K), room[K // 2:K // 2 + N].view(1, N)
+    else:
+        Y = room[:N].view(1, N)
+    layer.forward(X, Y, absmax_in=absmax)
+    assert torch.equal(Y.view(torch.int16), want.view(torch.int16))

@@ -16,6 +16,10 @@ extern "C" void absmax(long long M, long long K, int vec, long long cap, int* ou
     const fq::AbsmaxGrid a = fq::absmax_grid(M, K, vec, cap);
     out[0] = a.blocks; out[1] = a.strips; out[2] = a.rows_per_strip;
 }
+extern "C" int overlap(unsigned long long a, unsigned long long na, unsigned long long b, unsigned long long nb)
+{
+    return fq::overlap((const void*)a, na, (const void*)b, nb);
+}
 """
 
 
@@ -45,3 +49,11 @@ def test_absmax_grid_covers_the_matrix_and_fits_the_candidates(rules, vec, K, M)
     assert (strips - 1) * rows < M <= strips * rows
     assert blocks * strips <= capacity
     assert blocks * strips <= 1024 or strips == 1
+
+
+@pytest.mark.parametrize("a,na,b,nb,want", [(1000, 16, 1000, 16, 1), (1000, 16, 1015, 1, 1), (1000, 16, 1016, 1, 0), (1000, 16, 999, 1, 0),
+                                            (1000, 16, 990, 11, 1), (1000, 16, 900, 500, 1), (1000, 500, 1100, 4, 1), (1000, 4, 2000, 4, 0)])
+def test_overlap(rules, a, na, b, nb, want):
+    u = ctypes.c_ulonglong
+    assert rules.overlap(u(a), u(na), u(b), u(nb)) == want
+    assert rules.overlap(u(b), u(nb), u(a), u(na)) == want
