@@ -1,6 +1,7 @@
 // Kernel-variant selection and the entry points of the GEMM family: they forward to the per-mode
 // dispatchers, which live in the four translation units built from fq_gemm.hip.
 #include "fq_internal.h"
+#include "fq_rules.h"
 #include "../../include/fq_peak.h"
 
 namespace fq {
@@ -70,6 +71,7 @@ namespace {
 // Products of few output tiles.  `done` says whether a kernel for them was chosen (and its launch attempted).
 //   - At most 4 rows, or 4-bit values and at most 16: the weights go straight into registers (gemm_skinny; INT8 at 8 and 16
 //     rows, 6400 x 15360: 23.0, 24.3 us against 20.9, 21.0 for the stream kernel; nibbles 10.2, 10.4 against 11.6, 11.6).
+//     Its 512 threads per 16 columns are more than a launch holds from 2^27 columns on; those go to the 128-column tiles.
 //   - Otherwise the smallest tile with which one round of workgroups, one per CU, covers the output: a larger one leaves CUs
 //     idle, a smaller one takes a second round and reads the operands more often (INT8 12544 x 4096, 256 rows: 32 x 64 30.6,
 //     64 x 64 21.7, 96 x 64 25.2 us).  Up to 96 x 64 the reduction is split over the waves.  Beyond it INT8 goes through the
@@ -83,7 +85,7 @@ int launch_few_tiles(const void* A, const void* B, int M, int N, int Kpad, int b
     done = false;
     const int rowbytes = bits == 8 ? Kpad : bits == 4 ? Kpad / 2 : Kpad / 4 * 3;
     if (g_variant >= 0 || (bt.count > 1 && rowbytes < 512)) return FQ_OK;
-    if (M <= 4 || (bits != 8 && M <= 16 && N <= 16384)) {
+    if ((M <= 4 && skinny_holds(N)) || (bits != 8 && M <= 16 && N <= 16384)) {
         done = true;
         return launch_gemm_skinny(bits, A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
     }

@@ -14,6 +14,13 @@ inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes
     return p < q + b_bytes && q < p + a_bytes;
 }
 
+// What one dimension of a launch can hold: the work items along it are counted in 32 bits.
+inline bool launch_holds(long long workgroups, int threads) { return workgroups * threads < (1LL << 32); }
+
+// The weight-streaming kernel for at most 4 rows has 512 threads per 16 columns.
+constexpr int SKINNY_COLUMNS = 16, SKINNY_THREADS = 512;
+inline bool skinny_holds(long long N) { return launch_holds((N + SKINNY_COLUMNS - 1) / SKINNY_COLUMNS, SKINNY_THREADS); }
+
 // Grid of the absmax pass: `blocks` workgroups side by side cover the columns (64 * vec of them each), `strips` of
 // rows_per_strip rows each cover the rows.  Every workgroup leaves one candidate.
 struct AbsmaxGrid {

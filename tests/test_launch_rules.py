@@ -16,6 +16,7 @@ extern "C" void absmax(long long M, long long K, int vec, long long cap, int* ou
     const fq::AbsmaxGrid a = fq::absmax_grid(M, K, vec, cap);
     out[0] = a.blocks; out[1] = a.strips; out[2] = a.rows_per_strip;
 }
+extern "C" int skinny(long long N) { return fq::skinny_holds(N); }
 extern "C" int overlap(unsigned long long a, unsigned long long na, unsigned long long b, unsigned long long nb)
 {
     return fq::overlap((const void*)a, na, (const void*)b, nb);
@@ -57,3 +58,10 @@ def test_overlap(rules, a, na, b, nb, want):
     u = ctypes.c_ulonglong
     assert rules.overlap(u(a), u(na), u(b), u(nb)) == want
     assert rules.overlap(u(b), u(nb), u(a), u(na)) == want
+
+
+def test_weight_streaming_launches_stay_within_32_bits(rules):
+    """Operands of less than 4 GiB admit N up to 2^27 - 1 (INT8, 32 slots) or 2^28 - 1 (nibbles, 32 slots)."""
+    for N in (1, 16, 4097, 2**27 - 16, 2**27 - 15, 2**27 - 1, 2**27, 2**28 - 1):
+        assert rules.skinny(ctypes.c_longlong(N)) == ((N + 15) // 16 * 512 < 2**32)
+    assert not rules.skinny(ctypes.c_longlong(2**27 - 1))
