@@ -338,9 +338,11 @@ __global__ __launch_bounds__(256) void flatten_quant_kernel(const void* __restri
         for (int j = 0; j < 4; ++j) { s[4 * i + j] = sv[j]; m[4 * i + j] = mv[j]; }
     }
     bool contig = (s[0] >= 0) && (s[0] % VEC == 0) && (s[0] + 15 < K);
+    uint32_t pad = 0;                                          // padding / invalid slots: 0 whatever X holds
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        if ((unsigned)s[i] >= (unsigned)K) {                                            // padding / invalid
+        if ((unsigned)s[i] >= (unsigned)K) {
+            pad |= 1u << i;
             s[i] = 0;
             m[i] = PEEL ? __builtin_inff() : 0.0f;
             contig = false;
@@ -366,7 +368,7 @@ __global__ __launch_bounds__(256) void flatten_quant_kernel(const void* __restri
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) x[i] = Elem<DT>::widen(row[s[i]]);
+            for (int i = 0; i < 16; ++i) x[i] = ((pad >> i) & 1) ? 0.0f : Elem<DT>::widen(row[s[i]]);
         }
         int q[16];
 #pragma unroll
@@ -510,18 +512,19 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
 #pragma unroll
             for (int j = 0; j < 4; ++j) { s[4 * i + j] = sv[j]; m[4 * i + j] = mv[j]; }
         }
-        bool ident[16];
+        bool ident[16], pad[16];                                // padding / invalid slots: 0 whatever X holds
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             ident[i] = to_lds && s[i] == p0 + i;
-            if ((unsigned)s[i] >= (unsigned)K) { s[i] = 0; m[i] = 0.0f; }
+            pad[i] = (unsigned)s[i] >= (unsigned)K;
+            if (pad[i]) { s[i] = 0; m[i] = 0.0f; }
         }
         uint8_t* o = out + (size_t)(r0 + ra) * orow_bytes + group_ofs(g);
         const T* row = X + (size_t)(r0 + ra) * ld;
         for (int r = ra; r < rb; ++r, row += ld, o += orow_bytes) {
             int q[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = quant1<BITS>(Elem<DT>::widen(row[s[i]]), m[i]);
+            for (int i = 0; i < 16; ++i) q[i] = quant1<BITS>(pad[i] ? 0.0f : Elem<DT>::widen(row[s[i]]), m[i]);
             if constexpr (BITS == 6) store_e3m2(q, r0 + r, g);
             else pack_store(q, o);
 #pragma unroll
@@ -870,10 +873,10 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
         load_slots(g << 4, s, n);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const bool valid = (unsigned)s[i] < (unsigned)K && n[i] > 0;
-            const float x = Elem<DT>::widen(xr[(unsigned)s[i] < (unsigned)K ? s[i] : 0]);
+            const bool in = (unsigned)s[i] < (unsigned)K;             // a slot without a channel: 0 whatever X holds
+            const float x = in ? Elem<DT>::widen(xr[s[i]]) : 0.0f;
             float mult = 0.0f;
-            if (valid) mult = n[i] < DIRECT_TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
+            if (in && n[i] > 0) mult = n[i] < DIRECT_TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
             q[i] = quant1<BITS>(x, mult);
         }
         if constexpr (BITS == 6) store_e3m2(q, row, g);

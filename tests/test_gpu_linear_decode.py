@@ -122,3 +122,30 @@ def test_output_in_the_memory_of_an_input(where, static, bits):
         Y = room[:N].view(1, N)
     layer.forward(X, Y, absmax_in=absmax)
     assert torch.equal(Y.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_what_is_not_finite(value, bits):
+    """The accumulators of both forms for a row with an element that is not finite, static scale: padding slots add nothing,
+    whatever the weights hold there."""
+    rng = np.random.default_rng(3)
+    K, N, Kpad = 500, 100, 1024
+    X = _x(rng, 1, K, "f32")
+    X[0, 0] = value
+    src = np.full(Kpad, -1, dtype=np.int32)
+    rep = np.zeros(Kpad, dtype=np.int32)
+    src[:K], rep[:K] = np.arange(K), 1
+    src[K:K + 300:7], rep[K:K + 300:7] = 3, 2                              # single copies among padding
+    Wq = torch.randint(-128, 128, (N, Kpad if bits == 8 else Kpad // 2), dtype=torch.int8, device=DEV)
+    ws = bytes_ws(fq.fq_linear_workspace_bytes(1, K, Kpad, bits))
+    out = []
+    for variant in (-1, 2):
+        Y = torch.zeros((1, N), dtype=torch.int32, device=DEV)
+        fq.fq_gemm_select(variant)
+        try:
+            fq.fq_linear(X, dev_i32(src), dev_i32(rep), Wq, scalar(1.0), bits, Y, ws, absmax_in=scalar(3.0))
+        finally:
+            fq.fq_gemm_select(-1)
+        out.append(Y)
+    assert torch.equal(out[0], out[1])

@@ -165,3 +165,35 @@ def test_more_column_blocks_than_candidates(dtype, M, K, bits):
             want, s_ref = O.flatten_weights(Xf, src, bits)
         assert np.float32(s.item()) == s_ref
         np.testing.assert_array_equal(out.cpu().numpy().reshape(-1), _packed(want, bits).reshape(-1))
+
+
+# Padding slots hold 0 and finite elements keep their values whatever else X holds (static scale): infinities and NaN sit in
+# column 0 and in a channel that is copied; padding stands in groups of copies, in the head and beside a slot that is gathered.
+# (K, M): the one-kernel form with one and two groups per thread, the row-strip kernel, and a layer too wide for either.
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("dtype,M,K", [("f32", 3, 500), ("bf16", 70, 4096), ("bf16", 3, 16400), ("bf16", 800, 16384), ("f16", 5, 33000)])
+def test_padding_beside_what_is_not_finite(dtype, M, K, bits):
+    rng = np.random.default_rng(K)
+    X = rng.standard_normal((M, K), dtype=np.float32)
+    Kpad = (K + 300 + 31) // 32 * 32
+    src = np.full(Kpad, -1, dtype=np.int32)
+    rep = np.zeros(Kpad, dtype=np.int32)
+    src[:K] = np.arange(K)
+    rep[:K] = 1
+    src[70] = -1                                                          # a hole in the head
+    src[K:K + 40] = 5
+    src[K + 50], src[K + 51], src[K + 90] = 7, K + 3, 9                    # single copies among padding
+    rep[K:K + 120] = np.where((src[K:K + 120] >= 0) & (src[K:K + 120] < K), 2, 0)
+    X[0, 0], X[M - 1, 0], X[1, 5], X[2, 9] = np.inf, -np.inf, np.nan, np.inf
+    Xd, Xf = _padded(X, dtype)
+    ok = np.isfinite(Xf)
+    valid = (src >= 0) & (src < K)
+    want, s_ref = O.flatten_quant_act(np.where(ok, Xf, 0).astype(np.float32), np.where(valid, src, -1).astype(np.int32), rep, bits, 3.0)
+    out = torch.full((M, Kpad if bits == 8 else Kpad // 2), 0x55, dtype=torch.uint8, device=DEV)
+    s_x = torch.zeros(1, dtype=torch.float32, device=DEV)
+    fq.fq_flatten_quant_act(Xd, dev_i32(src), dev_i32(rep), bits, out, s_x, bytes_ws(fq.fq_act_workspace_bytes(K, Kpad)), absmax_in=scalar(3.0))
+    got = out.cpu().numpy()
+    got = got.view(np.int8) if bits == 8 else O.unpack_i4(got)
+    defined = ~valid[None, :] | ok[:, np.where(valid, src, 0)]
+    np.testing.assert_array_equal(got[defined], want[defined])
+    assert np.float32(s_x.item()) == s_ref
