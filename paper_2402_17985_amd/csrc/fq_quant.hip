@@ -293,9 +293,9 @@ __global__ __launch_bounds__(1024) void scale_kernel(const float* __restrict__ c
 // ---------------------------------------------------------------------------------------------
 // flatten + quantize
 // ---------------------------------------------------------------------------------------------
-// LDS of flatten_quant_direct_kernel before the strip itself: the table of multipliers and the wave maxima.  Copy counts
-// below DIRECT_TABLE fit a byte.
-constexpr int DIRECT_TABLE = 256, DIRECT_RED = 16;
+// LDS of flatten_quant_direct_kernel before the strip itself: the table of multipliers and the wave maxima.  A plain group's
+// copy counts are kept as bytes; MANY stands for MANY copies or more, whose count is read from the map where it matters.
+constexpr int DIRECT_TABLE = 256, DIRECT_RED = 16, MANY = 255;
 constexpr int DIRECT_LDS_FIXED = (DIRECT_TABLE + DIRECT_RED) * 4;
 
 // PEEL = false: slot value x * m_p (equal split; m_p from mslot).  PEEL = true: the printed split of
@@ -623,8 +623,10 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
 // bound by its launches (each 4-8 us) and not by bytes.  A workgroup owns a run of rows, which it walks in strips of R,
 // and has one thread per P head groups, so that a strip is one round of loads.
 //   the map    thread t reads the sources and copy counts of its groups t, t + blockDim, ... of the head.  A group is
-//              plain when its slots are the channels at the same indices with tabulated copy counts; the counts of plain
-//              groups are left in LDS, and from them follows which appended groups only repeat their values.
+//              plain when its slots are the channels at the same indices with copies; the counts of plain groups are left
+//              in LDS, and from them follows which appended groups only repeat their values.  (Counts beyond the table are
+//              rare and divide once per slot.  Gathering their groups and copies element by element took 18.0 us for 1000 x
+//              4096 static with one channel of 300 copies and 25.6 with 2000; this 8.7 and 11.8.)
 //   a'         the static bound; or the maximum of the candidates that tensor_absmax_kernel left; or (few rows) taken
 //              from all of X by every workgroup, which costs M * K reads from L2 against a launch.
 //   strips     phase 1 quantizes the plain head groups from registers, phase 2 copies appended slots out of LDS; any
@@ -704,7 +706,7 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
 
     // ---- the map ----
     uint32_t nb[P][4];                                         // copy counts of this thread's plain groups, as bytes
-    int plain = 0;
+    int plain = 0, many = 0;                                   // groups of this thread: plain; with a count of MANY
     bool other = false;                                        // a group that is neither plain nor copies of plain ones
 #pragma unroll
     for (int p = 0; p < P; ++p) {
@@ -714,13 +716,17 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
         if (g < NH) {
             int sv[16], nv[16];
             load_slots(g << 4, sv, nv);
-            bool ok = true;
+            bool ok = true, big = false;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) ok = ok && sv[i] == (g << 4) + i && (unsigned)(nv[i] - 1) < DIRECT_TABLE - 1;
+            for (int i = 0; i < 16; ++i) {
+                ok = ok && sv[i] == (g << 4) + i && nv[i] > 0;
+                big = big || nv[i] >= MANY;
+            }
             if (ok) {
                 plain |= 1 << p;
+                if (big) many |= 1 << p;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) nb[p][i >> 2] |= (uint32_t)nv[i] << (8 * (i & 3));
+                for (int i = 0; i < 16; ++i) nb[p][i >> 2] |= (uint32_t)min(nv[i], MANY) << (8 * (i & 3));
             }
             *reinterpret_cast<v4u*>(qs + (g << 4)) = v4u{nb[p][0], nb[p][1], nb[p][2], nb[p][3]};
             other = other || !ok;
@@ -753,8 +759,15 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
 #pragma unroll
                 for (int i = 0; i < 16; ++i) mx[i] = fmaxf(mx[i], fabsf(x[i]));
             }
+            int nv[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) consider(mx[i], (nb[p][i >> 2] >> (8 * (i & 3))) & 0xff);
+            for (int i = 0; i < 16; ++i) nv[i] = (nb[p][i >> 2] >> (8 * (i & 3))) & 0xff;
+            if ((many >> p) & 1) {
+                load_counts((tid + p * nthr) << 4, nv);
+                load_counts(((tid + p * nthr) << 4) + 8, nv + 8);
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) consider(mx[i], nv[i]);
         }
     }
     __syncthreads();
@@ -765,14 +778,22 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
         int j[8], n[8];
         load8(src + KQ + t, j);
         load_counts(KQ + t, n);
-        bool copyable = true;
+        bool copyable = true, big = false;
         uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const bool in = (unsigned)j[i] < (unsigned)KQ;
             const int own = in ? qs[j[i]] : 0;
-            if ((unsigned)j[i] < (unsigned)K) copyable = copyable && own != 0 && n[i] == own;
+            if ((unsigned)j[i] < (unsigned)K) copyable = copyable && own != 0 && min(n[i], MANY) == own;
+            big = big || own == MANY;
             w[i >> 1] |= (in ? (uint32_t)j[i] : 0xffffu) << (16 * (i & 1));
+        }
+        if (copyable && big) {                                     // counts of MANY or more: compared with the map's
+            int c[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) c[i] = counts[(unsigned)j[i] < (unsigned)KQ ? j[i] : 0];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) copyable = copyable && ((unsigned)j[i] >= (unsigned)KQ || n[i] == c[i]);
         }
         *reinterpret_cast<v4u*>(ts + t) = v4u{w[0], w[1], w[2], w[3]};
         const int mine = copyable ? 1 : 0, both = mine & __shfl_xor(mine, 1, 64);
@@ -824,6 +845,13 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
     for (int p = 0; p < P; ++p)
 #pragma unroll
         for (int i = 0; i < 16; ++i) m[p][i] = table[(nb[p][i >> 2] >> (8 * (i & 3))) & 0xff];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        if (!((many >> p) & 1) || a == 0.0f) continue;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (((nb[p][i >> 2] >> (8 * (i & 3))) & 0xff) == MANY) m[p][i] = multiplier(counts[((tid + p * nthr) << 4) + i]);
+    }
 
     auto pack_store = [&](const int (&q)[16], uint8_t* o) {
         if (BITS == 8) {
@@ -874,7 +902,7 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const bool in = (unsigned)s[i] < (unsigned)K;             // a slot without a channel: 0 whatever X holds
-            const float x = in ? Elem<DT>::widen(xr[s[i]]) : 0.0f;
+            const float xs = Elem<DT>::widen(xr[in ? s[i] : 0]), x = in ? xs : 0.0f;
             float mult = 0.0f;
             if (in && n[i] > 0) mult = n[i] < DIRECT_TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
             q[i] = quant1<BITS>(x, mult);

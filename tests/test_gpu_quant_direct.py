@@ -197,3 +197,22 @@ def test_padding_beside_what_is_not_finite(dtype, M, K, bits):
     defined = ~valid[None, :] | ok[:, np.where(valid, src, 0)]
     np.testing.assert_array_equal(got[defined], want[defined])
     assert np.float32(s_x.item()) == s_ref
+
+
+# Copy counts on both sides of what a byte and the tables hold, one and two head groups per thread; a' from all of X in every
+# workgroup (few rows), from the candidates, static; and the row-strip kernel.
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("dtype,M,K,bits", [("bf16", 1, 640, 8), ("f32", 9, 640, 6), ("f16", 90, 640, 4), ("bf16", 5, 16500, 8), ("f32", 40, 16500, 4), ("bf16", 770, 16500, 8)])
+def test_copy_counts_beyond_a_byte(dtype, M, K, bits, static):
+    rng = np.random.default_rng(K + M)
+    counts = np.array([253, 254, 255, 256, 300, 1023, 1024, 3000])
+    at = np.concatenate([rng.choice(K - 20, counts.size - 1, replace=False), [K - 3]])      # the last one in the last group
+    chmax = np.full(K, 0.5, dtype=np.float32)
+    chmax[at] = counts - 0.5
+    src, rep, _, _ = fq.fq_flatten_plan(chmax, 1.0, 128 if bits == 6 else 32)
+    assert (rep[at] == counts).all()
+    X = (rng.uniform(-1.0, 1.0, (M, K)) * chmax).astype(np.float32)
+    X[M - 1, at[4]] = np.float32(299.25)                                                    # a' = 299.25 / 300
+    _check(X, dtype, src, rep, bits, 1.0 if static else None)
+    rep[src == at[4]] = rng.integers(250, 310, (src == at[4]).sum())                        # copies with other counts than the channel's
+    _check(X, dtype, src, rep, bits, 1.0 if static else None)
