@@ -26,9 +26,9 @@ inline int elem_size(int dtype)
     }
 }
 
-// Workspace layout of the activation path: [cmax: K f32][mslot: Kpad f32][scalars: 4 f32][gflag: Kpad/16 u8]
+// Workspace layout of the activation path: [cmax: max(K, 1024) f32][mslot: Kpad f32][scalars: 4 f32][gflag: Kpad/16 u8]
 struct ActWorkspace {
-    float* cmax;      // candidates for a' (one per workgroup of the absmax pass, at most K rounded up to 64)
+    float* cmax;      // candidates for a' (one per workgroup of the absmax pass)
     float* mslot;     // per flattened slot multiplier m_p
     float* scalars;   // [0] = a'
     uint8_t* gflag;   // per group of 16 slots: 1 = the 16 channels at the same indices; then, Kpad/16 + 1

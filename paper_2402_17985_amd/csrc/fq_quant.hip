@@ -1012,13 +1012,13 @@ void launch_colabsmax(const void* X, int M, int K, int ld, bool accumulate, uint
     colabsmax_kernel<DT><<<grid, 256, 0, stream>>>(X, M, K, ld, (int)rpb, cmax);
 }
 
-// Candidates for a' of the flattened tensor (or, all_channels, of the whole array) into cand, which holds the K floats of
-// the workspace; their number goes to *ncand.
+// Candidates for a' of the flattened tensor (or, all_channels, of the whole array) into cand, which has room for
+// candidate_capacity(K) floats; their number goes to *ncand.
 template <int DT>
 int launch_tensor_absmax(const void* X, int M, int K, int ld, const int32_t* src, const int32_t* rep, int Kpad,
                          bool all_channels, float* cand, int* ncand, hipStream_t stream)
 {
-    const AbsmaxGrid a = absmax_grid(M, K, Elem<DT>::VEC, (long long)(round_up((size_t)K * 4, 256) / 4));
+    const AbsmaxGrid a = absmax_grid(M, K, Elem<DT>::VEC);
     const dim3 grid((unsigned)a.blocks, (unsigned)a.strips);
     if (all_channels) tensor_absmax_kernel<DT, true><<<grid, 256, 0, stream>>>(X, M, K, ld, a.rows_per_strip, src, rep, Kpad, cand);
     else tensor_absmax_kernel<DT, false><<<grid, 512, 0, stream>>>(X, M, K, ld, a.rows_per_strip, src, rep, Kpad, cand);
@@ -1178,7 +1178,7 @@ ActWorkspace carve_act_workspace(void* base, int K, int Kpad)
     uint8_t* p = static_cast<uint8_t*>(base);
     size_t off = 0;
     ws.cmax = reinterpret_cast<float*>(p + off);
-    off += round_up((size_t)K * 4, 256);
+    off += round_up((size_t)candidate_capacity(K) * 4, 256);
     ws.mslot = reinterpret_cast<float*>(p + off);
     off += round_up((size_t)Kpad * 4, 256);
     ws.scalars = reinterpret_cast<float*>(p + off);

@@ -28,17 +28,20 @@ struct AbsmaxGrid {
     int candidates() const { return blocks * strips; }
 };
 
+// Candidates that the workspace has room for: one per column block however wide the matrix, and enough strips of a narrow one.
+constexpr int MAX_CANDIDATES = 1024;
+inline long long candidate_capacity(long long K) { return std::max<long long>(MAX_CANDIDATES, (K + 63) / 64 * 64); }
+
 // Strips of 64 rows (16 loads in flight for each of the four waves) while that gives at most 512 workgroups, then higher
 // ones.  Odd multiples of 64: with a power-of-two row stride, strips that start a power-of-two number of rows apart hit
-// the same memory channels (16384 x 8192 bf16: 54 us at 576 rows, 59 us at 512).  At most 1024 candidates, and at most
-// `capacity`; one strip has always room (capacity >= K >= blocks), however many column blocks a wide matrix has.
-inline AbsmaxGrid absmax_grid(long long M, long long K, int vec, long long capacity)
+// the same memory channels (16384 x 8192 bf16: 54 us at 576 rows, 59 us at 512).  At most 1024 candidates, or one strip.
+inline AbsmaxGrid absmax_grid(long long M, long long K, int vec)
 {
-    const long long bx = (K + 64 * vec - 1) / (64 * vec), cap = std::min(1024LL, capacity);
+    const long long bx = (K + 64 * vec - 1) / (64 * vec);
     long long rpb = (M * bx + 511) / 512;
     rpb = std::max(64LL, (rpb + 63) / 64 * 64);
     if (rpb > 64 && (rpb / 64) % 2 == 0) rpb += 64;
-    while (rpb < M && (M + rpb - 1) / rpb * bx > cap) rpb *= 2;
+    while (rpb < M && (M + rpb - 1) / rpb * bx > MAX_CANDIDATES) rpb *= 2;
     rpb = std::min(rpb, M);
     return AbsmaxGrid{(int)bx, (int)((M + rpb - 1) / rpb), (int)rpb};
 }

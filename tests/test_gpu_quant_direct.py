@@ -216,3 +216,15 @@ def test_copy_counts_beyond_a_byte(dtype, M, K, bits, static):
     _check(X, dtype, src, rep, bits, 1.0 if static else None)
     rep[src == at[4]] = rng.integers(250, 310, (src == at[4]).sum())                        # copies with other counts than the channel's
     _check(X, dtype, src, rep, bits, 1.0 if static else None)
+
+
+# Tall and narrow (an attention operand): more strips than the matrix has columns, the largest element in the last row.
+@pytest.mark.parametrize("dtype,M,K,bits", [("bf16", 70001, 64, 8), ("f32", 66000, 20, 4), ("bf16", 200000, 72, 8)])
+def test_more_strips_than_columns(dtype, M, K, bits):
+    rng = np.random.default_rng(K)
+    X = rng.standard_normal((M, K), dtype=np.float32)
+    X[M - 1, K - 1] = 9.5
+    Kpad = (K + 31) // 32 * 32
+    src = np.full(Kpad, -1, dtype=np.int32)
+    src[:K] = np.arange(K)
+    _check(X, dtype, src, np.where(src >= 0, 1, 0).astype(np.int32), bits, None)

@@ -11,9 +11,10 @@ CSRC = os.path.join(ROOT, "paper_2402_17985_amd", "csrc")
 
 DRIVER = """
 #include "fq_rules.h"
-extern "C" void absmax(long long M, long long K, int vec, long long cap, int* out)
+extern "C" long long capacity(long long K) { return fq::candidate_capacity(K); }
+extern "C" void absmax(long long M, long long K, int vec, int* out)
 {
-    const fq::AbsmaxGrid a = fq::absmax_grid(M, K, vec, cap);
+    const fq::AbsmaxGrid a = fq::absmax_grid(M, K, vec);
     out[0] = a.blocks; out[1] = a.strips; out[2] = a.rows_per_strip;
 }
 extern "C" int skinny(long long N) { return fq::skinny_holds(N); }
@@ -43,13 +44,16 @@ def rules(tmp_path_factory):
 @pytest.mark.parametrize("M", [1, 2, 16, 64, 65, 500, 8192, 131072, 2**31 - 1])
 def test_absmax_grid_covers_the_matrix_and_fits_the_candidates(rules, vec, K, M):
     out = (ctypes.c_int * 3)()
-    capacity = (K * 4 + 255) // 256 * 256 // 4
-    rules.absmax(ctypes.c_longlong(M), ctypes.c_longlong(K), vec, ctypes.c_longlong(capacity), out)
+    rules.absmax(ctypes.c_longlong(M), ctypes.c_longlong(K), vec, out)
     blocks, strips, rows = out
+    rules.capacity.restype = ctypes.c_longlong
+    capacity = rules.capacity(ctypes.c_longlong(K))
     assert rows > 0 and strips > 0 and (blocks - 1) * 64 * vec < K <= blocks * 64 * vec
     assert (strips - 1) * rows < M <= strips * rows
     assert blocks * strips <= capacity
     assert blocks * strips <= 1024 or strips == 1
+    # a tall matrix gets the workgroups that its height allows, however narrow it is
+    assert blocks * strips >= min(256, blocks * ((M + 63) // 64)) or blocks > 1024
 
 
 @pytest.mark.parametrize("a,na,b,nb,want", [(1000, 16, 1000, 16, 1), (1000, 16, 1015, 1, 1), (1000, 16, 1016, 1, 0), (1000, 16, 999, 1, 0),
