@@ -459,18 +459,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const uint8_t* __
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const ClockProbe probe(bt.ticks);
-    // Batched launches: the grid's y dimension counts the problems.  Ids are dealt round-robin to the XCDs over the whole
-    // grid, so each XCD gets a contiguous band of (problem, tile) pairs: a problem's operands then pass through one L2, not
-    // through all eight.
-    int problem = blockIdx.y, first = blockIdx.x;
-    const bool banded = gridDim.y > 1 && (unsigned long long)gridDim.x * gridDim.y < (1ull << 31);
-    if (banded) {
-        const unsigned total = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x;
-        const unsigned q = total >> 3, rem = total & 7, xcd = id & 7, idx = id >> 3;
-        const unsigned logical = (xcd < rem) ? xcd * (q + 1) + idx : rem * (q + 1) + (xcd - rem) * q + idx;
-        problem = __builtin_amdgcn_readfirstlane((int)(logical / gridDim.x));
-        first = __builtin_amdgcn_readfirstlane((int)(logical - (unsigned)problem * gridDim.x));
-    }
+    int problem, first;
+    const bool banded = place_of_workgroup(problem, first);
     A += (size_t)problem * bt.stride_a;
     B += (size_t)problem * bt.stride_b;
     Y = static_cast<uint8_t*>(Y) + (size_t)problem * bt.stride_y;
