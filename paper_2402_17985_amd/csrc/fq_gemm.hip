@@ -92,7 +92,7 @@ __device__ __forceinline__ void mfma_slice(const v4i (&a)[FM], const v4i (&b)[FN
 // =============================================================================================
 // gemm_dma_kernel: direct global -> LDS stages, register double-buffered MFMA operands
 // =============================================================================================
-template <int MODE, int BM, int BN, int BKB, int WM, int WN, int NSTAGE, int PIPE, int PP_SLICES = 2, bool ONLY_BF16 = false>
+template <int MODE, int BM, int BN, int BKB, int WM, int WN, int NSTAGE, int PIPE, int PP_SLICES = 2, int ONLY = ANY_OUTPUT>
 __device__ __forceinline__ void gemm_dma_tile(uint8_t* smem, int m0, int n0, const uint8_t* __restrict__ A,
                                               const uint8_t* __restrict__ B, int M, int N, int rowbytes,
                                               const float* __restrict__ s_x, const float* __restrict__ s_w,
@@ -436,11 +436,11 @@ __device__ __forceinline__ void gemm_dma_tile(uint8_t* smem, int m0, int n0, con
         constexpr int CH_FIT = SHARE / (32 * TN * 2);
         constexpr int CH = CH_FIT >= FM ? FM : (CH_FIT >= 2 ? 2 : CH_FIT);
         static_assert(CH >= 1 && FM % CH == 0, "output staging must fit the wave's share of a stage buffer");
-        store_tile<MODE, FM, FN, CH, ONLY_BF16>(acc, m0 + wm * TM, n0 + wn * TN, M, N, scale, Y, y_dtype, ldy,
+        store_tile<MODE, FM, FN, CH, ONLY>(acc, m0 + wm * TM, n0 + wn * TN, M, N, scale, Y, y_dtype, ldy,
                                      smem + STAGE + wave * SHARE, bias);
     } else {
         constexpr bool CAN_STAGE = NW * TM * TN * 2 <= NSTAGE * STAGE;
-        store_tile<MODE, FM, FN, FM, ONLY_BF16>(acc, m0 + wm * TM, n0 + wn * TN, M, N, scale, Y, y_dtype, ldy,
+        store_tile<MODE, FM, FN, FM, ONLY>(acc, m0 + wm * TM, n0 + wn * TN, M, N, scale, Y, y_dtype, ldy,
                                  CAN_STAGE ? smem + wave * (TM * TN * 2) : nullptr, bias);
     }
 }
@@ -449,7 +449,7 @@ __device__ __forceinline__ void gemm_dma_tile(uint8_t* smem, int m0, int n0, con
 // last, partly filled round of at most half the CUs, those tiles are instead computed as two
 // (BM/2) x BN halves by workgroups [n_main, n_main + 2 * n_tail), so that the last round takes about
 // half as long.
-template <int MODE, int BM, int BN, int BKB, int WM, int WN, int NSTAGE, int PIPE, int PP_SLICES = 2, bool ONLY_BF16 = false>
+template <int MODE, int BM, int BN, int BKB, int WM, int WN, int NSTAGE, int PIPE, int PP_SLICES = 2, int ONLY = ANY_OUTPUT>
 __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const uint8_t* __restrict__ A,
                                                                 const uint8_t* __restrict__ B, int M, int N,
                                                                 int rowbytes, const float* __restrict__ s_x,
@@ -478,7 +478,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const uint8_t* __
             const bool has_next = vn < n_main;
             int next_m = 0, next_n = 0;
             if (has_next) tile_of_workgroup(vn, n_main, tiles_m, tiles_n, next_m, next_n);
-            gemm_dma_tile<MODE, BM, BN, BKB, WM, WN, NSTAGE, PIPE, PP_SLICES, ONLY_BF16>(smem, tile_m * BM, tile_n * BN, A, B, M, N, rowbytes,
+            gemm_dma_tile<MODE, BM, BN, BKB, WM, WN, NSTAGE, PIPE, PP_SLICES, ONLY>(smem, tile_m * BM, tile_n * BN, A, B, M, N, rowbytes,
                                                                     s_x, s_w, Y, y_dtype, ldy, bt.bias, prefetched,
                                                                     has_next, next_m * BM, next_n * BN);
             prefetched = CAN_PREFETCH && has_next;
@@ -486,7 +486,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const uint8_t* __
             if constexpr (BM >= 128 && (BM / 2) % (64 / (BKB / 16) * WM * WN) == 0) {
                 const int t = v - n_main;
                 tile_of_logical(n_main + (t >> 1), tiles_m, tiles_n, tile_m, tile_n);
-                gemm_dma_tile<MODE, BM / 2, BN, BKB, WM, WN, NSTAGE, PIPE, PP_SLICES, ONLY_BF16>(smem, tile_m * BM + (t & 1) * (BM / 2),
+                gemm_dma_tile<MODE, BM / 2, BN, BKB, WM, WN, NSTAGE, PIPE, PP_SLICES, ONLY>(smem, tile_m * BM + (t & 1) * (BM / 2),
                                                                             tile_n * BN, A, B, M, N, rowbytes, s_x, s_w,
                                                                             Y, y_dtype, ldy, bt.bias);
             }
@@ -657,7 +657,7 @@ __device__ __forceinline__ void gemm_wide_tile(uint8_t* smem, int m0, int n0, co
     stage(kt, no{}, no{});
     __syncthreads();                                 // every wave is past its last LDS operand read
 
-    store_tile<MODE, FM, FN, 2, ONLY_BF16>(acc, m0 + wm * TM, n0 + wn * TN, M, N, scale, Y, y_dtype, ldy,
+    store_tile<MODE, FM, FN, 2, ONLY_BF16 ? FQ_BF16 : ANY_OUTPUT>(acc, m0 + wm * TM, n0 + wn * TN, M, N, scale, Y, y_dtype, ldy,
                                 smem + wave * (64 * TN * 2), bias);
 }
 
@@ -935,7 +935,7 @@ __device__ __forceinline__ void gemm_deep_tile(uint8_t* smem, int m0, int n0, co
     for (; kt < nk; ++kt) stage(kt, no{}, no{}, no{});                      // the last stage
     __syncthreads();                                 // every wave is past its last LDS operand read
 
-    store_tile<MODE, FM, FN, 2, ONLY_BF16>(acc, m0 + wm * TM, n0 + wn * TN, M, N, scale, Y, y_dtype, ldy,
+    store_tile<MODE, FM, FN, 2, ONLY_BF16 ? FQ_BF16 : ANY_OUTPUT>(acc, m0 + wm * TM, n0 + wn * TN, M, N, scale, Y, y_dtype, ldy,
                                 smem + W * (64 * TN * 2), bias);
 }
 
@@ -1183,7 +1183,7 @@ __device__ __forceinline__ void gemm_f6_wide_tile(uint8_t* smem, int m0, int n0,
     }
     __syncthreads();                                // every wave is past its last LDS operand read
 
-    store_tile<MODE_F6, FM, FN, 2, ONLY_BF16>(acc, m0 + wm * TM, n0 + wn * TN, M, N, scale, Y, y_dtype, ldy,
+    store_tile<MODE_F6, FM, FN, 2, ONLY_BF16 ? FQ_BF16 : ANY_OUTPUT>(acc, m0 + wm * TM, n0 + wn * TN, M, N, scale, Y, y_dtype, ldy,
                                    smem + wave * (64 * TN * 2), bias);
 }
 
@@ -1331,14 +1331,14 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_reg_kernel(const uint8_t* __
     probe.finish(bt.ticks);
 }
 
-template <int MODE, int BM, int BN, int BKB, int WM, int WN, int NSTAGE, int PIPE, int PP_SLICES = 2, bool ONLY_BF16 = false>
+template <int MODE, int BM, int BN, int BKB, int WM, int WN, int NSTAGE, int PIPE, int PP_SLICES = 2, int ONLY = ANY_OUTPUT>
 int launch_dma(const void* A, const void* B, int M, int N, int rowbytes, const float* s_x, const float* s_w,
                void* Y, int y_dtype, int ldy, Batch bt, hipStream_t stream)
 {
     // the DMA kernel addresses rows with 32-bit byte offsets
     if ((unsigned long long)M * rowbytes >= (1ull << 32) || (unsigned long long)N * rowbytes >= (1ull << 32))
         return fail(FQ_ERR_RANGE, "operand larger than 4 GiB");
-    auto kern = gemm_dma_kernel<MODE, BM, BN, BKB, WM, WN, NSTAGE, PIPE, PP_SLICES, ONLY_BF16>;
+    auto kern = gemm_dma_kernel<MODE, BM, BN, BKB, WM, WN, NSTAGE, PIPE, PP_SLICES, ONLY>;
     constexpr int smem = NSTAGE * (BM + BN) * BKB;
     static std::atomic<unsigned long long> attr_set{0};
     if (int rc = set_lds_limit(reinterpret_cast<const void*>(kern), smem, attr_set)) return rc;
@@ -1474,15 +1474,23 @@ int dispatch(const void* A, const void* B, int M, int N, int rowbytes, const flo
     }
     switch (v) {
     case 2: return launch_reg<MODE, 128, 128, 64, 2, 2>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
-    case 6: return launch_dma<MODE, 128, 128, 128, 2, 2, 2, 1>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+    // the kernels of direct copies have instantiations with one plain epilogue only: no spills, and less code to fetch, of which
+    // a call of 4 us notices 0.2-0.3 (128 x 128 tile, 12 x 128 x 512 x 128 4.56 -> 4.31 us, one 512 x 512 x 128 3.74 -> 3.53)
+    case 6:
+        if constexpr (MODE != MODE_BF16) {
+            if (y_dtype == FQ_BF16 && !bt.bias)
+                return launch_dma<MODE, 128, 128, 128, 2, 2, 2, 1, 2, FQ_BF16>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+            if (y_dtype == FQ_F16 && !bt.bias)
+                return launch_dma<MODE, 128, 128, 128, 2, 2, 2, 1, 2, FQ_F16>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+        }
+        return launch_dma<MODE, 128, 128, 128, 2, 2, 2, 1>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
     case 7:
-        // the large-problem kernels have an instantiation with the plain bf16 epilogue only (no spills)
         if (MODE != MODE_BF16 && y_dtype == FQ_BF16 && !bt.bias)
-            return launch_dma<MODE, 256, 256, 128, 2, 4, 2, 2, 2, true>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+            return launch_dma<MODE, 256, 256, 128, 2, 4, 2, 2, 2, FQ_BF16>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
         return launch_dma<MODE, 256, 256, 128, 2, 4, 2, 2, 2>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
     case 10:
         if (MODE != MODE_BF16 && y_dtype == FQ_BF16 && !bt.bias)
-            return launch_dma<MODE, 256, 256, 128, 2, 4, 2, 2, 4, true>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+            return launch_dma<MODE, 256, 256, 128, 2, 4, 2, 2, 4, FQ_BF16>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
         return launch_dma<MODE, 256, 256, 128, 2, 4, 2, 2, 4>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
     case 11: return launch_wide<MODE>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
     case 12: return launch_wide<MODE, true>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);

@@ -334,9 +334,10 @@ __device__ __forceinline__ void store_tile_via_lds(acc_t (&acc)[FM][FN], int row
     }
 }
 
-// ONLY_BF16: the caller guarantees y_dtype == FQ_BF16 and no bias, and only that path is compiled (a kernel
+// ONLY = an output type: the caller guarantees y_dtype == ONLY and no bias, and only that path is compiled (a kernel
 // that carries every output type keeps more live state across its main loop and spills in the epilogue).
-template <int MODE, int FM, int FN, int CH = FM, bool ONLY_BF16 = false, typename acc_t>
+constexpr int ANY_OUTPUT = -1;
+template <int MODE, int FM, int FN, int CH = FM, int ONLY = ANY_OUTPUT, typename acc_t>
 __device__ __forceinline__ void store_tile(acc_t (&acc)[FM][FN], int row0, int col0, int M, int N, float scale,
                                            void* __restrict__ Y, int y_dtype, int ldy, uint8_t* stage = nullptr,
                                            const float* __restrict__ bias = nullptr)
@@ -361,8 +362,10 @@ __device__ __forceinline__ void store_tile(acc_t (&acc)[FM][FN], int row0, int c
     typedef std::integral_constant<int, FQ_F16> f16_t;
     typedef std::integral_constant<int, FQ_F32> f32_t;
     typedef std::integral_constant<int, FQ_I32> i32_t;
-    if constexpr (MODE == MODE_BF16 || ONLY_BF16) {
+    if constexpr (MODE == MODE_BF16) {
         put(bf16_t{}, std::false_type{});
+    } else if constexpr (ONLY != ANY_OUTPUT) {
+        put(std::integral_constant<int, ONLY>{}, std::false_type{});
     } else if (y_dtype == FQ_I32) {
         put(i32_t{}, std::false_type{});
     } else if (bias) {
