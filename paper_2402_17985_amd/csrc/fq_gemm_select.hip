@@ -69,45 +69,28 @@ int check_forced_variant(int bits, int rowbytes)
 
 namespace {
 // Products of few output tiles.  `done` says whether a kernel for them was chosen (and its launch attempted).
-//   - At most 4 rows, or 4-bit values and at most 16: the weights go straight into registers (gemm_skinny; INT8 at 8 and 16
-//     rows, 6400 x 15360: 23.0, 24.3 us against 20.9, 21.0 for the stream kernel; nibbles 10.2, 10.4 against 11.6, 11.6).
-//     Its 512 threads per 16 columns are more than a launch holds from 2^27 columns on; those go to the 128-column tiles.
-//   - Otherwise the smallest tile with which one round of workgroups, one per CU, covers the output: a larger one leaves CUs
-//     idle, a smaller one takes a second round and reads the operands more often (INT8 12544 x 4096, 256 rows: 32 x 64 30.6,
-//     64 x 64 21.7, 96 x 64 25.2 us).  Up to 96 x 64 the reduction is split over the waves.  Beyond it INT8 goes through the
-//     ring (4608 x 11008, 128 rows, 128 x 64: 16.3 us, by split waves 18.5), 4-bit values stay with split waves (12544 x 4096, 500
-//     rows: nibbles 29.5 us, ring 37.6, 128 x 128 kernel 36.3; E3M2 27.3, its 256 x 256 kernel 46.2) up to 128 x 64; 128 x 128 tiles
-//     through the ring for INT8 and nibbles (4608 x 11008, 200 rows: 19.4 and 20.7 us against 26.0 and 21.9).
-//   - Batched products with a reduction of under four stages stay with the tiled kernels: there is nothing to split.
 int launch_few_tiles(const void* A, const void* B, int M, int N, int Kpad, int bits, const float* s_x, const float* s_w, void* Y,
                      int y_dtype, int ldy, const Batch& bt, hipStream_t stream, bool& done)
 {
     done = false;
+    if (g_variant >= 0) return FQ_OK;
     const int rowbytes = bits == 8 ? Kpad : bits == 4 ? Kpad / 2 : Kpad / 4 * 3;
-    if (g_variant >= 0 || (bt.count > 1 && rowbytes < 512)) return FQ_OK;
-    if ((M <= 4 && skinny_holds(N)) || (bits != 8 && M <= 16 && N <= 16384)) {
-        done = true;
-        return launch_gemm_skinny(bits, A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
-    }
-    const long long cus = compute_units();
-    auto one_round = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * bt.count <= cus; };
-    auto stream_tile = [&](StreamTile t) {
-        done = true;
+    const FewTilesChoice c = few_tiles(M, N, rowbytes, bits, bt.count, compute_units());
+    done = c.kernel != FewTiles::TILED;
+    const auto is = [&](int bm, int bn) { return c.bm == bm && c.bn == bn; };
+    switch (c.kernel) {
+    case FewTiles::SKINNY: return launch_gemm_skinny(bits, A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+    case FewTiles::STREAM: {
+        const StreamTile t = is(32, 32) ? STREAM_32x32 : is(32, 64) ? STREAM_32x64 : is(64, 64) ? STREAM_64x64 :
+                             is(32, 128) ? STREAM_32x128 : is(96, 64) ? STREAM_96x64 : is(128, 64) ? STREAM_128x64 : STREAM_64x128;
         return launch_gemm_stream(t, bits, A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
-    };
-    auto ring_tile = [&](RingTile t) {
-        done = true;
+    }
+    case FewTiles::RING: {
+        const RingTile t = is(128, 64) ? RING_128x64 : is(64, 128) ? RING_64x128 : RING_128x128;
         return launch_gemm_ring(t, bits, A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
-    };
-    if (one_round(32, 32)) return stream_tile(STREAM_32x32);
-    if (one_round(32, 64)) return stream_tile(STREAM_32x64);
-    if (one_round(64, 64)) return stream_tile(STREAM_64x64);
-    if (one_round(32, 128)) return stream_tile(STREAM_32x128);
-    if (one_round(96, 64)) return stream_tile(STREAM_96x64);
-    if (one_round(128, 64)) return bits == 8 ? ring_tile(RING_128x64) : stream_tile(STREAM_128x64);
-    if (one_round(64, 128)) return bits == 8 ? ring_tile(RING_64x128) : stream_tile(STREAM_64x128);
-    if (one_round(128, 128) && bits != FQ_BITS_I4_E3M2) return ring_tile(RING_128x128);
-    return FQ_OK;
+    }
+    default: return FQ_OK;
+    }
 }
 }  // namespace
 

@@ -21,6 +21,65 @@ inline bool launch_holds(long long workgroups, int threads) { return workgroups 
 constexpr int SKINNY_COLUMNS = 16, SKINNY_THREADS = 512;
 inline bool skinny_holds(long long N) { return launch_holds((N + SKINNY_COLUMNS - 1) / SKINNY_COLUMNS, SKINNY_THREADS); }
 
+// Integer products of few output tiles: which kernel takes one.  TILED: none of these, the large-tile kernels.
+enum class FewTiles { TILED, SKINNY, STREAM, RING };
+struct FewTilesChoice {
+    FewTiles kernel;
+    int bm, bn;      // tile of STREAM and RING
+};
+
+// The tiles in the order in which they are tried, and the shortest reduction (bytes of a quantized row) from which each is taken,
+// for INT8, packed nibbles and E3M2, unbatched and batched (no batched E3M2).  Below it there is too little to split: the partial
+// sums that meet in LDS (64 KiB of them for 64 x 64 tiles and eight waves) cost more than the latency that is hidden.
+// Us, this tile / the 128 x 128 tiles (E3M2: 256 x 256) at half of it and from it on: INT8 512 x 2048, 64 x 64 tiles, 256 bytes
+// 4.9 / 4.2, 640 5.5 / 6.3, 1024 5.7 / 8.4; 384 x 4096, 96 x 64 tiles, 512 bytes 6.9 / 6.6, 1024 7.9 / 9.1; nibbles 512 x 4096, 128 x 64
+// tiles, 512 bytes 9.4 / 7.6, 1024 11.3 / 10.3, 2048 14.9 / 15.2; E3M2 the same 384 bytes 8.5 / 6.8, 1152 10.0 / 10.1, 1536 11.0 / 11.6;
+// batched nibbles 12 x 256 x 512, 128 x 64 tiles, 512 bytes 9.3 / 8.1, 1024 11.8 / 12.5.
+constexpr int NEVER = 1 << 30;
+struct FewTilesRow {
+    int bm, bn, from[2][3];
+};
+constexpr FewTilesRow FEW_TILES[] = {
+    {32, 32, {{0, 0, 0}, {512, 512, NEVER}}},
+    {32, 64, {{0, 0, 0}, {512, 512, NEVER}}},
+    {64, 64, {{640, 384, 0}, {512, 512, NEVER}}},
+    {32, 128, {{0, 0, 0}, {512, 512, NEVER}}},
+    {96, 64, {{1024, 1024, 384}, {1024, 512, NEVER}}},
+    {128, 64, {{0, 2048, 1152}, {512, 1024, NEVER}}},
+    {64, 128, {{0, 1280, 768}, {512, 1024, NEVER}}},
+    {128, 128, {{0, 0, NEVER}, {512, 512, NEVER}}},
+};
+
+//   - At most 4 rows, or 4-bit values and at most 16: the weights go straight into registers (gemm_skinny; INT8 at 8 and 16
+//     rows, 6400 x 15360: 23.0, 24.3 us against 20.9, 21.0 for the stream kernel; nibbles 10.2, 10.4 against 11.6, 11.6).
+//     Its 512 threads per 16 columns are more than a launch holds from 2^27 columns on; those go to the 128-column tiles.
+//   - Otherwise the smallest tile with which one round of workgroups, one per CU, covers the output: a larger one leaves CUs
+//     idle, a smaller one takes a second round and reads the operands more often (INT8 12544 x 4096, 256 rows: 32 x 64 30.6,
+//     64 x 64 21.7, 96 x 64 25.2 us).  Up to 96 x 64 the reduction is split over the waves.  Beyond it INT8 goes through the
+//     ring (4608 x 11008, 128 rows, 128 x 64: 16.3 us, by split waves 18.5), 4-bit values stay with split waves (12544 x 4096, 500
+//     rows: nibbles 29.5 us, ring 37.6, 128 x 128 kernel 36.3; E3M2 27.3, its 256 x 256 kernel 46.2) up to 128 x 64; 128 x 128 tiles
+//     through the ring for INT8 and nibbles (4608 x 11008, 200 rows: 19.4 and 20.7 us against 26.0 and 21.9).
+//   - Batched products with a reduction of under 512 bytes stay with the tiled kernels throughout.
+//   - Tall INT8 outputs of 128 x 64 tiles from 1024 bytes on (2048 x 1024, us, ring / 128 x 128 tiles: 640 bytes 6.2 / 5.5, 1024 7.6 /
+//     8.0; wide 512 x 4096 of 640 bytes 6.1 / 7.6), batched nibbles of one 128-column tile not through the ring (64 x 512 x 128 of 1024
+//     bytes 15.6 / 14.3, 40 x 512 x 128 13.0 / 13.2; 4 x 700 x 700 12.3 / 13.9).
+inline FewTilesChoice few_tiles(long long M, long long N, int rowbytes, int bits, long long count, long long cus)
+{
+    const int batched = count > 1 ? 1 : 0, mode = bits == 8 ? 0 : bits == 4 ? 1 : 2;
+    const FewTilesChoice tiled = {FewTiles::TILED, 0, 0};
+    if (batched && rowbytes < 512) return tiled;
+    if ((M <= 4 && skinny_holds(N)) || (mode != 0 && M <= 16 && N <= 16384)) return {FewTiles::SKINNY, 0, 0};
+    for (const FewTilesRow& t : FEW_TILES) {
+        if ((M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn) * count > cus) continue;
+        if (rowbytes < t.from[batched][mode]) return tiled;
+        const bool large = t.bm * t.bn == 128 * 128, middle = t.bm * t.bn == 128 * 64;
+        if (mode == 0 && !batched && t.bm == 128 && t.bn == 64 && M > N && rowbytes < 1024) return tiled;
+        if (mode == 1 && batched && large && N <= 128) return tiled;
+        return {large || (mode == 0 && middle) ? FewTiles::RING : FewTiles::STREAM, t.bm, t.bn};
+    }
+    return tiled;
+}
+
 // Grid of the absmax pass: `blocks` workgroups side by side cover the columns (64 * vec of them each), `strips` of
 // rows_per_strip rows each cover the rows.  Every workgroup leaves one candidate.
 struct AbsmaxGrid {

@@ -18,6 +18,11 @@ extern "C" void absmax(long long M, long long K, int vec, int* out)
     out[0] = a.blocks; out[1] = a.strips; out[2] = a.rows_per_strip;
 }
 extern "C" int skinny(long long N) { return fq::skinny_holds(N); }
+extern "C" void few_tiles(long long M, long long N, int rowbytes, int bits, long long count, long long cus, int* out)
+{
+    const fq::FewTilesChoice c = fq::few_tiles(M, N, rowbytes, bits, count, cus);
+    out[0] = (int)c.kernel; out[1] = c.bm; out[2] = c.bn;
+}
 extern "C" int overlap(unsigned long long a, unsigned long long na, unsigned long long b, unsigned long long nb)
 {
     return fq::overlap((const void*)a, na, (const void*)b, nb);
@@ -69,3 +74,54 @@ def test_weight_streaming_launches_stay_within_32_bits(rules):
     for N in (1, 16, 4097, 2**27 - 16, 2**27 - 15, 2**27 - 1, 2**27, 2**28 - 1):
         assert rules.skinny(ctypes.c_longlong(N)) == ((N + 15) // 16 * 512 < 2**32)
     assert not rules.skinny(ctypes.c_longlong(2**27 - 1))
+
+
+TILED, SKINNY, STREAM, RING = range(4)
+
+
+def _few_tiles(rules, bits, M, N, rowbytes, count=1, cus=256):
+    out = (ctypes.c_int * 3)()
+    q = ctypes.c_longlong
+    rules.few_tiles(q(M), q(N), rowbytes, bits, q(count), q(cus), out)
+    return tuple(out)
+
+
+# Both sides of every line: (bits, M, N, batch, row bytes of a shorter reduction -> tiled kernels, of a longer one -> this)
+@pytest.mark.parametrize("bits,M,N,count,short,long,want", [
+    (8, 512, 2048, 1, 512, 640, (STREAM, 64, 64)), (4, 512, 2048, 1, 256, 384, (STREAM, 64, 64)), (8, 32, 256, 32, 480, 512, (STREAM, 32, 32)),
+    (8, 384, 4096, 1, 896, 1024, (STREAM, 96, 64)), (4, 384, 4096, 1, 896, 1024, (STREAM, 96, 64)), (6, 384, 4096, 1, 288, 384, (STREAM, 96, 64)),
+    (4, 512, 4096, 1, 1920, 2048, (STREAM, 128, 64)), (6, 512, 4096, 1, 1056, 1152, (STREAM, 128, 64)), (8, 2048, 1024, 1, 896, 1024, (RING, 128, 64)),
+    (4, 64, 32768, 1, 1152, 1280, (STREAM, 64, 128)), (6, 64, 32768, 1, 672, 768, (STREAM, 64, 128)),
+    (8, 256, 128, 40, 896, 1024, (STREAM, 96, 64)), (4, 256, 128, 40, 480, 512, (STREAM, 96, 64)), (4, 384, 128, 40, 896, 1024, (STREAM, 128, 64)),
+    (4, 40, 1500, 20, 896, 1024, (STREAM, 64, 128)), (8, 768, 128, 40, 480, 512, (RING, 128, 128)), (4, 700, 700, 4, 480, 512, (RING, 128, 128)),
+])
+def test_reductions_too_short_to_split_stay_with_the_tiled_kernels(rules, bits, M, N, count, short, long, want):
+    assert _few_tiles(rules, bits, M, N, short, count)[0] == TILED
+    assert _few_tiles(rules, bits, M, N, long, count) == want
+
+
+@pytest.mark.parametrize("bits,M,N,rowbytes,count,want", [
+    (8, 4, 24576, 32, 1, (SKINNY, 0, 0)), (8, 5, 4096, 32, 1, (STREAM, 32, 32)), (4, 16, 16384, 16, 1, (SKINNY, 0, 0)), (4, 16, 16400, 128, 1, (STREAM, 32, 128)),
+    (8, 1, 2**27 - 1, 32, 1, (TILED, 0, 0)), (8, 512, 4096, 128, 1, (RING, 128, 64)), (8, 512, 8192, 32, 1, (RING, 128, 128)), (6, 512, 8192, 3072, 1, (TILED, 0, 0)),
+    (4, 768, 128, 2048, 40, (TILED, 0, 0)), (8, 8192, 4096, 4096, 1, (TILED, 0, 0)), (8, 1, 128, 480, 160, (TILED, 0, 0)), (8, 1, 128, 512, 160, (SKINNY, 0, 0)),
+])
+def test_products_of_few_tiles(rules, bits, M, N, rowbytes, count, want):
+    assert _few_tiles(rules, bits, M, N, rowbytes, count) == want
+
+
+@pytest.mark.parametrize("bits", [8, 4, 6])
+def test_every_choice_has_a_kernel(rules, bits):
+    stream = {(32, 32), (32, 64), (64, 64), (32, 128), (96, 64)} | ({(128, 64), (64, 128)} if bits != 8 else set())
+    ring = {8: {(128, 64), (64, 128), (128, 128)}, 4: {(128, 128)}, 6: set()}[bits]
+    seen = set()
+    for cus in (32, 80, 256, 304):
+        for M in (1, 4, 5, 16, 17, 40, 64, 96, 130, 300, 500, 1000, 2000, 9000):
+            for N in (16, 100, 500, 1000, 2048, 4096, 9000, 16384, 16385, 30000):
+                for rowbytes in (96, 384, 768, 1536, 6144):
+                    for count in (1, 3, 40) if bits != 6 else (1,):
+                        kernel, bm, bn = _few_tiles(rules, bits, M, N, rowbytes, count, cus)
+                        assert kernel in (TILED, SKINNY) or (bm, bn) in (stream if kernel == STREAM else ring)
+                        if kernel in (STREAM, RING):
+                            assert -(-M // bm) * -(-N // bn) * count <= cus
+                            seen.add((kernel, bm, bn))
+    assert seen == {(STREAM, *t) for t in stream} | {(RING, *t) for t in ring}
