@@ -460,7 +460,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const uint8_t* __
     extern __shared__ __align__(16) uint8_t smem[];
     const ClockProbe probe(bt.ticks);
     int problem, first;
-    const bool banded = place_of_workgroup(problem, first);
+    const bool banded = place_of_workgroup((int)gridDim.x, (int)gridDim.y, problem, first);
     A += (size_t)problem * bt.stride_a;
     B += (size_t)problem * bt.stride_b;
     Y = static_cast<uint8_t*>(Y) + (size_t)problem * bt.stride_y;

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_ring_kernel(const uint8_t* 
     extern __shared__ __align__(16) uint8_t smem[];
     const ClockProbe probe(bt.ticks);
     int problem, id, tile_m, tile_n;
-    if (place_of_workgroup(problem, id)) tile_of_logical(id, tiles_m, tiles_n, tile_m, tile_n);
+    if (place_of_workgroup(tiles_m * tiles_n, bt.count, problem, id)) tile_of_logical(id, tiles_m, tiles_n, tile_m, tile_n);
     else tile_of_workgroup(id, tiles_m * tiles_n, tiles_m, tiles_n, tile_m, tile_n);
     A += (size_t)problem * bt.stride_a;
     B += (size_t)problem * bt.stride_b;

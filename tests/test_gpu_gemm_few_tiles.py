@@ -121,3 +121,49 @@ def test_batched_tiles_and_their_order(batch, M, N, K, bits):
     (fq.fq_bmm_i8 if bits == 8 else fq.fq_bmm_i4)(X.view(batch, M, -1), W.view(batch, N, -1), None, None, Y)
     want = torch.bmm(xq.view(batch, M, K).double(), wq.view(batch, N, K).double().transpose(1, 2).contiguous())
     assert torch.equal(Y.double(), want)
+
+
+def _device_operand(g, rows, K, bits):
+    """(integer values as float64, the same in storage), made on the device: long reductions of many columns."""
+    lo, hi = (-128, 128) if bits == 8 else (-8, 8)
+    q = torch.randint(lo, hi, (rows, K), dtype=torch.int8, device=DEV, generator=g)
+    if bits == 8:
+        return q.double(), q
+    if bits == 4:
+        return q.double(), ((q[:, 0::2] & 15) | ((q[:, 1::2] & 15) << 4)).view(torch.uint8)
+    # the quantizer with an identity map and the bound 7 multiplies by one: it stores these integers' codes
+    codes, s = torch.empty((K // 128, rows, 96), dtype=torch.uint8, device=DEV), torch.empty(1, dtype=torch.float32, device=DEV)
+    src, rep = torch.arange(K, dtype=torch.int32, device=DEV), torch.ones(K, dtype=torch.int32, device=DEV)
+    ws = torch.empty(fq.fq_act_workspace_bytes(K, K), dtype=torch.uint8, device=DEV)
+    fq.fq_flatten_quant_act(q.float(), src, rep, 6, codes, s, ws, absmax_in=scalar(7.0))
+    return q.double(), codes
+
+
+# Reductions long enough for every wave's main loop to reuse its registers or its stages: the weight-streaming kernel reloads
+# a register slot from five k-steps per wave on (40 steps of 128 bytes, 96 in E3M2, with eight waves, 20 with four), the
+# split-reduction kernels refill a buffer from 17 stages on at most, the ring from seven.  Lengths that give the waves four
+# and five steps, six and seven, and more, the last step partial.
+@pytest.mark.parametrize("bits,K", [(8, 4128), (8, 6304), (8, 12576), (4, 8256), (4, 12576), (4, 22048), (6, 4224), (6, 6400), (6, 9088)])
+@pytest.mark.parametrize("M,N", [(1, 300), (4, 9001), (3, 20000), (16, 300), (16, 5000), (16, 16380),             # rows into registers
+                                 (33, 1000), (32, 11008), (130, 4000), (20, 20000), (90, 16001),                  # split over waves
+                                 (125, 15999), (60, 30000), (257, 9999)])                                         # the same, or the ring
+def test_long_reductions(M, N, bits, K):
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    xq, X = _device_operand(g, M, K, bits)
+    wq, W = _device_operand(g, N, K, bits)
+    Y = torch.full((M, N), 0x55555555, dtype=torch.int32, device=DEV)
+    _gemm(bits, X, W, None, None, None, Y)
+    assert torch.equal(Y.double(), xq @ wq.t().contiguous())
+
+
+# Batched: problems dealt to the XCDs in bands, with one tile each and with several, reductions that refill the buffers
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("batch,M,N,K", [(9, 60, 60, 4192), (7, 100, 200, 4192), (40, 250, 128, 2112), (12, 250, 500, 2112), (13, 65, 129, 1088),
+                                         (3, 700, 701, 1088), (20, 40, 1500, 2624), (40, 768, 128, 1088)])
+def test_batched_long_reductions(batch, M, N, K, bits):
+    g = torch.Generator(device=DEV).manual_seed(M + N)
+    xq, X = _device_operand(g, batch * M, K, bits)
+    wq, W = _device_operand(g, batch * N, K, bits)
+    Y = torch.full((batch, M, N), -1, dtype=torch.int32, device=DEV)
+    (fq.fq_bmm_i8 if bits == 8 else fq.fq_bmm_i4)(X.view(batch, M, -1), W.view(batch, N, -1), None, None, Y)
+    assert torch.equal(Y.double(), torch.bmm(xq.view(batch, M, K), wq.view(batch, N, K).transpose(1, 2).contiguous()))
