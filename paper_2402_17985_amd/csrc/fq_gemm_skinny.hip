@@ -159,13 +159,17 @@ int launch_mode(const void* A, const void* B, int M, int N, int rowbytes, const 
                 int y_dtype, int ldy, Batch bt, hipStream_t stream)
 {
     // Column fragments per workgroup: X is read once per workgroup, so wider is less traffic from L2, but the workgroups
-    // should still number about the CUs.  The smallest FN that makes them at most 256 (two when none does: several rounds
-    // then even out).  Nibbles, 16 rows, us at FN = 1 / 2 / 4: 4608 x 11008 8.8 / 9.0 / 8.3, 6400 x 15360 13.6 / 11.3 / 10.6,
-    // 8960 x 24576 29.6 / 25.0 / 26.7; with a row or few (X is cached) FN = 1 is best throughout: 20.4 / 20.6 / 24.4.
-    const int FN = M <= 4 || N <= 4096 ? 1 : N <= 8192 || N > 16384 ? 2 : 4;
-    if (FN == 1) return launch<MODE, 1, 8, 2>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
-    if (FN == 2) return launch<MODE, 2, 8, 2>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
-    return launch<MODE, 4, 4, 2>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+    // should still number about the CUs: the smallest FN that makes them at most those.  Nibbles, 16 rows, us at FN = 1 / 2 / 4
+    // on 256 CUs: 4608 x 11008 8.8 / 9.0 / 8.3, 6400 x 15360 13.6 / 11.3 / 10.6.  With a row or few (X is cached) FN = 1 is best
+    // throughout (8960 x 24576 20.4 / 20.6 / 24.4); INT8 comes with at most 4 rows.
+    if constexpr (MODE != MODE_I8) {
+        const long long cus = compute_units();
+        if (M > 4 && (N + 15) / 16 > cus) {
+            if ((N + 31) / 32 <= cus) return launch<MODE, 2, 8, 2>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+            return launch<MODE, 4, 4, 2>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
+        }
+    }
+    return launch<MODE, 1, 8, 2>(A, B, M, N, rowbytes, s_x, s_w, Y, y_dtype, ldy, bt, stream);
 }
 
 }  // namespace

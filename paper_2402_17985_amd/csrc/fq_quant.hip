@@ -1077,8 +1077,7 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
         const size_t lds = DIRECT_LDS_FIXED + (size_t)R * kq + tail_src;
         // what the CUs hold at once: 1024 threads (128 registers each) and 160 KiB of LDS
         const int occ = std::max(1, std::min((int)(160u * 1024u / lds), 1024 / nthr));
-        // a row each while there are CUs for them, then strips of R rows
-        const int nblk = std::min(std::max((M + R - 1) / R, std::min(M, 256)), 256 * occ);
+        const int nblk = direct_workgroups(M, R, compute_units(), occ);
         direct_kernel_t kern = nullptr;
         int rc;
         if (P == 1) rc = bits == 8 ? direct_kernel<DT, 8, 1>(&kern) : bits == 6 ? direct_kernel<DT, 6, 1>(&kern) : direct_kernel<DT, 4, 1>(&kern);

@@ -50,7 +50,7 @@ constexpr FewTilesRow FEW_TILES[] = {
     {128, 128, {{0, 0, NEVER}, {512, 512, NEVER}}},
 };
 
-//   - At most 4 rows, or 4-bit values and at most 16: the weights go straight into registers (gemm_skinny; INT8 at 8 and 16
+//   - At most 4 rows, or 4-bit values, at most 16 and at most 64 columns per CU: the weights go straight into registers (gemm_skinny; INT8 at 8 and 16
 //     rows, 6400 x 15360: 23.0, 24.3 us against 20.9, 21.0 for the stream kernel; nibbles 10.2, 10.4 against 11.6, 11.6).
 //     Its 512 threads per 16 columns are more than a launch holds from 2^27 columns on; those go to the 128-column tiles.
 //   - Otherwise the smallest tile with which one round of workgroups, one per CU, covers the output: a larger one leaves CUs
@@ -68,7 +68,7 @@ inline FewTilesChoice few_tiles(long long M, long long N, int rowbytes, int bits
     const int batched = count > 1 ? 1 : 0, mode = bits == 8 ? 0 : bits == 4 ? 1 : 2;
     const FewTilesChoice tiled = {FewTiles::TILED, 0, 0};
     if (batched && rowbytes < 512) return tiled;
-    if ((M <= 4 && skinny_holds(N)) || (mode != 0 && M <= 16 && N <= 16384)) return {FewTiles::SKINNY, 0, 0};
+    if ((M <= 4 && skinny_holds(N)) || (mode != 0 && M <= 16 && N <= 64 * cus)) return {FewTiles::SKINNY, 0, 0};
     for (const FewTilesRow& t : FEW_TILES) {
         if ((M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn) * count > cus) continue;
         if (rowbytes < t.from[batched][mode]) return tiled;
@@ -78,6 +78,13 @@ inline FewTilesChoice few_tiles(long long M, long long N, int rowbytes, int bits
         return {large || (mode == 0 && middle) ? FewTiles::RING : FewTiles::STREAM, t.bm, t.bn};
     }
     return tiled;
+}
+
+// Workgroups of the one-kernel quantizer, each of which walks a run of the M rows in strips of R: a row each while there are
+// CUs for them, then strips, and no more than the CUs hold at once (`resident` per CU).
+inline int direct_workgroups(int M, int R, int cus, int resident)
+{
+    return (int)std::min<long long>(std::max((M + (long long)R - 1) / R, (long long)std::min(M, cus)), (long long)cus * resident);
 }
 
 // Grid of the absmax pass: `blocks` workgroups side by side cover the columns (64 * vec of them each), `strips` of

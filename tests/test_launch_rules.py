@@ -23,6 +23,7 @@ extern "C" void few_tiles(long long M, long long N, int rowbytes, int bits, long
     const fq::FewTilesChoice c = fq::few_tiles(M, N, rowbytes, bits, count, cus);
     out[0] = (int)c.kernel; out[1] = c.bm; out[2] = c.bn;
 }
+extern "C" int direct(int M, int R, int cus, int resident) { return fq::direct_workgroups(M, R, cus, resident); }
 extern "C" int overlap(unsigned long long a, unsigned long long na, unsigned long long b, unsigned long long nb)
 {
     return fq::overlap((const void*)a, na, (const void*)b, nb);
@@ -101,7 +102,7 @@ def test_reductions_too_short_to_split_stay_with_the_tiled_kernels(rules, bits, 
 
 
 @pytest.mark.parametrize("bits,M,N,rowbytes,count,want", [
-    (8, 4, 24576, 32, 1, (SKINNY, 0, 0)), (8, 5, 4096, 32, 1, (STREAM, 32, 32)), (4, 16, 16384, 16, 1, (SKINNY, 0, 0)), (4, 16, 16400, 128, 1, (STREAM, 32, 128)),
+    (8, 4, 24576, 32, 1, (SKINNY, 0, 0)), (8, 5, 4096, 32, 1, (STREAM, 32, 32)), (4, 16, 16384, 16, 1, (SKINNY, 0, 0)), (4, 16, 16400, 128, 1, (STREAM, 32, 128)), (6, 16, 16384, 96, 1, (SKINNY, 0, 0)),
     (8, 1, 2**27 - 1, 32, 1, (TILED, 0, 0)), (8, 512, 4096, 128, 1, (RING, 128, 64)), (8, 512, 8192, 32, 1, (RING, 128, 128)), (6, 512, 8192, 3072, 1, (TILED, 0, 0)),
     (4, 768, 128, 2048, 40, (TILED, 0, 0)), (8, 8192, 4096, 4096, 1, (TILED, 0, 0)), (8, 1, 128, 480, 160, (TILED, 0, 0)), (8, 1, 128, 512, 160, (SKINNY, 0, 0)),
 ])
@@ -125,3 +126,13 @@ def test_every_choice_has_a_kernel(rules, bits):
                             assert -(-M // bm) * -(-N // bn) * count <= cus
                             seen.add((kernel, bm, bn))
     assert seen == {(STREAM, *t) for t in stream} | {(RING, *t) for t in ring}
+
+
+def test_lines_follow_the_number_of_compute_units(rules):
+    """64 columns per CU for 4-bit values of up to 16 rows; the quantizer's workgroups a row each up to the CUs, then strips."""
+    for cus in (32, 64, 256):
+        assert _few_tiles(rules, 4, 16, 64 * cus, 2048, cus=cus)[0] == SKINNY
+        assert _few_tiles(rules, 4, 16, 64 * cus + 1, 2048, cus=cus)[0] != SKINNY
+        assert [rules.direct(M, 4, cus, 2) for M in (1, cus, 2 * cus, 4 * cus, 6 * cus, 8 * cus, 100 * cus)] == \
+            [1, cus, cus, cus, (6 * cus + 3) // 4, 2 * cus, 2 * cus]
+    assert rules.direct(2**31 - 1, 1, 256, 16) == 4096
