@@ -159,36 +159,8 @@ __global__ __launch_bounds__(NTHR, 4) void linear_decode_kernel(const void* __re
             if ((unsigned)s[i] < (unsigned)K && n[i] > 0) m = n[i] < TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
             q[i] = quant1<BITS>(x[i], m);
         }
-        if constexpr (MODE == MODE_I8) {
-            v4u o;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                o[i] = (uint32_t)(q[4 * i] & 0xff) | ((uint32_t)(q[4 * i + 1] & 0xff) << 8) |
-                       ((uint32_t)(q[4 * i + 2] & 0xff) << 16) | ((uint32_t)(q[4 * i + 3] & 0xff) << 24);
-            *reinterpret_cast<v4u*>(xq + 16 * g) = o;
-        } else if constexpr (MODE == MODE_I4) {
-            v2u o;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                o[i] = 0;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) o[i] |= (uint32_t)(q[8 * i + j] & 0xf) << (4 * j);
-            }
-            *reinterpret_cast<v2u*>(xq + 8 * g) = o;
-        } else {
-            // the blocked E3M2 layout of a one-row matrix: block g / 8, units of a 48-byte group stored X Y Y X
-            const u3 v = pack16_e3m2(q);
-            const int gi = g & 7, e = gi & 1;
-            uint8_t* grp = xq + (g >> 3) * 96 + 48 * (gi >> 2);
-            if (((gi >> 1) & 1) == 0) {
-                *reinterpret_cast<u3*>(grp + 12 * e) = v;
-            } else if (e == 0) {
-                *reinterpret_cast<u3*>(grp + 32) = v;
-            } else {
-                *reinterpret_cast<uint32_t*>(grp + 44) = v.a;
-                *reinterpret_cast<v2u*>(grp + 24) = v2u{v.b, v.c};
-            }
-        }
+        if constexpr (MODE == MODE_F6) store16_e3m2(q, xq, 1, 0, g);    // a matrix of one row
+        else pack16<BITS>(q, xq + (MODE == MODE_I8 ? 16 : 8) * g);
     };
     if (tid < G) quantize(tid, s0, n0, x0);
     for (int g = tid + NTHR; g < G; g += NTHR) {

@@ -338,11 +338,9 @@ __global__ __launch_bounds__(256) void flatten_quant_kernel(const void* __restri
         for (int j = 0; j < 4; ++j) { s[4 * i + j] = sv[j]; m[4 * i + j] = mv[j]; }
     }
     bool contig = (s[0] >= 0) && (s[0] % VEC == 0) && (s[0] + 15 < K);
-    uint32_t pad = 0;                                          // padding / invalid slots: 0 whatever X holds
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         if ((unsigned)s[i] >= (unsigned)K) {
-            pad |= 1u << i;
             s[i] = 0;
             m[i] = PEEL ? __builtin_inff() : 0.0f;
             contig = false;
@@ -368,7 +366,10 @@ __global__ __launch_bounds__(256) void flatten_quant_kernel(const void* __restri
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) x[i] = ((pad >> i) & 1) ? 0.0f : Elem<DT>::widen(row[s[i]]);
+            for (int i = 0; i < 16; ++i) {
+                x[i] = Elem<DT>::widen(row[s[i]]);
+                if constexpr (!PEEL) x[i] = gathered(x[i]);
+            }
         }
         int q[16];
 #pragma unroll
@@ -380,24 +381,7 @@ __global__ __launch_bounds__(256) void flatten_quant_kernel(const void* __restri
                 q[i] = quant1<BITS>(x[i], m[i]);
             }
         }
-        if (BITS == 8) {
-            v4u w;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                w[i] = (uint32_t)(q[4 * i] & 0xff) | ((uint32_t)(q[4 * i + 1] & 0xff) << 8) |
-                       ((uint32_t)(q[4 * i + 2] & 0xff) << 16) | ((uint32_t)(q[4 * i + 3] & 0xff) << 24);
-            *reinterpret_cast<v4u*>(o) = w;
-        } else {
-            v2u w;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                uint32_t acc = 0;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc |= (uint32_t)(q[8 * i + j] & 0xf) << (4 * j);
-                w[i] = acc;
-            }
-            *reinterpret_cast<v2u*>(o) = w;
-        }
+        pack16<BITS>(q, o);
     }
 }
 
@@ -437,7 +421,7 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
     const int nr = min(M - r0, R);
     // bytes of an output row and of one group of 16 slots: 16 (INT8), 8 (INT4 nibbles), 12 (E3M2 codes)
     constexpr int GB = (BITS == 8) ? 16 : (BITS == 4 ? 8 : 12);
-    // INT8 / INT4 rows are dense (E3M2 output has its own addressing, see store_e3m2)
+    // INT8 / INT4 rows are dense (E3M2 output has its own addressing, see store16_e3m2)
     const size_t orow_bytes = (size_t)(Kpad >> 4) * GB;
     auto group_ofs = [&](int g) -> size_t { return (size_t)g * GB; };
 
@@ -458,47 +442,6 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
     }
     for (int t = threadIdx.x; t < NT; t += nthr) tf[t] = cflag[NH + t];
 
-    auto pack_store = [&](const int (&q)[16], uint8_t* o) {
-        if (BITS == 8) {
-            v4u w;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                w[i] = (uint32_t)(q[4 * i] & 0xff) | ((uint32_t)(q[4 * i + 1] & 0xff) << 8) |
-                       ((uint32_t)(q[4 * i + 2] & 0xff) << 16) | ((uint32_t)(q[4 * i + 3] & 0xff) << 24);
-            *reinterpret_cast<v4u*>(o) = w;
-        } else if (BITS == 6) {
-            (void)o;                                // E3M2 output goes through store_e3m2
-        } else {
-            v2u w;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                uint32_t acc = 0;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc |= (uint32_t)(q[8 * i + j] & 0xf) << (4 * j);
-                w[i] = acc;
-            }
-            *reinterpret_cast<v2u*>(o) = w;
-        }
-    };
-    // E3M2 output, blocked along k: block t (codes 128 t .. 128 t + 127) holds 96 bytes of every row in turn.
-    // A row's 96 bytes are two 48-byte groups of 64 codes; the 24-byte bit stream of each 32-code unit a is
-    // split into its first 16 bytes X_a and last 8 bytes Y_a, and the group is stored X_a Y_a Y_b X_b with
-    // (a, b) = (0, 1) in rows whose index has bit 4 clear and (1, 0) in the others (what the GEMM's LDS reads
-    // want).  A thread's 16 codes are half a unit: stream bytes 0..11 (e = 0) or 12..23 (e = 1).
-    auto store_e3m2 = [&](const int (&q)[16], int row, int g) {
-        const u3 v = pack16_e3m2(q);
-        const int gi = g & 7, e = gi & 1;
-        uint8_t* grp = out + ((size_t)(g >> 3) * (size_t)M + (size_t)row) * 96 + 48 * (gi >> 2);
-        const bool mirrored = (((gi >> 1) ^ (row >> 4)) & 1) != 0;
-        if (!mirrored) {
-            *reinterpret_cast<u3*>(grp + 12 * e) = v;                 // X at 0, Y at 16: the plain stream
-        } else if (e == 0) {
-            *reinterpret_cast<u3*>(grp + 32) = v;                     // X at 32
-        } else {
-            *reinterpret_cast<uint32_t*>(grp + 44) = v.a;             // the last 4 bytes of X
-            *reinterpret_cast<v2u*>(grp + 24) = v2u{v.b, v.c};        // Y at 24
-        }
-    };
     // the general form of one group over rows [ra, rb) of the strip: every slot's source element is
     // gathered from global memory; identity slots of the head also leave their value in LDS
     auto gather_group = [&](int g, int ra, int rb, bool to_lds) {
@@ -512,21 +455,20 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
 #pragma unroll
             for (int j = 0; j < 4; ++j) { s[4 * i + j] = sv[j]; m[4 * i + j] = mv[j]; }
         }
-        bool ident[16], pad[16];                                // padding / invalid slots: 0 whatever X holds
+        bool ident[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             ident[i] = to_lds && s[i] == p0 + i;
-            pad[i] = (unsigned)s[i] >= (unsigned)K;
-            if (pad[i]) { s[i] = 0; m[i] = 0.0f; }
+            if ((unsigned)s[i] >= (unsigned)K) { s[i] = 0; m[i] = 0.0f; }
         }
         uint8_t* o = out + (size_t)(r0 + ra) * orow_bytes + group_ofs(g);
         const T* row = X + (size_t)(r0 + ra) * ld;
         for (int r = ra; r < rb; ++r, row += ld, o += orow_bytes) {
             int q[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = quant1<BITS>(pad[i] ? 0.0f : Elem<DT>::widen(row[s[i]]), m[i]);
-            if constexpr (BITS == 6) store_e3m2(q, r0 + r, g);
-            else pack_store(q, o);
+            for (int i = 0; i < 16; ++i) q[i] = quant1<BITS>(gathered(Elem<DT>::widen(row[s[i]])), m[i]);
+            if constexpr (BITS == 6) store16_e3m2(q, out, M, r0 + r, g);
+            else pack16<BITS>(q, o);
 #pragma unroll
             for (int i = 0; i < 16; ++i)
                 if (ident[i]) qs[(size_t)r * KQ + p0 + i] = (uint8_t)q[i];
@@ -559,14 +501,9 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
             int q[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) q[i] = quant1<BITS>(x[i], m[i]);
-            if constexpr (BITS == 6) store_e3m2(q, r0 + r, g);
-            else pack_store(q, o);
-            v4u w;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                w[i] = (uint32_t)(q[4 * i] & 0xff) | ((uint32_t)(q[4 * i + 1] & 0xff) << 8) |
-                       ((uint32_t)(q[4 * i + 2] & 0xff) << 16) | ((uint32_t)(q[4 * i + 3] & 0xff) << 24);
-            *reinterpret_cast<v4u*>(ql) = w;
+            if constexpr (BITS == 6) store16_e3m2(q, out, M, r0 + r, g);
+            else pack16<BITS>(q, o);
+            pack16<8>(q, ql);
         }
     }
     __syncthreads();
@@ -610,8 +547,8 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
         for (int u = 0; u < U; ++u)
             if (ok[u]) {
                 const int g = NH + gt[u];
-                if constexpr (BITS == 6) store_e3m2(q[u], r0 + rr[u], g);
-                else pack_store(q[u], out + (size_t)(r0 + rr[u]) * orow_bytes + group_ofs(g));
+                if constexpr (BITS == 6) store16_e3m2(q[u], out, M, r0 + rr[u], g);
+                else pack16<BITS>(q[u], out + (size_t)(r0 + rr[u]) * orow_bytes + group_ofs(g));
             }
     }
 }
@@ -684,7 +621,7 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
 
     // bytes of an output row and of one group of 16 slots: 16 (INT8), 8 (INT4 nibbles), 12 (E3M2 codes)
     constexpr int GB = (BITS == 8) ? 16 : (BITS == 4 ? 8 : 12);
-    // INT8 / INT4 rows are dense (E3M2 output has its own addressing, see store_e3m2)
+    // INT8 / INT4 rows are dense (E3M2 output has its own addressing, see store16_e3m2)
     const size_t orow_bytes = (size_t)(Kpad >> 4) * GB;
     auto group_ofs = [&](int g) -> size_t { return (size_t)g * GB; };
 
@@ -853,47 +790,6 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
             if (((nb[p][i >> 2] >> (8 * (i & 3))) & 0xff) == MANY) m[p][i] = multiplier(counts[((tid + p * nthr) << 4) + i]);
     }
 
-    auto pack_store = [&](const int (&q)[16], uint8_t* o) {
-        if (BITS == 8) {
-            v4u w;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                w[i] = (uint32_t)(q[4 * i] & 0xff) | ((uint32_t)(q[4 * i + 1] & 0xff) << 8) |
-                       ((uint32_t)(q[4 * i + 2] & 0xff) << 16) | ((uint32_t)(q[4 * i + 3] & 0xff) << 24);
-            *reinterpret_cast<v4u*>(o) = w;
-        } else if (BITS == 6) {
-            (void)o;                                // E3M2 output goes through store_e3m2
-        } else {
-            v2u w;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                uint32_t acc = 0;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc |= (uint32_t)(q[8 * i + j] & 0xf) << (4 * j);
-                w[i] = acc;
-            }
-            *reinterpret_cast<v2u*>(o) = w;
-        }
-    };
-    // E3M2 output, blocked along k: block t (codes 128 t .. 128 t + 127) holds 96 bytes of every row in turn.
-    // A row's 96 bytes are two 48-byte groups of 64 codes; the 24-byte bit stream of each 32-code unit a is
-    // split into its first 16 bytes X_a and last 8 bytes Y_a, and the group is stored X_a Y_a Y_b X_b with
-    // (a, b) = (0, 1) in rows whose index has bit 4 clear and (1, 0) in the others (what the GEMM's LDS reads
-    // want).  A thread's 16 codes are half a unit: stream bytes 0..11 (e = 0) or 12..23 (e = 1).
-    auto store_e3m2 = [&](const int (&q)[16], int row, int g) {
-        const u3 v = pack16_e3m2(q);
-        const int gi = g & 7, e = gi & 1;
-        uint8_t* grp = out + ((size_t)(g >> 3) * (size_t)M + (size_t)row) * 96 + 48 * (gi >> 2);
-        const bool mirrored = (((gi >> 1) ^ (row >> 4)) & 1) != 0;
-        if (!mirrored) {
-            *reinterpret_cast<u3*>(grp + 12 * e) = v;                 // X at 0, Y at 16: the plain stream
-        } else if (e == 0) {
-            *reinterpret_cast<u3*>(grp + 32) = v;                     // X at 32
-        } else {
-            *reinterpret_cast<uint32_t*>(grp + 44) = v.a;             // the last 4 bytes of X
-            *reinterpret_cast<v2u*>(grp + 24) = v2u{v.b, v.c};        // Y at 24
-        }
-    };
     // one group of one row in its general form: every slot's source element gathered from global memory
     auto gather_group = [&](int g, int row) {
         const T* xr = X + (size_t)row * ld;
@@ -907,8 +803,8 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
             if (in && n[i] > 0) mult = n[i] < DIRECT_TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
             q[i] = quant1<BITS>(x, mult);
         }
-        if constexpr (BITS == 6) store_e3m2(q, row, g);
-        else pack_store(q, out + (size_t)row * orow_bytes + group_ofs(g));
+        if constexpr (BITS == 6) store16_e3m2(q, out, M, row, g);
+        else pack16<BITS>(q, out + (size_t)row * orow_bytes + group_ofs(g));
     };
 
     // head groups of this thread that are not plain
@@ -933,14 +829,9 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
                         int q[16];
 #pragma unroll
                         for (int i = 0; i < 16; ++i) q[i] = quant1<BITS>(x[i], m[p][i]);
-                        if constexpr (BITS == 6) store_e3m2(q, rs + r, g);
-                        else pack_store(q, out + (size_t)(rs + r) * orow_bytes + group_ofs(g));
-                        v4u w;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            w[i] = (uint32_t)(q[4 * i] & 0xff) | ((uint32_t)(q[4 * i + 1] & 0xff) << 8) |
-                                   ((uint32_t)(q[4 * i + 2] & 0xff) << 16) | ((uint32_t)(q[4 * i + 3] & 0xff) << 24);
-                        *reinterpret_cast<v4u*>(qs + (size_t)r * KQ + (g << 4)) = w;
+                        if constexpr (BITS == 6) store16_e3m2(q, out, M, rs + r, g);
+                        else pack16<BITS>(q, out + (size_t)(rs + r) * orow_bytes + group_ofs(g));
+                        pack16<8>(q, qs + (size_t)r * KQ + (g << 4));
                     }
             }
         }
@@ -979,8 +870,8 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
                 const uint32_t j = (i & 1) ? (word >> 16) : (word & 0xffffu);
                 q[i] = (j == 0xffffu) ? 0 : (int)ql[j];
             }
-            if constexpr (BITS == 6) store_e3m2(q, rs + rr, g);
-            else pack_store(q, out + (size_t)(rs + rr) * orow_bytes + group_ofs(g));
+            if constexpr (BITS == 6) store16_e3m2(q, out, M, rs + rr, g);
+            else pack16<BITS>(q, out + (size_t)(rs + rr) * orow_bytes + group_ofs(g));
         }
         strip_barrier();
     }

@@ -101,5 +101,54 @@ template <int BITS> __device__ __forceinline__ int quant1(float x, float m)
     else return (int)r;
 }
 
+// A gathered element, the largest finite value of its sign in place of an infinity (NaN counts as negative): the multiplier of
+// a padding slot is 0, and 0 times what is not finite would be NaN, which clamps to qmin.  What other slots give is unchanged.
+__device__ __forceinline__ float gathered(float x) { return __builtin_amdgcn_fmed3f(x, -3.402823466e38f, 3.402823466e38f); }
+
+// 16 quantized values of a row, packed: 16 bytes of INT8 or 8 bytes of nibbles (even slot in the low nibble)
+template <int BITS> __device__ __forceinline__ void pack16(const int (&q)[16], uint8_t* o)
+{
+    static_assert(BITS == 8 || BITS == 4, "E3M2 codes go through store16_e3m2");
+    if constexpr (BITS == 8) {
+        v4u w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            w[i] = (uint32_t)(q[4 * i] & 0xff) | ((uint32_t)(q[4 * i + 1] & 0xff) << 8) |
+                   ((uint32_t)(q[4 * i + 2] & 0xff) << 16) | ((uint32_t)(q[4 * i + 3] & 0xff) << 24);
+        *reinterpret_cast<v4u*>(o) = w;
+    } else {
+        v2u w;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            uint32_t acc = 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc |= (uint32_t)(q[8 * i + j] & 0xf) << (4 * j);
+            w[i] = acc;
+        }
+        *reinterpret_cast<v2u*>(o) = w;
+    }
+}
+
+// The 16 codes of group g of a row of a matrix of `rows` rows in E3M2 storage, blocked along k: block t (codes 128 t .. 128 t +
+// 127) holds 96 bytes of every row in turn.  A row's 96 bytes are two 48-byte groups of 64 codes; the 24-byte bit stream of each
+// 32-code unit a is split into its first 16 bytes X_a and last 8 bytes Y_a, and the group is stored X_a Y_a Y_b X_b with
+// (a, b) = (0, 1) in rows whose index has bit 4 clear and (1, 0) in the others (what the GEMM's LDS reads want).  16 codes
+// are half a unit: stream bytes 0..11 (e = 0) or 12..23 (e = 1).
+__device__ __forceinline__ void store16_e3m2(const int (&q)[16], uint8_t* out, size_t rows, int row, int g)
+{
+    const u3 v = pack16_e3m2(q);
+    const int gi = g & 7, e = gi & 1;
+    uint8_t* grp = out + ((size_t)(g >> 3) * rows + (size_t)row) * 96 + 48 * (gi >> 2);
+    const bool mirrored = (((gi >> 1) ^ (row >> 4)) & 1) != 0;
+    if (!mirrored) {
+        *reinterpret_cast<u3*>(grp + 12 * e) = v;                     // X at 0, Y at 16: the plain stream
+    } else if (e == 0) {
+        *reinterpret_cast<u3*>(grp + 32) = v;                         // X at 32
+    } else {
+        *reinterpret_cast<uint32_t*>(grp + 44) = v.a;                 // the last 4 bytes of X
+        *reinterpret_cast<v2u*>(grp + 24) = v2u{v.b, v.c};            // Y at 24
+    }
+}
+
 }  // namespace
 }  // namespace fq
