@@ -374,7 +374,8 @@ def main():
             int4_storage[storage_name[st]] = dict(
                 timed_path=(st == timed_store), ms_per_step=round(t_ms, 4), value=round(ops_st / (t_ms * 1e-3) / 1e12, 2),
                 bytes_per_value=0.5 if st == 4 else 0.75, roofline=storage_roofline(st))
-    flatten_roofline = dict(bound="hbm", kernel="colabsmax + scale + flatten_quant", achieved=round(fqa["bytes"] / fqa["ms"] / 1e6, 1),
+    flatten_kernels = ("" if args.static else "tensor_absmax + ") + "scale + flatten_quant_rows (few rows: flatten_quant_direct)"
+    flatten_roofline = dict(bound="hbm", kernel=flatten_kernels, achieved=round(fqa["bytes"] / fqa["ms"] / 1e6, 1),
                             peak=HBM_PEAK_GBS, unit="GB/s", frac=round(fqa["bytes"] / fqa["ms"] / 1e6 / HBM_PEAK_GBS, 4))
 
     # ---------------- ceilings measured on this GPU ----------------

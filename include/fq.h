@@ -152,6 +152,7 @@ size_t fq_weights_workspace_bytes(int K, int Kpad);
  *   s_x = fl32(a' / qmax),  m_p = fl32(qmax / (rep[p] * a'))  (both formed in float64),
  *   Xq_out[i,p] = clamp(rne(X[i,src_idx[p]] * m_p), qmin, qmax); 0 in padding slots;
  *   bits = 4 packs two slots per byte.   a' = 0: Xq_out = 0, s_x = 1.
+ * The map may drop channels (Kpad < K); padding slots hold 0 whatever X holds.
  *
  * X         [M, K] device, x_dtype in {FQ_F32, FQ_F16, FQ_BF16}, row stride ldx >= K elements;
  *           ldx * sizeof(element) must be a multiple of 16.
@@ -322,8 +323,10 @@ int fq_bmm_i4(const uint8_t* Aq, const uint8_t* Bq, int batch, int M, int N, int
  * fq_linear — the end-to-end inference call: fq_flatten_quant_act followed by fq_gemm_i8 /
  * fq_gemm_i4 (fq_gemm_i4_e3m2 for bits = FQ_BITS_I4_E3M2) on one stream.  Wq / s_w come from
  * fq_flatten_weights with the same map and bits.
- * workspace  fq_linear_workspace_bytes(M, K, Kpad, bits) bytes, device, 16-byte aligned; holds
- *            the quantized activation, the per-slot multipliers and s_x.
+ * workspace  fq_linear_workspace_bytes(M, K, Kpad, bits) bytes, device, 16-byte aligned; contents undefined
+ *            after the call (which intermediate results it passes through depends on the sizes).
+ * Y          may take the place of X, the map or the static bound (a row updated in place): they are read before
+ *            Y is written.  It must not share memory with Wq, s_w, bias or the workspace.
  * ------------------------------------------------------------------------------------------- */
 int fq_linear(const void* X, int x_dtype, int M, int K, int ldx,
               const int32_t* src_idx, const int32_t* rep, int Kpad,
@@ -346,8 +349,8 @@ size_t fq_linear_workspace_bytes(int M, int K, int Kpad, int bits);
  * for every output type.  Every 128-column tile of the output converts its rows of X again, inside the MFMA loop:
  * measured 2.4 to 4.8 times slower than fq_linear_bias at every shape tried (narrow outputs included).  It is
  * the measured answer to that future-work item, not a path to prefer.
- * X bf16 only (FQ_ERR_DTYPE otherwise); workspace >= fq_act_workspace_bytes(K, Kpad); other arguments, layouts,
- * ownership and errors as fq_linear_bias.  fq_gemm_select does not apply (one kernel).
+ * X bf16 only (FQ_ERR_DTYPE otherwise); workspace >= fq_act_workspace_bytes(K, Kpad); Y must not share memory with X,
+ * which the GEMM itself reads; other arguments, layouts, ownership and errors as fq_linear_bias.  fq_gemm_select does not apply (one kernel).
  * ------------------------------------------------------------------------------------------- */
 int fq_linear_fused_a_i8(const void* X, int x_dtype, int M, int K, int ldx, const int32_t* src_idx, const int32_t* rep,
                          int Kpad, const void* Wq, const float* s_w, const float* bias, int N, const float* absmax_in,
@@ -379,8 +382,9 @@ int fq_gemm_bf16(const void* X, const void* W, int M, int N, int K, void* Y, int
  *   6:  128x128 tile, 4 waves, direct global->LDS copies (small problems, narrow outputs).
  *   2:  128x128 tile, 64-byte k-stages, 4 waves, operands staged through registers.
  * fq_gemm_i4_e3m2 has a single kernel of this kind: any of these values selects it.
- * With -1, products of at most 4 rows (4-bit values: 16) and outputs that one small tile per CU covers go to kernels of
- * their own (weights streamed into registers; the reduction split over a workgroup's waves; a deep ring of stages).
+ * With -1, products of at most 4 rows (4-bit values: 16), and outputs that one small tile per CU covers with a
+ * reduction long enough to split, go to kernels of their own (weights streamed into registers; the reduction split over
+ * a workgroup's waves; a deep ring of stages), and fq_linear with one row to a single kernel.
  * Every variant computes the same values.  Returns FQ_ERR_RANGE for an unknown variant.
  * ------------------------------------------------------------------------------------------- */
 int fq_gemm_select(int variant);

@@ -11,8 +11,10 @@
 // integers, or fp32 holding integers below 2^24).
 // Us before / now: INT8 12544 x 4096, 64 rows 52.5 / 13.0, 128 rows 52.6 / 16.8, 256 rows 54.6 / 21.7, 384 rows 57.1 / 27.7;
 // 6400 x 15360, 64 rows 44.9 / 24.5; nibbles 12544 x 4096, 64 rows 33.9 / 8.9, 256 rows 33.6 / 18.1; E3M2 42.3 / 10.4 and 40.3 / 17.4.
-// What bounds it then is the traffic from L2 into the CUs, (BM + BN) * Kpad bytes per workgroup: 16-17 TB/s measured with
-// all CUs busy.  So the tile is the smallest for which one round of workgroups covers the output.  Batched products keep a
+// What bounds it then, while the operands are near, is the traffic from L2 into the CUs, (BM + BN) * Kpad bytes per workgroup:
+// 15.6-18.0 TB/s of L2 reads counted with all CUs busy (INT8 12544 x 4096, 64-384 rows; nibbles 12.5).  So the tile is the
+// smallest for which one round of workgroups covers the output.  Weights that come from memory bound it first: INT8 77 x 15360
+// x 5760 reads 211 MB from L2 at 7.2 TB/s, 100 MB of them past it at 3.4.  Batched products keep a
 // problem's tiles on one XCD (place_of_workgroup): dealt over all of them, every L2 read every problem's operands, and 40 x
 // 256 x 128 of 1024 bytes took 11.4 us against 9.0 so and 9.6 by the 128 x 128 tiles; 40 x 128 x 128 7.6 / 6.2 / 9.0.
 #include <atomic>

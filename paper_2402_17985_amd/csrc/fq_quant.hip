@@ -1010,10 +1010,11 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
         const size_t lds = (size_t)R * kq + tail_src;
         const unsigned nblk = (unsigned)((M + R - 1) / R);
         // 256 threads walk the strip's groups while the LDS lets four such workgroups share a CU (16 waves to hide the
-        // loads).  Strips cut to two rows or one whose LDS admits only two or three get 512 threads (us, 256 -> 512):
-        // weight 5120 x 20480 to nibbles 105.0 -> 98.5, activation 8192 x 22016 to INT8 147 -> 133, 8192 x 28672
-        // 195 -> 163.  With four workgroups 512 threads lose: 8192 x 16384 99 -> 102, 8192 x 36000 230 -> 242, weight
-        // 8192 x 28672 255 -> 275; on higher strips they lose or gain little: 8192 x 11008 nibbles 78.5 -> 80.4.
+        // loads).  Strips cut to two rows or one whose LDS admits only two or three get 512 threads.  Whole calls, us, 256 /
+        // 512 threads: weight 5120 x 20480 to nibbles 111.1 / 104.3; activation, static, 8192 x 22016 to INT8 137.2 / 124.4, 8192
+        // x 28672 188.0 / 155.8.  With four workgroups 512 threads lose: 8192 x 16384 91.4 / 95.0, 8192 x 36000 227.6 / 240.5,
+        // weight 8192 x 28672 to INT8 278 / 291.  On higher strips it depends: 8192 x 11008 static 68.4 / 62.7, dynamic 97.0 /
+        // 96.6, 8192 x 8192 static 45.8 / 46.4.
         const int nthr = (R <= 2 && lds > 160u * 1024u / 4) ? 512 : 256;
         if (bits == 8)
             flatten_quant_rows_kernel<DT, 8><<<nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad, R, o8);

@@ -126,7 +126,7 @@ def cmd_traffic(fetch_dir, write_dir, out, out_json, command):
 
 
 def cmd_table(out, files, static_files):
-    L = ["bench.py on the configurations of BASELINE.json (one MI355X; HIP-event timings inside bench.py; dynamic per-tensor",
+    L = ["bench.py on its named configurations (one MI355X; HIP-event timings inside bench.py; dynamic per-tensor",
          "activation scale unless marked static; bf16 output; Kpad padded to 128 channels (256 for packed nibbles)).",
          "4-bit layers as packed nibbles on the int8 MFMA; 'e3m2 us' / 'e3m2 TOPS' = the same layer's GEMM in E3M2 storage on the 6-bit MFMA.",
          "commands (from the repository root):  python3 bench.py --no-cpu --no-peak --configs <cfg> --steps 50 --warmup 30   [--static]",
