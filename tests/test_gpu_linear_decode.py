@@ -149,3 +149,17 @@ def test_what_is_not_finite(value, bits):
             fq.fq_gemm_select(-1)
         out.append(Y)
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("bits,K", [(8, 5000), (4, 70000), (8, 300000)])
+def test_fewer_slots_than_channels(bits, K, static):
+    """A map that drops most channels, the last one among those it reads."""
+    rng = np.random.default_rng(K)
+    Kpad, N = 256, 70
+    X = _x(rng, 1, K, "bf16")
+    W = torch.from_numpy(rng.standard_normal((N, (K + 15) // 16 * 16), dtype=np.float32)).to(DEV).to(torch.bfloat16)[:, :K]
+    src = rng.integers(0, K, Kpad).astype(np.int32)
+    src[:4], src[-3:] = [0, 1, K - 1, K - 1], -1
+    rep = np.where(src >= 0, rng.integers(1, 4, Kpad), 0).astype(np.int32)
+    _compare(X, src, rep, W, bits, scalar(2.0) if static else None, torch.float32, None)
