@@ -98,18 +98,28 @@ struct AbsmaxGrid {
 constexpr int MAX_CANDIDATES = 1024;
 inline long long candidate_capacity(long long K) { return std::max<long long>(MAX_CANDIDATES, (K + 63) / 64 * 64); }
 
-// Strips of 64 rows (16 loads in flight for each of the four waves) while that gives at most 512 workgroups, then higher
-// ones.  Odd multiples of 64: with a power-of-two row stride, strips that start a power-of-two number of rows apart hit
-// the same memory channels (16384 x 8192 bf16: 54 us at 576 rows, 59 us at 512).  At most 1024 candidates, or one strip.
-inline AbsmaxGrid absmax_grid(long long M, long long K, int vec)
+// A workgroup's four waves read 32 rows per round, eight loads in flight each; two to four workgroups per CU (at most 1024
+// candidates), strips of a round at least.  Of the three counts the one whose fullest CU has the fewest rounds, the lowest on a
+// tie.  Strips of a multiple of 64 rows on a pitch of whole 4 KiB count for a tenth more: they start on the same memory
+// channels.  TB/s, bf16: 16384 x 8192 with 768 workgroups (342 rows) 6.4, 512 (512 rows) 6.0, 1024 (256 rows) 5.4; 5120 x
+// 20480 with 760 (270 rows) 6.4, 520 (394) 5.4, 400 (512) 6.2; 8192 x 11008 with 506 (357) 6.25, 770 (235) 5.7, 264 (683) 5.2.
+constexpr int ABSMAX_ROUND = 32;
+inline AbsmaxGrid absmax_grid(long long M, long long K, int vec, long long cus = 256)
 {
     const long long bx = (K + 64 * vec - 1) / (64 * vec);
-    long long rpb = (M * bx + 511) / 512;
-    rpb = std::max(64LL, (rpb + 63) / 64 * 64);
-    if (rpb > 64 && (rpb / 64) % 2 == 0) rpb += 64;
-    while (rpb < M && (M + rpb - 1) / rpb * bx > MAX_CANDIDATES) rpb *= 2;
-    rpb = std::min(rpb, M);
-    return AbsmaxGrid{(int)bx, (int)((M + rpb - 1) / rpb), (int)rpb};
+    const long long most = (M + ABSMAX_ROUND - 1) / ABSMAX_ROUND, pitch = K * (16 / vec);
+    long long rows = M, best = -1;
+    for (int per_cu = 2; per_cu <= 4; ++per_cu) {
+        const long long s = std::max(1LL, std::min(most, std::min<long long>(MAX_CANDIDATES, per_cu * cus) / bx));
+        const long long r = (M + s - 1) / s, wgs = bx * ((M + r - 1) / r);
+        long long cost = 10 * ((wgs + cus - 1) / cus) * ((r + ABSMAX_ROUND - 1) / ABSMAX_ROUND);
+        if (r % 64 == 0 && pitch % 4096 == 0) cost += cost / 10;
+        if (best < 0 || cost < best) {
+            best = cost;
+            rows = r;
+        }
+    }
+    return AbsmaxGrid{(int)bx, (int)((M + rows - 1) / rows), (int)rows};
 }
 
 }  // namespace fq

@@ -1,0 +1,41 @@
+"""The passes that take maxima over an activation (calibration, the dynamic scale): rounds of 32 rows and what is left of
+them, ragged columns, and the streaming form for matrices beyond a cache."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2402_17985_amd as fq
+from tests.gpu_util import DEV, bytes_ws, dev_i32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("dtype,M,K", [
+    (torch.float32, 1, 4), (torch.bfloat16, 3, 520), (torch.float16, 31, 64), (torch.bfloat16, 33, 1000), (torch.float32, 65, 257),
+    (torch.bfloat16, 4099, 4104), (torch.float32, 2061, 4100), (torch.float16, 70000, 24),      # > 32 MiB: the first two stream
+])
+def test_channel_maxima(dtype, M, K, accumulate):
+    g = torch.Generator(device=DEV).manual_seed(M + K)
+    X = torch.randn((M, (K + 7) // 8 * 8), device=DEV, generator=g).to(dtype)[:, :K]
+    for r, c in ((0, 0), (M - 1, K - 1), (M // 2, K // 2)):
+        X[r, c] = -40.0 - c % 7
+    start = torch.rand(K, device=DEV, generator=g) * 6.0
+    out = start.clone()
+    fq.fq_channel_absmax(X, out, accumulate=accumulate)
+    want = X.float().abs().amax(dim=0)
+    assert torch.equal(out, torch.maximum(want, start) if accumulate else want)
+
+
+@pytest.mark.parametrize("M,K", [(33, 2048), (257, 11008), (4100, 1000), (14500, 8200)])       # the last beyond 224 MiB
+@pytest.mark.parametrize("at", ["first", "last"])
+def test_dynamic_scale_finds_the_maximum_wherever_it_lies(M, K, at):
+    Kpad = (K + 127) // 128 * 128
+    src, rep = np.full(Kpad, -1, np.int32), np.zeros(Kpad, np.int32)
+    src[:K], rep[:K] = np.arange(K), 1
+    X = torch.rand((M, K), device=DEV).to(torch.bfloat16)
+    X[(0, 0) if at == "first" else (M - 1, K - 1)] = -9.25
+    out = torch.empty((M, Kpad), dtype=torch.int8, device=DEV)
+    s_x = torch.zeros(1, device=DEV)
+    fq.fq_flatten_quant_act(X, dev_i32(src), dev_i32(rep), 8, out, s_x, bytes_ws(fq.fq_act_workspace_bytes(K, Kpad)))
+    assert np.float32(s_x.item()) == np.float32(9.25 / 127.0)
