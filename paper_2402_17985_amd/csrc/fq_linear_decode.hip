@@ -115,15 +115,18 @@ __global__ __launch_bounds__(NTHR, 4) void linear_decode_kernel(const void* __re
         a = *absmax_in;
         if (!(a >= 0.0f) || a > 3.0e38f) a = 0.0f;             // negative / NaN / Inf static bound: treated as 0
     } else {
-        // a' = max fl32(|x| / n): the largest exact quotient, compared by cross multiplication in float64 (exact for
-        // n < 2^29), divided once per thread; rounding is monotonic
-        float bc = 0.0f;
+        // a' = max fl32(|x| / n): of several copies the largest exact quotient, compared by cross multiplication in float64
+        // (exact for n < 2^29), divided once per thread; rounding is monotonic
+        float best = 0.0f, bc = 0.0f;
         int bn = 1;
         auto consider = [&](const int (&s)[16], const int (&n)[16], const float (&x)[16]) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
+                if ((unsigned)s[i] >= (unsigned)K || n[i] <= 0) continue;
                 const float v = fabsf(x[i]);
-                if ((unsigned)s[i] < (unsigned)K && n[i] > 0 && (double)v * (double)bn > (double)bc * (double)n[i]) {
+                if (n[i] == 1) {
+                    best = fmaxf(best, v);
+                } else if ((double)v * (double)bn > (double)bc * (double)n[i]) {
                     bc = v;
                     bn = n[i];
                 }
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(NTHR, 4) void linear_decode_kernel(const void* __re
             load_x(g, s, load_slots(g, s, n), x);
             consider(s, n, x);
         }
-        float best = (float)((double)bc / (double)bn);
+        best = fmaxf(best, (float)((double)bc / (double)bn));
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
         if (lane == 0) red[wave] = best;
@@ -152,15 +155,13 @@ __global__ __launch_bounds__(NTHR, 4) void linear_decode_kernel(const void* __re
     const float s_x = (a == 0.0f) ? 1.0f : (float)(ad / (double)QMAX);
     const float scale = s_w ? s_x * *s_w : 1.0f;
     auto quantize = [&](int g, const int (&s)[16], const int (&n)[16], const float (&x)[16]) {
-        int q[16];
+        float m[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            float m = 0.0f;
-            if ((unsigned)s[i] < (unsigned)K && n[i] > 0) m = n[i] < TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
-            q[i] = quant1<BITS>(x[i], m);
+            m[i] = 0.0f;
+            if ((unsigned)s[i] < (unsigned)K && n[i] > 0) m[i] = n[i] < TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
         }
-        if constexpr (MODE == MODE_F6) store16_e3m2(q, xq, 1, 0, g);    // a matrix of one row
-        else pack16<BITS>(q, xq + (MODE == MODE_I8 ? 16 : 8) * g);
+        store_group<BITS>(quantize16<BITS>(x, m), xq, 0, 1, 0, g);      // a matrix of one row
     };
     if (tid < G) quantize(tid, s0, n0, x0);
     for (int g = tid + NTHR; g < G; g += NTHR) {

@@ -365,17 +365,18 @@ __global__ __launch_bounds__(256) void flatten_quant_kernel(const void* __restri
                 if constexpr (!PEEL) x[i] = gathered(x[i]);
             }
         }
-        int q[16];
+        if constexpr (PEEL) {
+            float mult[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if constexpr (PEEL) {
+            for (int i = 0; i < 16; ++i) {
                 const float mag = fminf(fmaxf(fabsf(x[i]) - m[i], 0.0f), thr);
-                q[i] = quant1<BITS>(x[i] < 0.0f ? -mag : mag, mq);
-            } else {
-                q[i] = quant1<BITS>(x[i], m[i]);
+                x[i] = x[i] < 0.0f ? -mag : mag;
+                mult[i] = mq;
             }
+            store16<BITS>(quantize16<BITS>(x, mult), o);
+        } else {
+            store16<BITS>(quantize16<BITS>(x, m), o);
         }
-        pack16<BITS>(q, o);
     }
 }
 
@@ -391,6 +392,9 @@ __global__ __launch_bounds__(256) void flatten_quant_kernel(const void* __restri
 // with the same copy count as its channel's identity slot holds the same quantized value, so a group
 // made of such slots and padding (cflag) is copied from LDS; any other group is gathered from global
 // memory and quantized with its own multipliers.
+// (ROW_PAD: a row in LDS is followed by a byte that is 0, the source of padding slots.)
+constexpr int ROW_PAD = 16;
+
 template <int DT, int BITS>
 __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __restrict__ Xv, int M, int K, int ld,
                                                                  const int32_t* __restrict__ src,
@@ -406,20 +410,19 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
     const int KQ = NH << 4;
     const int G = Kpad >> 4;
     const int NT = G - NH;                                     // groups of phase 2
-    uint8_t* qs = lds;                                         // [R][KQ] int8
-    uint16_t* ts = reinterpret_cast<uint16_t*>(lds + (size_t)R * KQ);   // sources of the phase-2 slots
-    uint8_t* tf = lds + (size_t)R * KQ + (size_t)NT * 32;               // copy flags of the phase-2 groups
+    const int pitch = KQ + ROW_PAD;
+    uint8_t* qs = lds;                                         // [R][pitch], a byte per value; byte KQ of a row is 0
+    uint16_t* ts = reinterpret_cast<uint16_t*>(lds + (size_t)R * pitch);   // sources of the phase-2 slots
+    uint8_t* tf = lds + (size_t)R * pitch + (size_t)NT * 32;               // copy flags of the phase-2 groups
     const uint8_t* cflag = gflag + (G + 1);
     const int r0 = blockIdx.x * R;
     const int nthr = blockDim.x;
     const int nr = min(M - r0, R);
-    // bytes of an output row and of one group of 16 slots: 16 (INT8), 8 (INT4 nibbles), 12 (E3M2 codes)
-    constexpr int GB = (BITS == 8) ? 16 : (BITS == 4 ? 8 : 12);
-    // INT8 / INT4 rows are dense (E3M2 output has its own addressing, see store16_e3m2)
-    const size_t orow_bytes = (size_t)(Kpad >> 4) * GB;
-    auto group_ofs = [&](int g) -> size_t { return (size_t)g * GB; };
+    // bytes of an output row: 16 (INT8) or 8 (nibbles) per group of 16 slots (E3M2 has its own addressing, see store16_e3m2)
+    const size_t orow_bytes = (size_t)G * (BITS == 8 ? 16 : 8);
+    if ((int)threadIdx.x < R) qs[(size_t)threadIdx.x * pitch + KQ] = 0;
 
-    // sources of the phase-2 slots as 16-bit channel numbers (0xffff: the slot holds 0); eight slots per
+    // sources of the phase-2 slots as 16-bit channel numbers (KQ: the slot holds 0); eight slots per
     // thread and pass, loaded before any is stored, so that the passes do not each wait a round trip
     for (int t = threadIdx.x * 8; t < NT * 16; t += nthr * 8) {
         const v4i a = *reinterpret_cast<const v4i*>(src + KQ + t);
@@ -428,8 +431,7 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int j0 = (i < 2) ? a[2 * i] : b[2 * i - 4], j1 = (i < 2) ? a[2 * i + 1] : b[2 * i - 3];
-            const uint32_t lo = ((unsigned)j0 < (unsigned)KQ) ? (uint32_t)j0 : 0xffffu;
-            const uint32_t hi = ((unsigned)j1 < (unsigned)KQ) ? (uint32_t)j1 : 0xffffu;
+            const uint32_t lo = min((uint32_t)j0, (uint32_t)KQ), hi = min((uint32_t)j1, (uint32_t)KQ);     // -1 is the largest
             w[i] = lo | (hi << 16);
         }
         *reinterpret_cast<v4u*>(ts + t) = v4u{w[0], w[1], w[2], w[3]};
@@ -455,17 +457,16 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
             ident[i] = to_lds && s[i] == p0 + i;
             if ((unsigned)s[i] >= (unsigned)K) { s[i] = 0; m[i] = 0.0f; }
         }
-        uint8_t* o = out + (size_t)(r0 + ra) * orow_bytes + group_ofs(g);
         const T* row = X + (size_t)(r0 + ra) * ld;
-        for (int r = ra; r < rb; ++r, row += ld, o += orow_bytes) {
-            int q[16];
+        for (int r = ra; r < rb; ++r, row += ld) {
+            float x[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = quant1<BITS>(gathered(Elem<DT>::widen(row[s[i]])), m[i]);
-            if constexpr (BITS == 6) store16_e3m2(q, out, M, r0 + r, g);
-            else pack16<BITS>(q, o);
+            for (int i = 0; i < 16; ++i) x[i] = gathered(Elem<DT>::widen(row[s[i]]));
+            const v4u q = quantize16<BITS>(x, m);
+            store_group<BITS>(q, out, orow_bytes, M, r0 + r, g);
 #pragma unroll
             for (int i = 0; i < 16; ++i)
-                if (ident[i]) qs[(size_t)r * KQ + p0 + i] = (uint8_t)q[i];
+                if (ident[i]) qs[(size_t)r * pitch + p0 + i] = (uint8_t)(q[i >> 2] >> (8 * (i & 3)));
         }
     };
 
@@ -483,21 +484,16 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
 #pragma unroll
             for (int j = 0; j < 4; ++j) m[4 * i + j] = mv[j];
         }
-        uint8_t* o = out + (size_t)r0 * orow_bytes + group_ofs(g);
         const T* row = X + (size_t)r0 * ld + p0;
         uint8_t* ql = qs + p0;
 #pragma unroll 4
-        for (int r = 0; r < nr; ++r, row += ld, o += orow_bytes, ql += KQ) {
+        for (int r = 0; r < nr; ++r, row += ld, ql += pitch) {
             float x[16];
-            const v4u* vp = reinterpret_cast<const v4u*>(row);
 #pragma unroll
-            for (int i = 0; i < 16 / VEC; ++i) widen16<DT>(vp[i], x + i * VEC);
-            int q[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = quant1<BITS>(x[i], m[i]);
-            if constexpr (BITS == 6) store16_e3m2(q, out, M, r0 + r, g);
-            else pack16<BITS>(q, o);
-            pack16<8>(q, ql);
+            for (int i = 0; i < 16 / VEC; ++i) widen16<DT>(*reinterpret_cast<const v4u*>(row + i * VEC), x + i * VEC);
+            const v4u q = quantize16<BITS>(x, m);
+            store_group<BITS>(q, out, orow_bytes, M, r0 + r, g);
+            *reinterpret_cast<v4u*>(ql) = q;
         }
     }
     __syncthreads();
@@ -526,24 +522,12 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
             t0[u] = tp[0];
             t1[u] = tp[1];
         }
-        int q[U][16];
+        v4u q[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int8_t* ql = reinterpret_cast<const int8_t*>(qs) + (size_t)rr[u] * KQ;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const uint32_t word = (i < 8) ? t0[u][i >> 1] : t1[u][(i - 8) >> 1];
-                const uint32_t j = (i & 1) ? (word >> 16) : (word & 0xffffu);
-                q[u][i] = (j == 0xffffu) ? 0 : (int)ql[j];
-            }
-        }
+        for (int u = 0; u < U; ++u) q[u] = gather16(qs + (size_t)rr[u] * pitch, t0[u], t1[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (ok[u]) {
-                const int g = NH + gt[u];
-                if constexpr (BITS == 6) store16_e3m2(q[u], out, M, r0 + rr[u], g);
-                else pack16<BITS>(q[u], out + (size_t)(r0 + rr[u]) * orow_bytes + group_ofs(g));
-            }
+            if (ok[u]) store_group<BITS>(q[u], out, orow_bytes, M, r0 + rr[u], NH + gt[u]);
     }
 }
 
@@ -553,15 +537,23 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
 // The same two phases as the row-strip kernel, but nothing is prepared in kernels of their own: at these sizes a call is
 // bound by its launches (each 4-8 us) and not by bytes.  A workgroup owns a run of rows, which it walks in strips of R,
 // and has one thread per P head groups, so that a strip is one round of loads.
-//   the map    thread t reads the sources and copy counts of its groups t, t + blockDim, ... of the head.  A group is
+//   loads      X of the first strip, the map (head and tail) and the bound or the candidates are asked for at once: what
+//              follows waits one round trip to memory for all of them.
+//   the map    thread t reads the sources and copy counts of its groups t, t + head threads, ... of the head.  A group is
 //              plain when its slots are the channels at the same indices with copies; the counts of plain groups are left
 //              in LDS, and from them follows which appended groups only repeat their values.  (Counts beyond the table are
 //              rare and divide once per slot.  Gathering their groups and copies element by element took 18.0 us for 1000 x
 //              4096 static with one channel of 300 copies and 25.6 with 2000; this 8.7 and 11.8.)
 //   a'         the static bound; or the maximum of the candidates that tensor_absmax_kernel left; or (few rows) taken
-//              from all of X by every workgroup, which costs M * K reads from L2 against a launch.
+//              from all of X by every workgroup, which costs M * K reads from L2 against a launch: its threads then form
+//              several slots of head threads, each with its share of the rows, so that the reads are one round trip.
 //   strips     phase 1 quantizes the plain head groups from registers, phase 2 copies appended slots out of LDS; any
 //              other group is gathered slot by slot.  The next strip is read before phase 2.
+// A kernel that only loads and stores takes 2.0 us here; of the rest about half is loads, half the instructions of a wave that
+// has its SIMD to itself (1.5 ns each).  Whole call before / with one round of loads, unconditional look-ups, divisions on the
+// host and quantize16, us: 77 x 5120 fp16 static 6.3 / 5.1, 1000 x 4096 static 8.2 / 6.7, 16 x 4096 dynamic 8.3 / 7.7, 500 x
+// 11008 dynamic 18.3 / 16.5, 1024 x 11008 22.7 / 20.3.  (The map by four slots per lane, whole lines per instruction, was slower:
+// 1000 x 4096 7.8.)
 template <int DT, int BITS, int P, int R>
 __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* __restrict__ Xv, int M, int K, int ld,
                                                                     const int32_t* __restrict__ src,
@@ -569,32 +561,43 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
                                                                     const float* __restrict__ absmax_in,
                                                                     const float* __restrict__ cand, int ncand,
                                                                     float* __restrict__ scale_out,
-                                                                    float* __restrict__ scalars, uint8_t* __restrict__ out)
+                                                                    float* __restrict__ scalars, uint8_t* __restrict__ out,
+                                                                    int rows_each, int rows_more, int slots)
 {
     typedef typename Elem<DT>::type T;
     constexpr int VEC = Elem<DT>::VEC, NV = 16 / VEC;
     constexpr int QMAX = (BITS == 8) ? 127 : 7;
-    const int nthr = blockDim.x, tid = threadIdx.x;
+    const int nthr = blockDim.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = nthr >> 6;
     extern __shared__ __align__(16) uint8_t lds[];
     const T* X = static_cast<const T*>(Xv);
     const int NH = K >> 4;                                     // groups of the head
     const int KQ = NH << 4;
     const int G = Kpad >> 4;
     const int NT = G - NH;                                     // groups of phase 2
+    const int pitch = KQ + ROW_PAD;
     float* table = reinterpret_cast<float*>(lds);              // [DIRECT_TABLE] m(n) = fl32(qmax / (n a'))
     float* red = table + DIRECT_TABLE;                         // [DIRECT_RED]
-    uint8_t* qs = lds + DIRECT_LDS_FIXED;                      // [R][KQ] int8
-    uint16_t* ts = reinterpret_cast<uint16_t*>(qs + (size_t)R * KQ);    // sources of the phase-2 slots
-    uint8_t* tf = qs + (size_t)R * KQ + (size_t)NT * 32;                // copy flags of the phase-2 groups
-    const int row_begin = (int)((long long)M * blockIdx.x / gridDim.x);
-    const int row_end = (int)((long long)M * (blockIdx.x + 1) / gridDim.x);
+    uint8_t* counts8 = lds + DIRECT_LDS_FIXED;                 // [pitch] copy counts of the plain groups, 0 elsewhere
+    uint8_t* qs = counts8 + pitch;                             // [R][pitch], a byte per value; byte KQ of a row is 0
+    uint16_t* ts = reinterpret_cast<uint16_t*>(qs + (size_t)R * pitch);    // sources of the phase-2 slots
+    uint8_t* tf = qs + (size_t)R * pitch + (size_t)NT * 32;                // copy flags of the phase-2 groups
+    // rows_each rows per workgroup, one more in the first rows_more (from the host: a division here takes 0.3 us)
+    const int wg = blockIdx.x, row_begin = wg * rows_each + min(wg, rows_more), row_end = row_begin + rows_each + (wg < rows_more ? 1 : 0);
+    // the threads of one slot cover the head; slot 0 quantizes it, the others help with a' and with phase 2
+    const int head_waves = (NH + 64 * P - 1) / (64 * P), head = head_waves << 6;
+    int slot = 0;
+    for (int w = wave; w >= head_waves; w -= head_waves) ++slot;
+    const int t0 = tid - slot * head;
+    const bool first = slot == 0;
 
     // the head groups of a strip of X; every row index is below row_end, every group inside the row
     v4u raw[P][R][NV];
     auto load_strip = [&](int rs) {
+        if (!first) return;
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            const int g = tid + p * nthr;
+            const int g = t0 + p * head;
             if (g < NH) {
 #pragma unroll
                 for (int r = 0; r < R; ++r)
@@ -606,18 +609,6 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
             }
         }
     };
-    load_strip(row_begin);
-    // the static bound, or this thread's share of the candidates: on their way while the map is worked out
-    float best = 0.0f;
-    if (absmax_in) best = *absmax_in;
-    else if (cand)
-        for (int c = tid; c < ncand; c += nthr) best = fmaxf(best, cand[c]);
-
-    // bytes of an output row and of one group of 16 slots: 16 (INT8), 8 (INT4 nibbles), 12 (E3M2 codes)
-    constexpr int GB = (BITS == 8) ? 16 : (BITS == 4 ? 8 : 12);
-    // INT8 / INT4 rows are dense (E3M2 output has its own addressing, see store16_e3m2)
-    const size_t orow_bytes = (size_t)(Kpad >> 4) * GB;
-    auto group_ofs = [&](int g) -> size_t { return (size_t)g * GB; };
 
     // copy counts of eight slots (weights: no counts, every slot a plain copy)
     const int32_t* counts = rep ? rep : src;
@@ -635,116 +626,182 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
         load_counts(p0 + 8, nv + 8);
     };
 
+    // ---- the loads ----
+    float best = 0.0f;
+    if (absmax_in) best = *absmax_in;
+    int sv[P][16], nv[P][16];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        if (t0 + p * head < NH) load_slots((t0 + p * head) << 4, sv[p], nv[p]);
+    // eight slots of the tail per thread and pass, the first pass now; the two threads of a group sit in adjacent lanes
+    int tj[8], tn[8];
+    if (tid * 8 < NT * 16) {
+        load8(src + KQ + tid * 8, tj);
+        load_counts(KQ + tid * 8, tn);
+    }
+    load_strip(row_begin);
+    if (cand) {                                                // at most 1024 unless K is beyond 2^18: four per thread and pass
+        for (int c = tid * 4; c < ncand; c += nthr * 16) {
+            v4f v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int at = c + q * nthr * 4;
+                v[q] = at < ncand ? *reinterpret_cast<const v4f*>(cand + at) : v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int i = 1; i < 4; ++i) v[q][i] = at + i < ncand ? v[q][i] : 0.0f;     // beyond the candidates: not written
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) best = fmaxf(fmaxf(best, fmaxf(v[q][0], v[q][1])), fmaxf(v[q][2], v[q][3]));
+        }
+    }
+    if (tid <= R) counts8[(size_t)tid * pitch + KQ] = 0;       // also of the rows of qs, which follow
+    float a = 0.0f;
+    auto multiplier = [&](int n) -> float { return (float)((double)QMAX / ((double)n * (double)a)); };
+    auto fill_table = [&]() {
+        for (int n = tid; n < DIRECT_TABLE; n += nthr) table[n] = (n > 0 && a != 0.0f) ? multiplier(n) : 0.0f;
+    };
+    if (absmax_in) {
+        a = best;
+        if (!(a >= 0.0f) || a > 3.0e38f) a = 0.0f;             // negative / NaN / Inf static bound: treated as 0
+        fill_table();
+    }
+
     // ---- the map ----
     uint32_t nb[P][4];                                         // copy counts of this thread's plain groups, as bytes
     int plain = 0, many = 0;                                   // groups of this thread: plain; with a count of MANY
     bool other = false;                                        // a group that is neither plain nor copies of plain ones
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        const int g = tid + p * nthr;
+        const int g = t0 + p * head;
 #pragma unroll
         for (int i = 0; i < 4; ++i) nb[p][i] = 0;
         if (g < NH) {
-            int sv[16], nv[16];
-            load_slots(g << 4, sv, nv);
-            bool ok = true, big = false;
+            int differ = 0, least = nv[p][0], most = nv[p][0];
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                ok = ok && sv[i] == (g << 4) + i && nv[i] > 0;
-                big = big || nv[i] >= MANY;
+                differ |= sv[p][i] ^ ((g << 4) + i);
+                least = min(least, nv[p][i]);
+                most = max(most, nv[p][i]);
             }
-            if (ok) {
+            if (differ == 0 && least > 0) {
                 plain |= 1 << p;
-                if (big) many |= 1 << p;
+                if (most >= MANY) many |= 1 << p;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) nb[p][i >> 2] |= (uint32_t)min(nv[i], MANY) << (8 * (i & 3));
+                for (int i = 0; i < 16; ++i) nb[p][i >> 2] |= (uint32_t)min(nv[p][i], MANY) << (8 * (i & 3));
+            } else {
+                other = true;
             }
-            *reinterpret_cast<v4u*>(qs + (g << 4)) = v4u{nb[p][0], nb[p][1], nb[p][2], nb[p][3]};
-            other = other || !ok;
+            if (first) *reinterpret_cast<v4u*>(counts8 + (g << 4)) = v4u{nb[p][0], nb[p][1], nb[p][2], nb[p][3]};
         }
     }
-    // a' from all of X (few rows): the plain groups' part, the largest exact quotient |x| / n compared by cross
-    // multiplication in float64 (exact for n < 2^29) and divided once; rounding is monotonic
+    // a' from all of X (few rows): the plain groups' part.  Rounding is monotonic, so the largest element is divided.
     const bool self = !absmax_in && !cand;
+    // Of several copies the largest exact quotient |x| / n, compared by cross multiplication in float64 (exact for n < 2^29)
+    // and divided once; few channels have them, most waves none at a given place of their groups.
     float bc = 0.0f;
     int bn = 1;
     auto consider = [&](float v, int n) {
-        if ((double)v * (double)bn > (double)bc * (double)n) {
+        if (n == 1) {
+            best = fmaxf(best, v);
+        } else if ((double)v * (double)bn > (double)bc * (double)n) {
             bc = v;
             bn = n;
         }
+    };
+    auto reduce_to_red = [&]() {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
+        if (lane == 0) red[wave] = best;
+    };
+    auto max_of_red = [&]() -> float {
+        float v = red[0];
+#pragma unroll
+        for (int w = 1; w < DIRECT_RED; ++w) v = (w < waves) ? fmaxf(v, red[w]) : v;
+        return v;
     };
     if (self) {
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             if (!((plain >> p) & 1)) continue;
+            constexpr int U = 4;                               // rows in flight
             float mx[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) mx[i] = 0.0f;
-            const T* xp = X + ((tid + p * nthr) << 4);
-#pragma unroll 4
-            for (int r = 0; r < M; ++r, xp += ld) {
-                float x[16];
+            const T* xp = X + ((t0 + p * head) << 4);
+            for (int r = slot; r < M; r += U * slots) {
+                v4u in[U][NV];
 #pragma unroll
-                for (int i = 0; i < NV; ++i) widen16<DT>(reinterpret_cast<const v4u*>(xp)[i], x + i * VEC);
+                for (int u = 0; u < U; ++u) {
+                    const T* xr = xp + (size_t)min(r + u * slots, M - 1) * ld;      // beyond the last row: that one again
 #pragma unroll
-                for (int i = 0; i < 16; ++i) mx[i] = fmaxf(mx[i], fabsf(x[i]));
+                    for (int i = 0; i < NV; ++i) in[u][i] = reinterpret_cast<const v4u*>(xr)[i];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float x[16];
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) widen16<DT>(in[u][i], x + i * VEC);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) mx[i] = fmaxf(mx[i], fabsf(x[i]));
+                }
             }
-            int nv[16];
+            int n[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) nv[i] = (nb[p][i >> 2] >> (8 * (i & 3))) & 0xff;
+            for (int i = 0; i < 16; ++i) n[i] = (nb[p][i >> 2] >> (8 * (i & 3))) & 0xff;
             if ((many >> p) & 1) {
-                load_counts((tid + p * nthr) << 4, nv);
-                load_counts(((tid + p * nthr) << 4) + 8, nv + 8);
+                load_counts((t0 + p * head) << 4, n);
+                load_counts(((t0 + p * head) << 4) + 8, n + 8);
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) consider(mx[i], nv[i]);
+            for (int i = 0; i < 16; ++i) consider(mx[i], n[i]);
         }
+        best = fmaxf(best, (float)((double)bc / (double)bn));
     }
+    if (!absmax_in) reduce_to_red();
     __syncthreads();
-    // Sources of the phase-2 slots as 16-bit channel numbers (0xffff: the slot holds 0) and, per group, whether every
-    // slot holds 0 whatever the input or repeats a channel of a plain group with that channel's own copy count.  Eight
-    // slots per thread and pass; the two threads of a group sit in adjacent lanes.
+    if (!absmax_in) {
+        a = max_of_red();
+        fill_table();
+    }
+    // Sources of the phase-2 slots as 16-bit channel numbers (KQ: the slot holds 0) and, per group, whether every
+    // slot holds 0 whatever the input or repeats a channel of a plain group with that channel's own copy count.
     for (int t = tid * 8; t < NT * 16; t += nthr * 8) {
-        int j[8], n[8];
-        load8(src + KQ + t, j);
-        load_counts(KQ + t, n);
+        if (t != tid * 8) {
+            load8(src + KQ + t, tj);
+            load_counts(KQ + t, tn);
+        }
         bool copyable = true, big = false;
         uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const bool in = (unsigned)j[i] < (unsigned)KQ;
-            const int own = in ? qs[j[i]] : 0;
-            if ((unsigned)j[i] < (unsigned)K) copyable = copyable && own != 0 && min(n[i], MANY) == own;
+            const uint32_t j = min((uint32_t)tj[i], (uint32_t)KQ);
+            const int own = counts8[j];
+            copyable = copyable && ((unsigned)tj[i] >= (unsigned)K || (own != 0 && min(tn[i], MANY) == own));
             big = big || own == MANY;
-            w[i >> 1] |= (in ? (uint32_t)j[i] : 0xffffu) << (16 * (i & 1));
+            w[i >> 1] |= j << (16 * (i & 1));
         }
         if (copyable && big) {                                     // counts of MANY or more: compared with the map's
             int c[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) c[i] = counts[(unsigned)j[i] < (unsigned)KQ ? j[i] : 0];
+            for (int i = 0; i < 8; ++i) c[i] = counts[(unsigned)tj[i] < (unsigned)KQ ? tj[i] : 0];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) copyable = copyable && ((unsigned)j[i] >= (unsigned)KQ || n[i] == c[i]);
+            for (int i = 0; i < 8; ++i) copyable = copyable && ((unsigned)tj[i] >= (unsigned)KQ || tn[i] == c[i]);
         }
         *reinterpret_cast<v4u*>(ts + t) = v4u{w[0], w[1], w[2], w[3]};
         const int mine = copyable ? 1 : 0, both = mine & __shfl_xor(mine, 1, 64);
         if ((tid & 1) == 0) tf[t >> 4] = (uint8_t)both;
         other = other || !both;
     }
-    const bool others = __syncthreads_or(other ? 1 : 0) != 0;
-
-    // ---- a' and the table of multipliers ----
-    float a;
-    if (absmax_in) {
-        a = best;
-        if (!(a >= 0.0f) || a > 3.0e38f) a = 0.0f;             // negative / NaN / Inf static bound: treated as 0
-    } else {
-        if (self) {
-            // the slots of every other group (head groups that are not plain, appended groups that do not repeat plain
-            // ones), one by one; plain groups and their copies have been seen above
-            for (int q = tid; others && q < G * 16; q += nthr) {
+    if (self) {
+        // the slots of every other group (head groups that are not plain, appended groups that do not repeat plain
+        // ones), one by one; plain groups and their copies have been seen above
+        if (__syncthreads_or(other ? 1 : 0)) {
+            best = a;
+            bc = 0.0f;
+            bn = 1;
+            for (int q = tid; q < G * 16; q += nthr) {
                 const int g = q >> 4;
-                const bool seen = g < NH ? qs[g << 4] != 0 : tf[g - NH] != 0;
+                const bool seen = g < NH ? counts8[g << 4] != 0 : tf[g - NH] != 0;
                 if (seen) continue;
                 const int j = src[q], n = counted ? rep[q] : 1;
                 if ((unsigned)j >= (unsigned)K || n <= 0) continue;
@@ -753,24 +810,22 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
                 for (int r = 0; r < M; ++r) mx = fmaxf(mx, fabsf(Elem<DT>::widen(X[(size_t)r * ld + j])));
                 consider(mx, n);
             }
-            best = (float)((double)bc / (double)bn);
+            best = fmaxf(best, (float)((double)bc / (double)bn));
+            reduce_to_red();                                   // every thread has read the first maxima before the barrier above
+            __syncthreads();
+            a = max_of_red();
+            fill_table();
+            __syncthreads();
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
-        if ((tid & 63) == 0) red[tid >> 6] = best;
+    } else if (!absmax_in) {
         __syncthreads();
-        a = red[0];
-#pragma unroll
-        for (int w = 1; w < DIRECT_RED; ++w) a = (w < (nthr >> 6)) ? fmaxf(a, red[w]) : a;
     }
-    const double ad = (double)a;
-    auto multiplier = [&](int n) -> float { return (float)((double)QMAX / ((double)n * ad)); };
-    for (int n = tid; n < DIRECT_TABLE; n += nthr) table[n] = (n > 0 && a != 0.0f) ? multiplier(n) : 0.0f;
     if (blockIdx.x == 0 && tid == 0) {
-        *scale_out = (a == 0.0f) ? 1.0f : (float)(ad / (double)QMAX);
+        *scale_out = (a == 0.0f) ? 1.0f : (float)((double)a / (double)QMAX);
         scalars[0] = a;
     }
-    __syncthreads();
+
+    // ---- the multipliers ----
     float m[P][16];
 #pragma unroll
     for (int p = 0; p < P; ++p)
@@ -781,91 +836,72 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
         if (!((many >> p) & 1) || a == 0.0f) continue;
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-            if (((nb[p][i >> 2] >> (8 * (i & 3))) & 0xff) == MANY) m[p][i] = multiplier(counts[((tid + p * nthr) << 4) + i]);
+            if (((nb[p][i >> 2] >> (8 * (i & 3))) & 0xff) == MANY) m[p][i] = multiplier(counts[((t0 + p * head) << 4) + i]);
     }
 
+    // bytes of an output row: 16 (INT8) or 8 (nibbles) per group of 16 slots (E3M2 has its own addressing, see store16_e3m2)
+    const size_t orow_bytes = (size_t)G * (BITS == 8 ? 16 : 8);
     // one group of one row in its general form: every slot's source element gathered from global memory
     auto gather_group = [&](int g, int row) {
         const T* xr = X + (size_t)row * ld;
-        int s[16], n[16], q[16];
+        int s[16], n[16];
+        float x[16], mult[16];
         load_slots(g << 4, s, n);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const bool in = (unsigned)s[i] < (unsigned)K;             // a slot without a channel: 0 whatever X holds
-            const float xs = Elem<DT>::widen(xr[in ? s[i] : 0]), x = in ? xs : 0.0f;
-            float mult = 0.0f;
-            if (in && n[i] > 0) mult = n[i] < DIRECT_TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
-            q[i] = quant1<BITS>(x, mult);
+            const float xs = Elem<DT>::widen(xr[in ? s[i] : 0]);
+            x[i] = in ? xs : 0.0f;
+            mult[i] = 0.0f;
+            if (in && n[i] > 0) mult[i] = n[i] < DIRECT_TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
         }
-        if constexpr (BITS == 6) store16_e3m2(q, out, M, row, g);
-        else pack16<BITS>(q, out + (size_t)row * orow_bytes + group_ofs(g));
+        store_group<BITS>(quantize16<BITS>(x, mult), out, orow_bytes, M, row, g);
     };
 
     // head groups of this thread that are not plain
     int slow = 0;
 #pragma unroll
     for (int p = 0; p < P; ++p)
-        if (tid + p * nthr < NH && !((plain >> p) & 1)) slow |= 1 << p;
+        if (first && t0 + p * head < NH && !((plain >> p) & 1)) slow |= 1 << p;
 
+    const int tail_waves = (NT + 63) >> 6;
     for (int rs = row_begin; rs < row_end; rs += R) {
         const int nr = min(row_end - rs, R);
         // ---- phase 1: the head ----
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            const int g = tid + p * nthr;
-            if ((plain >> p) & 1) {
+            const int g = t0 + p * head;
+            if (first && ((plain >> p) & 1)) {
 #pragma unroll
                 for (int r = 0; r < R; ++r)
                     if (r < nr) {
                         float x[16];
 #pragma unroll
                         for (int i = 0; i < NV; ++i) widen16<DT>(raw[p][r][i], x + i * VEC);
-                        int q[16];
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) q[i] = quant1<BITS>(x[i], m[p][i]);
-                        if constexpr (BITS == 6) store16_e3m2(q, out, M, rs + r, g);
-                        else pack16<BITS>(q, out + (size_t)(rs + r) * orow_bytes + group_ofs(g));
-                        pack16<8>(q, qs + (size_t)r * KQ + (g << 4));
+                        const v4u q = quantize16<BITS>(x, m[p]);
+                        store_group<BITS>(q, out, orow_bytes, M, rs + r, g);
+                        *reinterpret_cast<v4u*>(qs + (size_t)r * pitch + (g << 4)) = q;
                     }
             }
         }
         load_strip(rs + R);
         strip_barrier();
 
-        // ---- phase 2: appended copies and padding, (group, row) items over all threads; before them, this thread's
-        //      own head groups that are not plain ----
-        const int items = NT * nr, own = slow ? P * nr : 0;
-        for (int it = tid, k = 0; k < own || it < items;) {
-            int g, rr, gt = 0;
-            bool copy = false;
-            if (k < own) {
-                const int p = k / nr;
-                rr = k++ - p * nr;
-                if (!((slow >> p) & 1)) continue;
-                g = tid + p * nthr;
-            } else {
-                gt = it % NT;
-                rr = it / NT;
-                it += nthr;
-                g = NH + gt;
-                copy = tf[gt] != 0;
-            }
-            if (!copy) {
-                gather_group(g, rs + rr);
+        // ---- this thread's head groups that are not plain; then phase 2, appended copies and padding: a wave takes 64
+        //      groups of a row ----
+        for (int k = 0; slow && k < P * nr; ++k)
+            if ((slow >> (k / nr)) & 1) gather_group(t0 + (k / nr) * head, rs + k % nr);
+        for (int rr = 0, w = wave;; w += waves) {
+            for (; rr < nr && w >= tail_waves; w -= tail_waves) ++rr;
+            if (rr >= nr) break;
+            const int gt = w * 64 + lane;
+            if (gt >= NT) continue;
+            if (!tf[gt]) {
+                gather_group(NH + gt, rs + rr);
                 continue;
             }
             const v4u* tp = reinterpret_cast<const v4u*>(ts + gt * 16);
-            const v4u t0 = tp[0], t1 = tp[1];
-            const int8_t* ql = reinterpret_cast<const int8_t*>(qs) + (size_t)rr * KQ;
-            int q[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const uint32_t word = (i < 8) ? t0[i >> 1] : t1[(i - 8) >> 1];
-                const uint32_t j = (i & 1) ? (word >> 16) : (word & 0xffffu);
-                q[i] = (j == 0xffffu) ? 0 : (int)ql[j];
-            }
-            if constexpr (BITS == 6) store16_e3m2(q, out, M, rs + rr, g);
-            else pack16<BITS>(q, out + (size_t)(rs + rr) * orow_bytes + group_ofs(g));
+            store_group<BITS>(gather16(qs + (size_t)rr * pitch, tp[0], tp[1]), out, orow_bytes, M, rs + rr, NH + gt);
         }
         strip_barrier();
     }
@@ -907,7 +943,7 @@ int launch_tensor_absmax(const void* X, int M, int K, int ld, const int32_t* src
 }
 
 typedef void (*direct_kernel_t)(const void*, int, int, int, const int32_t*, const int32_t*, int, const float*, const float*, int,
-                                float*, float*, uint8_t*);
+                                float*, float*, uint8_t*, int, int, int);
 
 // Rows per strip of flatten_quant_direct_kernel: what the registers hold in flight (fp32 takes twice as many).
 template <int DT, int P> constexpr int direct_rows() { return DT == FQ_F32 ? (P == 1 ? 2 : 1) : (P == 1 ? 4 : 2); }
@@ -918,6 +954,16 @@ int direct_kernel(direct_kernel_t* kern)
     static std::atomic<unsigned long long> raised{0};
     *kern = flatten_quant_direct_kernel<DT, BITS, P, direct_rows<DT, P>()>;
     return set_lds_limit(reinterpret_cast<const void*>(*kern), 144 * 1024, raised);
+}
+
+typedef void (*rows_kernel_t)(const void*, int, int, int, const int32_t*, const float*, const uint8_t*, int, int, uint8_t*);
+
+template <int DT, int BITS>
+int rows_kernel(rows_kernel_t* kern)
+{
+    static std::atomic<unsigned long long> raised{0};
+    *kern = flatten_quant_rows_kernel<DT, BITS>;
+    return set_lds_limit(reinterpret_cast<const void*>(*kern), 132 * 1024, raised);
 }
 
 // LDS of a strip kernel: K / 16 * 16 bytes per row, and per appended slot 2 bytes (its source), per appended group 1 (its
@@ -951,8 +997,13 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
     // 25.5 / 24.7, 1024 x 20480 36.5 / 32.4, 8192 x 11008 98.9 / 87.0.
     if (out && !peel && narrow && NH <= 2048 && (long long)M * K <= (12ll << 20)) {
         const int R = P == 1 ? direct_rows<DT, 1>() : direct_rows<DT, 2>();
-        const int nthr = (int)round_up((size_t)(NH + P - 1) / P, 64);
-        const size_t lds = DIRECT_LDS_FIXED + (size_t)R * kq + tail_src;
+        // A few rows: every workgroup reads all of X for a' rather than a launch that does (16 x 4096 bf16: 10.2 against
+        // 12.4 us for the call); at most 64 rows, since a slot that repeats no plain group walks them one by one.
+        const bool self = mode == 0 && M <= 64 && (size_t)M * K * sizeof(typename Elem<DT>::type) <= 256u * 1024u;
+        const int head = (int)round_up((size_t)(NH + P - 1) / P, 64);
+        // several slots of head threads up to 256 threads (16 x 256: 7.8 us with one, 6.9 with four; 16 x 4096: 8.3, 9.8)
+        const int slots = self ? std::max(1, std::min(256 / head, (M + 3) / 4)) : 1, nthr = head * slots;
+        const size_t lds = DIRECT_LDS_FIXED + (size_t)(R + 1) * (kq + ROW_PAD) + tail_src;
         // what the CUs hold at once: 1024 threads (128 registers each) and 160 KiB of LDS
         const int occ = std::max(1, std::min((int)(160u * 1024u / lds), 1024 / nthr));
         const int nblk = direct_workgroups(M, R, compute_units(), occ);
@@ -961,22 +1012,20 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
         if (P == 1) rc = bits == 8 ? direct_kernel<DT, 8, 1>(&kern) : bits == 6 ? direct_kernel<DT, 6, 1>(&kern) : direct_kernel<DT, 4, 1>(&kern);
         else rc = bits == 8 ? direct_kernel<DT, 8, 2>(&kern) : bits == 6 ? direct_kernel<DT, 6, 2>(&kern) : direct_kernel<DT, 4, 2>(&kern);
         if (rc) return rc;
-        // A few rows: every workgroup reads all of X for a' rather than a launch that does (16 x 4096 bf16: 10.2 against
-        // 12.4 us for the call); at most 64 rows, since a slot that repeats no plain group walks them one by one.
-        const bool self = mode == 0 && M <= 64 && (size_t)M * K * sizeof(typename Elem<DT>::type) <= 256u * 1024u;
         int ncand = 0;
         if (dynamic && !self)
             if ((rc = launch_tensor_absmax<DT>(X, M, K, ld, src_idx, rep, Kpad, all_channels, cand, &ncand, stream))) return rc;
         kern<<<(unsigned)nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, mode == 2 ? nullptr : rep, Kpad, absmax_in,
-                                                    ncand ? cand : nullptr, ncand, scale_out, ws.scalars, o8);
+                                                    ncand ? cand : nullptr, ncand, scale_out, ws.scalars, o8, M / nblk, M % nblk, slots);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(FQ_ERR_HIP, "flatten-quantize launch failed: %s", hipGetErrorString(e));
         return FQ_OK;
     }
-    if (bits == 6) {
-        // very wide layers launch the row-strip kernel with up to 128 KiB of LDS: raise its limit once per device
-        static std::atomic<unsigned long long> raised{0};
-        if (int rc = set_lds_limit(reinterpret_cast<const void*>(flatten_quant_rows_kernel<DT, 6>), 128 * 1024, raised)) return rc;
+    rows_kernel_t rows = nullptr;
+    if (!peel && narrow) {
+        // the strip's rows in LDS, each with its padding, may come to a little more than 64 KiB (E3M2: 128): raised before anything
+        // of this call is enqueued
+        if (int rc = bits == 8 ? rows_kernel<DT, 8>(&rows) : bits == 6 ? rows_kernel<DT, 6>(&rows) : rows_kernel<DT, 4>(&rows)) return rc;
     }
     int ncand = 0;
     if (dynamic)
@@ -994,35 +1043,26 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
         // (at most 64 KiB, so that two workgroups fit a CU); wider layers use the general kernel below
         int R = 8;
         while (R > 1 && (size_t)R * kq + tail_src > 64u * 1024u) R >>= 1;
-        const size_t lds = (size_t)R * kq + tail_src;
-        const unsigned nblk = (unsigned)((M + R - 1) / R);
         // 256 threads walk the strip's groups while the LDS lets four such workgroups share a CU (16 waves to hide the
         // loads).  Strips cut to two rows or one whose LDS admits only two or three get 512 threads.  Whole calls, us, 256 /
         // 512 threads: weight 5120 x 20480 to nibbles 111.1 / 104.3; activation, static, 8192 x 22016 to INT8 137.2 / 124.4, 8192
         // x 28672 188.0 / 155.8.  With four workgroups 512 threads lose: 8192 x 16384 91.4 / 95.0, 8192 x 36000 227.6 / 240.5,
         // weight 8192 x 28672 to INT8 278 / 291.  On higher strips it depends: 8192 x 11008 static 68.4 / 62.7, dynamic 97.0 /
         // 96.6, 8192 x 8192 static 45.8 / 46.4.
-        const int nthr = (R <= 2 && lds > 160u * 1024u / 4) ? 512 : 256;
-        if (bits == 8)
-            flatten_quant_rows_kernel<DT, 8><<<nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad, R, o8);
-        else if (bits == 6) {
-            // Very wide layers (strips cut to two rows or one): the blocked E3M2 layout then gets runs of only
-            // 192 or 96 bytes per block.  A strip twice as high in a 512-thread workgroup with up to 128 KiB of
-            // LDS (one workgroup per CU) measured 11 % faster at K = 22016; at K = 11008 (four rows -> eight)
-            // the same change was 16 % slower, so it stops there.
-            int R6 = R;
-            size_t lds6 = lds;
-            int nthr6 = 256;
+        int nthr = (R <= 2 && (size_t)R * kq + tail_src > 160u * 1024u / 4) ? 512 : 256;
+        // Very wide layers (strips cut to two rows or one): the blocked E3M2 layout then gets runs of only
+        // 192 or 96 bytes per block.  A strip twice as high in a 512-thread workgroup with up to 128 KiB of
+        // LDS (one workgroup per CU) measured 11 % faster at K = 22016; at K = 11008 (four rows -> eight)
+        // the same change was 16 % slower, so it stops there.
+        if (bits == 6) {
+            nthr = 256;
             if (R <= 2 && (size_t)(2 * R) * kq + tail_src <= 128u * 1024u) {
-                R6 = 2 * R;
-                lds6 = (size_t)R6 * kq + tail_src;
-                nthr6 = 512;
-                // (the kernel's LDS limit was raised above, before anything of this call was enqueued)
+                R *= 2;
+                nthr = 512;
             }
-            flatten_quant_rows_kernel<DT, 6><<<(unsigned)((M + R6 - 1) / R6), nthr6, lds6, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad, R6, o8);
         }
-        else
-            flatten_quant_rows_kernel<DT, 4><<<nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad, R, o8);
+        rows<<<(unsigned)((M + R - 1) / R), nthr, (size_t)R * (kq + ROW_PAD) + tail_src, stream>>>(X, M, K, ld, src_idx, ws.mslot, ws.gflag, Kpad,
+                                                                                                   R, o8);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(FQ_ERR_HIP, "flatten-quantize launch failed: %s", hipGetErrorString(e));
         return FQ_OK;

@@ -1,5 +1,5 @@
-// What the quantizing translation units share: element types, the map loads, the quantizer of one element and the packing of
-// 16 quantized values (GPU code only; everything has internal linkage).
+// What the quantizing translation units share: element types, the map loads, the quantizer of 16 elements and the packing of
+// its values (GPU code only; everything has internal linkage).
 #pragma once
 #include "fq_internal.h"
 
@@ -13,23 +13,22 @@ typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 // 12 bytes at 4-byte alignment (a 3-element vector type would claim 16)
 struct __attribute__((aligned(4))) u3 { uint32_t a, b, c; };
 
-// 6-bit E3M2 code (sign, 3 exponent bits with bias 3, 2 mantissa bits) of an integer-valued float r in
-// [-8, 8]: the fp32 form of |r| already holds the exponent and, in its top mantissa bits, the two
-// mantissa bits (exponent field 127 + e -> 3 + e: subtract 124 << 2 after the shift); 0 -> 0.
-__device__ __forceinline__ int e3m2_code_of_float(float r)
+// Bytes of the result: those of a (selector 4..7) or b (0..3), 0x0c gives 0.
+__device__ __forceinline__ uint32_t bytes_of(uint32_t a, uint32_t b, uint32_t sel) { return __builtin_amdgcn_perm(a, b, sel); }
+
+// Four quantized values in [-8, 7], one per byte, to their 6-bit E3M2 codes (sign, 3 exponent bits with bias 3, 2 mantissa
+// bits): byte tables for the values 0..7 and -8..-1, looked up by the low three bits, chosen by the sign.
+__device__ __forceinline__ uint32_t e3m2_codes(uint32_t q)
 {
-    const uint32_t bits = __float_as_uint(r + 0.0f);                   // -0 -> +0
-    const int mag = max((int)((bits & 0x7fffffffu) >> 21) - (124 << 2), 0);
-    return mag | (int)((bits >> 26) & 0x20u);
+    const uint32_t sel = q & 0x07070707u, neg = (q >> 3) & 0x01010101u, mask = (neg << 8) - neg;
+    const uint32_t pos = bytes_of(0x17161514u, 0x12100c00u, sel), low = bytes_of(0x2c303234u, 0x35363738u, sel);
+    return (low & mask) | (pos & ~mask);
 }
-// 16 codes as a 96-bit little-endian bit stream (code i in bits 6 i .. 6 i + 5)
-__device__ __forceinline__ u3 pack16_e3m2(const int (&c)[16])
+// Four codes, one per byte, as 24 bits (code i in bits 6 i .. 6 i + 5)
+__device__ __forceinline__ uint32_t e3m2_stream(uint32_t c)
 {
-    uint32_t g[4];                                                     // four codes = 24 bits
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        g[i] = (uint32_t)c[4 * i] | ((uint32_t)c[4 * i + 1] << 6) | ((uint32_t)c[4 * i + 2] << 12) | ((uint32_t)c[4 * i + 3] << 18);
-    return u3{g[0] | (g[1] << 24), (g[1] >> 8) | (g[2] << 16), (g[2] >> 16) | (g[3] << 8)};
+    const uint32_t y = (c & 0x003f003fu) | ((c >> 2) & 0x0fc00fc0u);
+    return (y & 0xfffu) | ((y >> 4) & 0xfff000u);
 }
 
 template <int DT> struct Elem;
@@ -88,44 +87,43 @@ __device__ __forceinline__ void load8(const int32_t* p, int* out)
     for (int i = 0; i < 4; ++i) { out[i] = a.v[i]; out[4 + i] = b.v[i]; }
 }
 
-// BITS = 8, 4, or 6 = the 4-bit quantizer with its values stored as 6-bit E3M2 codes (k-blocked layout);
-// for 6 the result is the code itself, which is also what the row strip keeps in LDS
-template <int BITS> __device__ __forceinline__ int quant1(float x, float m)
+// 16 elements times their multipliers, quantized, one per byte: the product rounded to fp32, clamped, rounded half to even.
+// BITS = 8, 4, or 6 = the 4-bit quantizer with its values as 6-bit E3M2 codes.
+// The kernels for many rows spend about as long on these instructions as on memory.  Adding 1.5 * 2^23 rounds to an integer as
+// rintf does and leaves it, in two's complement, in the low bits of the sum, from where a byte permute collects it: 4 to 5
+// instructions per element with the widening, where rintf, clamp, conversion and packing by shifts take 8 or 9.
+template <int BITS> __device__ __forceinline__ v4u quantize16(const float (&x)[16], const float (&m)[16])
 {
     constexpr int QB = (BITS == 6) ? 4 : BITS;
-    constexpr float hi = (float)((1 << (QB - 1)) - 1);
-    constexpr float lo = -(float)(1 << (QB - 1));
-    float r = rintf(x * m);                 // one fp32 multiply, then round-half-even
-    r = fminf(fmaxf(r, lo), hi);
-    if constexpr (BITS == 6) return e3m2_code_of_float(r);
-    else return (int)r;
+    constexpr float hi = (float)((1 << (QB - 1)) - 1), lo = -(float)(1 << (QB - 1)), ROUND = 12582912.0f;
+    uint32_t t[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t[i] = __float_as_uint(__builtin_amdgcn_fmed3f(x[i] * m[i], lo, hi) + ROUND);
+    v4u w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t p = bytes_of(t[4 * i + 1], t[4 * i], 0x0c0c0400u), q = bytes_of(t[4 * i + 3], t[4 * i + 2], 0x0c0c0400u);
+        w[i] = bytes_of(q, p, 0x05040100u);
+        if constexpr (BITS == 6) w[i] = e3m2_codes(w[i]);
+    }
+    return w;
 }
 
 // A gathered element, the largest finite value of its sign in place of an infinity (NaN counts as negative): the multiplier of
 // a padding slot is 0, and 0 times what is not finite would be NaN, which clamps to qmin.  What other slots give is unchanged.
 __device__ __forceinline__ float gathered(float x) { return __builtin_amdgcn_fmed3f(x, -3.402823466e38f, 3.402823466e38f); }
 
-// 16 quantized values of a row, packed: 16 bytes of INT8 or 8 bytes of nibbles (even slot in the low nibble)
-template <int BITS> __device__ __forceinline__ void pack16(const int (&q)[16], uint8_t* o)
+// 16 quantized values of a row (one per byte) stored as INT8 (16 bytes) or nibbles (8 bytes, even slot in the low nibble)
+template <int BITS> __device__ __forceinline__ void store16(const v4u& q, uint8_t* o)
 {
     static_assert(BITS == 8 || BITS == 4, "E3M2 codes go through store16_e3m2");
     if constexpr (BITS == 8) {
-        v4u w;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            w[i] = (uint32_t)(q[4 * i] & 0xff) | ((uint32_t)(q[4 * i + 1] & 0xff) << 8) |
-                   ((uint32_t)(q[4 * i + 2] & 0xff) << 16) | ((uint32_t)(q[4 * i + 3] & 0xff) << 24);
-        *reinterpret_cast<v4u*>(o) = w;
+        *reinterpret_cast<v4u*>(o) = q;
     } else {
-        v2u w;
+        uint32_t y[4];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            uint32_t acc = 0;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc |= (uint32_t)(q[8 * i + j] & 0xf) << (4 * j);
-            w[i] = acc;
-        }
-        *reinterpret_cast<v2u*>(o) = w;
+        for (int i = 0; i < 4; ++i) y[i] = (q[i] & 0x000f000fu) | ((q[i] >> 4) & 0x00f000f0u);     // bytes 0 and 2: two values each
+        *reinterpret_cast<v2u*>(o) = v2u{bytes_of(y[1], y[0], 0x06040200u), bytes_of(y[3], y[2], 0x06040200u)};
     }
 }
 
@@ -134,9 +132,10 @@ template <int BITS> __device__ __forceinline__ void pack16(const int (&q)[16], u
 // 32-code unit a is split into its first 16 bytes X_a and last 8 bytes Y_a, and the group is stored X_a Y_a Y_b X_b with
 // (a, b) = (0, 1) in rows whose index has bit 4 clear and (1, 0) in the others (what the GEMM's LDS reads want).  16 codes
 // are half a unit: stream bytes 0..11 (e = 0) or 12..23 (e = 1).
-__device__ __forceinline__ void store16_e3m2(const int (&q)[16], uint8_t* out, size_t rows, int row, int g)
+__device__ __forceinline__ void store16_e3m2(const v4u& q, uint8_t* out, size_t rows, int row, int g)
 {
-    const u3 v = pack16_e3m2(q);
+    const uint32_t s0 = e3m2_stream(q[0]), s1 = e3m2_stream(q[1]), s2 = e3m2_stream(q[2]), s3 = e3m2_stream(q[3]);
+    const u3 v = {s0 | (s1 << 24), (s1 >> 8) | (s2 << 16), (s2 >> 16) | (s3 << 8)};
     const int gi = g & 7, e = gi & 1;
     uint8_t* grp = out + ((size_t)(g >> 3) * rows + (size_t)row) * 96 + 48 * (gi >> 2);
     const bool mirrored = (((gi >> 1) ^ (row >> 4)) & 1) != 0;
@@ -148,6 +147,26 @@ __device__ __forceinline__ void store16_e3m2(const int (&q)[16], uint8_t* out, s
         *reinterpret_cast<uint32_t*>(grp + 44) = v.a;                 // the last 4 bytes of X
         *reinterpret_cast<v2u*>(grp + 24) = v2u{v.b, v.c};            // Y at 24
     }
+}
+
+// 16 quantized values of group g of a row in the storage of BITS; dense rows start at out + row * orow_bytes.
+template <int BITS>
+__device__ __forceinline__ void store_group(const v4u& q, uint8_t* out, size_t orow_bytes, size_t rows, int row, int g)
+{
+    if constexpr (BITS == 6) store16_e3m2(q, out, rows, row, g);
+    else store16<BITS>(q, out + (size_t)row * orow_bytes + (size_t)g * (BITS == 8 ? 16 : 8));
+}
+
+// 16 bytes gathered from a row in LDS by 16-bit indexes
+__device__ __forceinline__ v4u gather16(const uint8_t* row, const v4u& t0, const v4u& t1)
+{
+    v4u q;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t a = i < 2 ? t0[2 * i] : t1[2 * i - 4], b = i < 2 ? t0[2 * i + 1] : t1[2 * i - 3];
+        q[i] = (uint32_t)row[a & 0xffffu] | ((uint32_t)row[a >> 16] << 8) | ((uint32_t)row[b & 0xffffu] << 16) | ((uint32_t)row[b >> 16] << 24);
+    }
+    return q;
 }
 
 }  // namespace
