@@ -15,6 +15,7 @@ SOURCES = [("fq_gemm.hip", ["-DFQ_GEMM_MODE=1"], "fq_gemm_i4.o"),
            ("fq_api.hip", [], "fq_api.o"), ("fq_quant.hip", [], "fq_quant.o"),
            ("fq_gemm_skinny.hip", [], "fq_gemm_skinny.o"), ("fq_gemm_stream.hip", [], "fq_gemm_stream.o"),
            ("fq_gemm_ring.hip", [], "fq_gemm_ring.o"), ("fq_linear_decode.hip", [], "fq_linear_decode.o"),
+           ("fq_linear_few.hip", [], "fq_linear_few.o"),
            ("fq_gemm_select.hip", [], "fq_gemm_select.o"), ("fq_peak.hip", [], "fq_peak.o")]
 # -packed-fp32-ops off: keeps the compiler from forming packed fp32 instructions
 # -ffp-contract=off: every fp32 multiply stays a single correctly rounded operation

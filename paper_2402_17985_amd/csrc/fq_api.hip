@@ -526,13 +526,18 @@ int fq_linear_bias(const void* X, int x_dtype, int M, int K, int ldx, const int3
     rc = check_bias(bias, y_dtype);
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // The one-row kernel quantizes in every workgroup: Y must not share memory with what that reads, since another workgroup
-    // may have stored its columns by then (the separate kernels have read all of it before Y is written).
-    const size_t y_bytes = (size_t)N * elem_size(y_dtype), map_bytes = (size_t)Kpad * sizeof(int32_t);
-    const bool y_apart = !overlap(Y, y_bytes, X, (size_t)K * elem_size(x_dtype)) && !overlap(Y, y_bytes, src_idx, map_bytes) &&
-                         !overlap(Y, y_bytes, rep, map_bytes) && !(absmax_in && overlap(Y, y_bytes, absmax_in, sizeof(float)));
-    if (forced_gemm_variant() < 0 && linear_decode_fits(M, N, K, Kpad, bits) && y_apart)
-        return launch_linear_decode(X, x_dtype, K, src_idx, rep, Kpad, bits, absmax_in, Wq, N, s_w, bias, Y, y_dtype, ldy, st);
+    // The kernels of the whole layer quantize in every workgroup: Y must not share memory with what that reads, since another
+    // workgroup may have stored its columns by then (the separate kernels have read all of it before Y is written).
+    if (M <= 16 && forced_gemm_variant() < 0) {
+        const size_t y_bytes = ((size_t)(M - 1) * ldy + N) * elem_size(y_dtype), map_bytes = (size_t)Kpad * sizeof(int32_t);
+        const size_t x_bytes = ((size_t)(M - 1) * ldx + K) * elem_size(x_dtype);
+        const bool y_apart = !overlap(Y, y_bytes, X, x_bytes) && !overlap(Y, y_bytes, src_idx, map_bytes) &&
+                             !overlap(Y, y_bytes, rep, map_bytes) && !(absmax_in && overlap(Y, y_bytes, absmax_in, sizeof(float)));
+        if (y_apart && linear_few_fits(M, N, K, Kpad, bits, x_dtype))
+            return launch_linear_few(X, x_dtype, M, K, ldx, src_idx, rep, Kpad, bits, absmax_in, Wq, N, s_w, bias, Y, y_dtype, ldy, st);
+        if (y_apart && linear_decode_fits(M, N, K, Kpad, bits))
+            return launch_linear_decode(X, x_dtype, K, src_idx, rep, Kpad, bits, absmax_in, Wq, N, s_w, bias, Y, y_dtype, ldy, st);
+    }
     rc = launch_flatten_quant(X, x_dtype, M, K, ldx, src_idx, rep, Kpad, bits, absmax_in ? 1 : 0, absmax_in, Xq,
                               s_x, ws, st);
     if (rc) return rc;

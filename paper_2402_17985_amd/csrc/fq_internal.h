@@ -103,6 +103,12 @@ int launch_linear_decode(const void* X, int x_dtype, int K, const int32_t* src, 
                          const float* absmax_in, const void* W, int N, const float* s_w, const float* bias, void* Y, int y_dtype,
                          int ldy, hipStream_t stream);
 
+// ... and for a few rows
+bool linear_few_fits(int M, int N, int K, int Kpad, int bits, int x_dtype);
+int launch_linear_few(const void* X, int x_dtype, int M, int K, int ld, const int32_t* src, const int32_t* rep, int Kpad, int bits,
+                      const float* absmax_in, const void* W, int N, const float* s_w, const float* bias, void* Y, int y_dtype,
+                      int ldy, hipStream_t stream);
+
 // `batch` independent products; operand strides in bytes, stride_y_bytes in bytes
 int launch_bmm_int(const void* Aq, const void* Bq, int batch, int M, int N, int Kpad, int bits, size_t stride_a,
                    size_t stride_b, const float* s_a, const float* s_b, void* Y, int y_dtype, int ldy,

@@ -8,10 +8,8 @@
 // workgroups (two per CU) forms the absmax (dynamic scale), the multipliers and the quantized row itself, into LDS,
 // while the first weights are on their way; then it walks the 16-column tiles w, w + gridDim, ... as gemm_skinny_kernel
 // does, with the X operand out of LDS.
-// Us, this kernel / the two: INT8 5120 x 5120 static 12.3 / 15.4, dynamic 13.3 / 18.4, 20480 x 5120 39.3 / 43.5, 8192 x 24576
-// 44.3 / 45.3; nibbles 4096 x 11008 dynamic 12.8 / 16.3; E3M2 4096 x 4096 10.9 / 13.5; 512 x 512 11.2 / 13.3.
-// From two rows on the separate kernels are faster (INT8 dynamic 5120 x 5120, 4 rows: 26.8 us so, 19.9 by them): every
-// workgroup repeats the work of all rows.
+// Us, this kernel / the two: INT8 20480 x 5120 39.3 / 43.5; E3M2 4096 x 4096 10.9 / 13.5; 512 x 512 11.2 / 13.3.  It serves the narrow
+// and the very wide layers; those between, and all of two to sixteen rows, go to linear_few_kernel (few_plan says which, and why).
 #include <algorithm>
 #include <atomic>
 

@@ -92,13 +92,18 @@ __device__ __forceinline__ void load8(const int32_t* p, int* out)
 // The kernels for many rows spend about as long on these instructions as on memory.  Adding 1.5 * 2^23 rounds to an integer as
 // rintf does and leaves it, in two's complement, in the low bits of the sum, from where a byte permute collects it: 4 to 5
 // instructions per element with the widening, where rintf, clamp, conversion and packing by shifts take 8 or 9.
-template <int BITS> __device__ __forceinline__ v4u quantize16(const float (&x)[16], const float (&m)[16])
+// (quantized_bits: one element, its value in two's complement in the low bits)
+template <int BITS> __device__ __forceinline__ uint32_t quantized_bits(float x, float m)
 {
     constexpr int QB = (BITS == 6) ? 4 : BITS;
     constexpr float hi = (float)((1 << (QB - 1)) - 1), lo = -(float)(1 << (QB - 1)), ROUND = 12582912.0f;
+    return __float_as_uint(__builtin_amdgcn_fmed3f(x * m, lo, hi) + ROUND);
+}
+template <int BITS> __device__ __forceinline__ v4u quantize16(const float (&x)[16], const float (&m)[16])
+{
     uint32_t t[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) t[i] = __float_as_uint(__builtin_amdgcn_fmed3f(x[i] * m[i], lo, hi) + ROUND);
+    for (int i = 0; i < 16; ++i) t[i] = quantized_bits<BITS>(x[i], m[i]);
     v4u w;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {

@@ -87,6 +87,63 @@ inline int direct_workgroups(int M, int R, int cus, int resident)
     return (int)std::min<long long>(std::max((M + (long long)R - 1) / R, (long long)std::min(M, cus)), (long long)cus * resident);
 }
 
+// ---- the kernel of the whole layer for a few rows (fq_linear_few.hip) ----
+constexpr int FEW_WAVES = 16, FEW_PREP_WAVES = 8;             // four waves per SIMD: 128 registers each
+constexpr int FEW_ROWS = 16, FEW_LDS = 160 * 1024;            // rows of an MFMA; LDS of a CU
+constexpr int FEW_TABLE = 256, FEW_LDS_FIXED = (FEW_TABLE + FEW_WAVES + 4) * 4;   // multipliers m(n), wave maxima, a count
+constexpr int FEW_PAD = 16;                                   // after a row in LDS
+constexpr uint32_t few_row(uint32_t rowbytes) { return (rowbytes + 127) / 128 * 128 + FEW_PAD; }   // rows on different banks
+constexpr int few_rows_held(int x_bytes) { return x_bytes == 4 ? 4 : 8; }         // per thread: 64 registers
+
+struct FewShape {
+    int M, K, ld, Kpad, N;
+    int prep_waves, slots;     // waves that quantize; rows dealt over so many sets of them
+    int cols;                  // columns of a workgroup and round
+};
+struct FewPlan {
+    FewShape sh;
+    int fn, threads;           // fragments of 16 columns
+    unsigned grid;
+    size_t lds;
+};
+
+// false: the layer is not for this kernel.  It takes up to 16 rows of up to 512 whole groups of 16 channels whose quantized form
+// fits LDS, where a thread's registers hold its rows (2-byte types: 16 rows up to K = 4096, 8 up to 8192).
+//   - E3M2 up to M K = 16384: its values are packed for LDS row by row.  Us, separate / this: 4 x 4096 x 4096 11.5 / 10.0, 8 x
+//     2048 x 4096 10.6 / 9.6, but 8 x 4096 x 256 10.8 / 11.2, 16 x 4096 x 4096 12.6 / 15.5, 8 x 5120 x 4096 13.5 / 16.1.
+//   - One row, where the other choice is linear_decode_kernel: its preparation is shorter, with several workgroups per CU from more
+//     than 16 columns per CU on it repeats it.  INT8 2048 x 256 6.3 / 7.1, 2048 x 4096 7.3 / 7.4, 4096 x 256 9.4 / 8.2, 2048 x 11008 10.9 /
+//     8.4; nibbles 2048 x 4096 6.7 / 7.3, 4096 x 1024 9.2 / 8.7, 2048 x 11008 9.1 / 7.4; E3M2 4096 x 1024 9.1 / 9.2, 8192 x 1024 10.2 / 8.1.
+//     With a ragged last group (K no multiple of 16, which is gathered) 257 x 11008 8.2 / 8.5, 2005 x 11008 10.0 / 8.6, nibbles 4100 x
+//     256 8.9 / 10.0, 4100 x 11008 13.6 / 12.5; E3M2 2005 x 11008 7.9 / 8.7.
+inline bool few_plan(int M, int N, int K, int ld, int Kpad, int bits, int x_bytes, int cus, FewPlan* plan)
+{
+    const int NH = K >> 4;
+    const bool e3m2 = bits != 8 && bits != 4;
+    if (M < 1 || M > FEW_ROWS || NH < 1 || NH > 64 * FEW_PREP_WAVES || Kpad < NH * 16 || Kpad >= 65536) return false;
+    if (e3m2 && (long long)M * K > 16384) return false;
+    if (M == 1) {
+        const bool wide = N > 16 * cus;
+        if (K % 16 != 0 ? !wide || K < 2000 || e3m2 : !wide && K < (e3m2 ? 8192 : 4096)) return false;
+    }
+    const int head = (NH + 63) / 64 * 64, slots = std::max(1, std::min(64 * FEW_PREP_WAVES / head, M));
+    if ((M + slots - 1) / slots > few_rows_held(x_bytes)) return false;
+    // as few rounds as 64 columns per workgroup allow, all of the same width
+    const long long rounds = ((long long)N + 64LL * cus - 1) / (64LL * cus), share = (N + cus * rounds - 1) / (cus * rounds);
+    const int cols = (int)std::max(16LL, (share + 3) / 4 * 4);
+    const int rowbytes = bits == 8 ? Kpad : bits == 4 ? Kpad / 2 : Kpad / 4 * 3, steps = e3m2 ? Kpad / 128 : (rowbytes + 127) / 128;
+    const int prep = head * slots / 64, stream = std::min(FEW_WAVES - prep, std::max(steps, 4));
+    plan->fn = (cols + 15) / 16;
+    const size_t kq = (size_t)NH * 16, nt = (size_t)Kpad / 16 - NH, rows = (size_t)M;
+    plan->lds = FEW_LDS_FIXED + kq + FEW_PAD + rows * (e3m2 ? (size_t)rowbytes : few_row(rowbytes)) + (bits == 8 ? 0 : rows * (kq + FEW_PAD)) +
+                32 * nt + (nt + 15) / 16 * 16 + 2 * (((size_t)Kpad / 16 + 7) / 8 * 8) + (size_t)stream * plan->fn * 1024;
+    if (plan->lds > FEW_LDS) return false;
+    plan->sh = FewShape{M, K, ld, Kpad, N, prep, slots, cols};
+    plan->threads = (prep + stream) * 64;
+    plan->grid = (unsigned)std::min<long long>(((long long)N + cols - 1) / cols, cus);
+    return true;
+}
+
 // Grid of the absmax pass: `blocks` workgroups side by side cover the columns (64 * vec of them each), `strips` of
 // rows_per_strip rows each cover the rows.  Every workgroup leaves one candidate.
 struct AbsmaxGrid {

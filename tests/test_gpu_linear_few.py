@@ -1,0 +1,111 @@
+"""The one-kernel form of the layer for a few rows against the separate kernels (a forced GEMM variant selects them; the
+other tests hold them to the oracle), bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2402_17985_amd as fq
+from tests.gpu_util import DEV, scalar
+from tests.test_gpu_linear_decode import _compare, _x
+
+pytestmark = pytest.mark.gpu
+
+
+def _w(rng, N, K):
+    return torch.from_numpy(rng.standard_normal((N, (K + 15) // 16 * 16), dtype=np.float32)).to(DEV).to(torch.bfloat16)[:, :K]
+
+
+# One group, a ragged one, one and several sets of quantizing waves, a thread's last row (and one more), the widest head; columns
+# of one to four fragments with ragged ends, and several rounds of all workgroups.
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("scale", ["static", "dynamic", "zero"])
+@pytest.mark.parametrize("dtype,M,K,N", [("bf16", 2, 16, 16), ("f32", 16, 31, 33), ("f16", 16, 256, 70), ("bf16", 15, 1000, 4097), ("f32", 3, 1040, 5119),
+                                         ("f16", 16, 1024, 8200), ("bf16", 1, 4096, 40), ("bf16", 1, 5120, 5121), ("f32", 4, 4100, 300),
+                                         ("bf16", 8, 4368, 12290), ("f16", 9, 4368, 100), ("bf16", 2, 8207, 16387), ("bf16", 5, 2064, 33000)])
+def test_planned_maps(dtype, M, K, N, scale, bits):
+    rng = np.random.default_rng(K + M)
+    X, W, T = _x(rng, M, K, dtype), _w(rng, N, K), 4.0
+    src, rep, _, _ = fq.fq_flatten_plan(X.float().abs().amax(dim=0).cpu().numpy(), T, 128 if bits == 6 else 32)
+    if scale == "zero":
+        X.zero_()
+    static = scalar(T) if scale == "static" else None
+    _compare(X, src, rep, W, bits, static, torch.bfloat16, None)
+    _compare(X, src, rep, W, bits, static, torch.float32, torch.from_numpy(rng.standard_normal(N, dtype=np.float32)).to(DEV), pad=3)
+    _compare(X, src, rep, W, bits, static, torch.int32, None)
+
+
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("copies", [254, 255, 256, 700])
+def test_many_copies(copies, static, bits):
+    """Channels of about as many copies as the table of multipliers and the byte counts hold."""
+    rng = np.random.default_rng(copies)
+    M, K, N = 7, 400, 100
+    X, W = _x(rng, M, K, "bf16"), _w(rng, N, K)
+    chmax = np.ones(K, dtype=np.float32)
+    chmax[[3, 200, 399]] = [copies, copies, 2]
+    X[:, 3] *= copies
+    src, rep, _, _ = fq.fq_flatten_plan(chmax, 1.0, 128)
+    assert rep[3] == copies
+    _compare(X, src, rep, W, bits, scalar(3.0) if static else None, torch.float32, None)
+
+
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("Kpad", [512, 1152, 8320])
+def test_maps_that_are_not_the_planners(Kpad, static, bits):
+    rng = np.random.default_rng(Kpad)
+    M, K, N = 6, 500, 100
+    X, W = _x(rng, M, K, "f32"), _w(rng, N, K)
+    src = np.full(Kpad, -1, dtype=np.int32)
+    rep = np.zeros(Kpad, dtype=np.int32)
+    src[:K] = np.arange(K)
+    rep[:K] = rng.integers(1, 4, K)
+    src[16:32] = src[16:32][::-1]
+    src[50], rep[70], rep[100], rep[101] = -1, 0, 256, 100000
+    if Kpad > K + 30:
+        tail = np.arange(K + 3, Kpad - 20)
+        src[tail] = rng.integers(0, K, tail.size)
+        rep[tail] = np.where(rng.random(tail.size) < 0.5, rep[src[tail]], rng.integers(-1, 5, tail.size))
+        src[tail[7]], src[tail[400]] = K + 5, 100
+        rep[tail[400]] = 256
+    _compare(X, src, rep, W, bits, scalar(3.0) if static else None, torch.float16, None)
+
+
+@pytest.mark.parametrize("static", [False, True])
+def test_fewer_slots_than_channels(static):
+    rng = np.random.default_rng(2)
+    M, K, N, Kpad = 4, 1000, 70, 256
+    X, W = _x(rng, M, K, "bf16"), _w(rng, N, K)
+    src = rng.integers(0, K, Kpad).astype(np.int32)
+    rep = rng.integers(1, 4, Kpad).astype(np.int32)
+    _compare(X, src, rep, W, 8, scalar(2.0) if static else None, torch.float32, None)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_what_is_not_finite(value, static, bits, dtype):
+    rng = np.random.default_rng(3)
+    M, K, N = 5, 500, 100
+    X, W = _x(rng, M, K, dtype), _w(rng, N, K)
+    src, rep, _, _ = fq.fq_flatten_plan(X.float().abs().amax(dim=0).cpu().numpy(), 4.0, 32)
+    X[2, 7] = value
+    _compare(X, src, rep, W, bits, scalar(3.0) if static else None, torch.int32, None)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("where", ["X", "second row of X", "map"])
+def test_output_in_the_memory_of_an_input(where, bits):
+    """Y may take the place of what only the quantizer reads: the result is that of a Y apart."""
+    rng = np.random.default_rng(bits)
+    M, K = 4, 2048
+    N = {"X": K, "second row of X": K, "map": 1024}[where]
+    room = torch.cat([_x(rng, M, K, "bf16").contiguous().view(-1), torch.zeros(M * K, dtype=torch.bfloat16, device=DEV)])
+    X = room[:M * K].view(M, K)
+    layer = fq.FqLinear(_w(rng, N, K), X.float().abs().amax(dim=0).cpu().numpy(), 4.0, bits, device=DEV)
+    want = layer.forward(X)
+    Y = {"X": X, "second row of X": room[K:K + M * N].view(M, N) if N == K else None, "map": layer.src.view(torch.bfloat16)[:M * N].view(M, N) if N < K else None}[where]
+    layer.forward(X, Y)
+    assert torch.equal(Y.view(torch.int16), want.view(torch.int16))

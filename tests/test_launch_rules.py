@@ -24,6 +24,13 @@ extern "C" void few_tiles(long long M, long long N, int rowbytes, int bits, long
     out[0] = (int)c.kernel; out[1] = c.bm; out[2] = c.bn;
 }
 extern "C" int direct(int M, int R, int cus, int resident) { return fq::direct_workgroups(M, R, cus, resident); }
+extern "C" int few(int M, int N, int K, int Kpad, int bits, int x_bytes, int cus, long long* out)
+{
+    fq::FewPlan p;
+    if (!fq::few_plan(M, N, K, K, Kpad, bits, x_bytes, cus, &p)) return 0;
+    out[0] = p.sh.prep_waves; out[1] = p.sh.slots; out[2] = p.sh.cols; out[3] = p.fn; out[4] = p.threads; out[5] = p.grid; out[6] = p.lds;
+    return 1;
+}
 extern "C" int overlap(unsigned long long a, unsigned long long na, unsigned long long b, unsigned long long nb)
 {
     return fq::overlap((const void*)a, na, (const void*)b, nb);
@@ -136,3 +143,29 @@ def test_lines_follow_the_number_of_compute_units(rules):
         assert [rules.direct(M, 4, cus, 2) for M in (1, cus, 2 * cus, 4 * cus, 6 * cus, 8 * cus, 100 * cus)] == \
             [1, cus, cus, cus, (6 * cus + 3) // 4, 2 * cus, 2 * cus]
     assert rules.direct(2**31 - 1, 1, 256, 16) == 4096
+
+
+# The kernel of the whole layer for a few rows: threads cover the head and registers the rows, LDS holds them, and the columns of
+# all rounds cover the output.
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("x_bytes", [2, 4])
+@pytest.mark.parametrize("cus", [1, 80, 256])
+def test_few_rows_plan(rules, bits, x_bytes, cus):
+    out = (ctypes.c_longlong * 7)()
+    taken = 0
+    for M in (1, 2, 3, 8, 9, 16, 17):
+        for K in (1, 15, 16, 31, 1000, 1024, 1040, 4096, 4100, 5120, 8192, 8207, 8208, 30000):
+            for Kpad in (K // 256 * 256, (K + 255) // 256 * 256, (K + 1000) // 128 * 128, 65408, 65536):
+                for N in (1, 16, 17, 256, 4096, 4097, 5120, 11008, 16384, 16385, 100000, 2**31 - 1):
+                    if Kpad <= 0 or not rules.few(M, N, K, Kpad, bits, x_bytes, cus, out):
+                        continue
+                    taken += 1
+                    prep, slots, cols, fn, threads, grid, lds = out
+                    assert M <= 16 and Kpad >= K // 16 * 16 and Kpad < 65536
+                    assert 0 < prep <= 8 and prep < threads // 64 <= 16 and threads % 64 == 0
+                    assert prep % slots == 0 and K // 16 <= prep // slots * 64
+                    assert -(-M // slots) <= (8 if x_bytes == 2 else 4) and slots <= M
+                    assert cols % 4 == 0 and 16 <= cols <= 64 and 16 * (fn - 1) < cols <= 16 * fn
+                    assert 0 < grid <= cus and (grid == cus or (grid - 1) * cols < N <= grid * cols)
+                    assert lds <= 160 * 1024
+    assert taken > 0
