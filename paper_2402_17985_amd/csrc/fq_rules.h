@@ -156,10 +156,11 @@ constexpr int MAX_CANDIDATES = 1024;
 inline long long candidate_capacity(long long K) { return std::max<long long>(MAX_CANDIDATES, (K + 63) / 64 * 64); }
 
 // A workgroup's four waves read 32 rows per round, eight loads in flight each; two to four workgroups per CU (at most 1024
-// candidates), strips of a round at least.  Of the three counts the one whose fullest CU has the fewest rounds, the lowest on a
-// tie.  Strips of a multiple of 64 rows on a pitch of whole 4 KiB count for a tenth more: they start on the same memory
-// channels.  TB/s, bf16: 16384 x 8192 with 768 workgroups (342 rows) 6.4, 512 (512 rows) 6.0, 1024 (256 rows) 5.4; 5120 x
-// 20480 with 760 (270 rows) 6.4, 520 (394) 5.4, 400 (512) 6.2; 8192 x 11008 with 506 (357) 6.25, 770 (235) 5.7, 264 (683) 5.2.
+// candidates), strips of whole rounds.  Of the three counts, and one round more, the one whose fullest CU has the fewest rounds, the
+// lowest on a tie.  Strips of an even number of rounds on a pitch of whole 4 KiB count for a quarter more: they start on the same
+// memory channels.  Whole quantizer call, fp32, us: 8192 x 4096 with strips of 128 rows 63.4, 256 63.6, 288 58.1, 342 59.1; 4096 x
+// 8192 256 rows 63.0, 288 60.5; bf16 8192 x 4096 256 rows 37.8, 288 34.9.  One workgroup per CU loses elsewhere: fp32 3000 x 5001
+// 42.4, with two 35.7; weights 5120 x 20480 96.6, 92.4.
 constexpr int ABSMAX_ROUND = 32;
 inline AbsmaxGrid absmax_grid(long long M, long long K, int vec, long long cus = 256)
 {
@@ -168,14 +169,18 @@ inline AbsmaxGrid absmax_grid(long long M, long long K, int vec, long long cus =
     long long rows = M, best = -1;
     for (int per_cu = 2; per_cu <= 4; ++per_cu) {
         const long long s = std::max(1LL, std::min(most, std::min<long long>(MAX_CANDIDATES, per_cu * cus) / bx));
-        const long long r = (M + s - 1) / s, wgs = bx * ((M + r - 1) / r);
-        long long cost = 10 * ((wgs + cus - 1) / cus) * ((r + ABSMAX_ROUND - 1) / ABSMAX_ROUND);
-        if (r % 64 == 0 && pitch % 4096 == 0) cost += cost / 10;
-        if (best < 0 || cost < best) {
-            best = cost;
-            rows = r;
+        const long long least = ((M + s - 1) / s + ABSMAX_ROUND - 1) / ABSMAX_ROUND;
+        for (long long rounds = least; rounds <= least + 1 && rounds <= most; ++rounds) {
+            const long long wgs = bx * ((most + rounds - 1) / rounds);
+            long long cost = 10 * ((wgs + cus - 1) / cus) * rounds;
+            if (rounds % 2 == 0 && pitch % 4096 == 0) cost += cost / 4;
+            if (best < 0 || cost < best) {
+                best = cost;
+                rows = rounds * ABSMAX_ROUND;
+            }
         }
     }
+    rows = std::min(rows, M);
     return AbsmaxGrid{(int)bx, (int)((M + rows - 1) / rows), (int)rows};
 }
 
