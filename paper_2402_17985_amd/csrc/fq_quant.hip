@@ -122,11 +122,60 @@ __global__ __launch_bounds__(256) void colabsmax_kernel(const void* __restrict__
 // What this replaces: a kernel that cleared K channel maxima, atomic maxima on them, and a gather of all channel maxima
 // over the map in every workgroup of the kernel that forms the multipliers.
 // ALL: a' = max |X| over all channels, whatever the map (weights, peel split).
+// What flatten_quant_direct_kernel needs of the map, worked out once instead of in each of its workgroups: copy counts of plain
+// head groups as bytes (MANY: that many or more; 0 in other groups), sources of the tail's slots as 16-bit channel numbers (KQ:
+// the slot holds 0), and per tail group whether each slot holds 0 whatever the input or repeats a channel of a plain group with
+// that channel's own copy count.  Lies in the workspace where the general path keeps its multipliers.
+constexpr int MANY = 255;
+struct PreparedMap {
+    uint8_t* counts;      // [KQ]
+    uint16_t* sources;    // [16 NT]
+    uint8_t* copies;      // [NT]
+};
+__host__ __device__ __forceinline__ PreparedMap prepared_map(float* mslot, int K, int Kpad)
+{
+    PreparedMap m;
+    m.counts = reinterpret_cast<uint8_t*>(mslot);
+    m.sources = reinterpret_cast<uint16_t*>(m.counts + (K & ~15));
+    m.copies = reinterpret_cast<uint8_t*>(m.sources + (Kpad - (K & ~15)));
+    return m;
+}
+// Workgroup w of n, 512 threads, a slot each.
+__device__ void prepare_map(const int32_t* __restrict__ src, const int32_t* __restrict__ rep, int K, int Kpad, int w, int n, PreparedMap out)
+{
+    const int KQ = K & ~15, tid = threadIdx.x, lane = tid & 63;
+    auto group_all = [&](bool ok) -> bool { return ((__ballot(ok) >> (lane & 48)) & 0xffffull) == 0xffffull; };
+    for (int p = w * 512 + tid; p < Kpad; p += n * 512) {       // Kpad and KQ are multiples of 16: groups stay together
+        const int j = src[p], c = rep[p];
+        if (p < KQ) {
+            const bool plain = group_all(j == p && c > 0);
+            out.counts[p] = plain ? (uint8_t)min(c, MANY) : (uint8_t)0;
+            continue;
+        }
+        bool ok = (unsigned)j >= (unsigned)K;
+        out.sources[p - KQ] = (uint16_t)(ok ? KQ : min(j, KQ));
+        if (!ok && j < KQ && c > 0 && rep[j] == c) {
+            int sv[16], nv[16];
+            const int g0 = j & ~15;
+            load8(src + g0, sv);
+            load8(src + g0 + 8, sv + 8);
+            load8(rep + g0, nv);
+            load8(rep + g0 + 8, nv + 8);
+            ok = true;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) ok = ok && sv[i] == g0 + i && nv[i] > 0;
+        }
+        const bool copies = group_all(ok);
+        if ((lane & 15) == 0) out.copies[(p - KQ) >> 4] = copies ? 1 : 0;
+    }
+}
+
+// map: when not null, the grid's first row of workgroups prepares the map there and the strips follow.
 template <int DT, bool ALL, bool NT>
 __global__ __launch_bounds__(ALL ? 256 : 512) void tensor_absmax_kernel(const void* __restrict__ Xv, int M, int K, int ld,
                                                                         int rows_per_block, const int32_t* __restrict__ src,
                                                                         const int32_t* __restrict__ rep, int Kpad,
-                                                                        float* __restrict__ cand)
+                                                                        float* __restrict__ cand, float* __restrict__ map)
 {
     constexpr int VEC = Elem<DT>::VEC, COLS = 64 * VEC, NONE = 0x7fffffff, NTHR = ALL ? 256 : 512;
     __shared__ float part[4][COLS];
@@ -134,7 +183,14 @@ __global__ __launch_bounds__(ALL ? 256 : 512) void tensor_absmax_kernel(const vo
     __shared__ float red[NTHR / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c0 = blockIdx.x * COLS;
-    const int r0 = blockIdx.y * rows_per_block;
+    int strip = blockIdx.y;
+    if constexpr (!ALL) {
+        if (map && strip-- == 0) {
+            prepare_map(src, rep, K, Kpad, blockIdx.x, gridDim.x, prepared_map(map, K, Kpad));
+            return;
+        }
+    }
+    const int r0 = strip * rows_per_block;
     if constexpr (!ALL) {
         for (int c = tid; c < COLS; c += NTHR) copies[c] = NONE;
         __syncthreads();
@@ -185,7 +241,7 @@ __global__ __launch_bounds__(ALL ? 256 : 512) void tensor_absmax_kernel(const vo
     if (tid == 0) {
 #pragma unroll
         for (int w = 1; w < NTHR / 64; ++w) best = fmaxf(best, red[w]);
-        cand[blockIdx.y * gridDim.x + blockIdx.x] = best;
+        cand[strip * gridDim.x + blockIdx.x] = best;
     }
 }
 
@@ -194,7 +250,8 @@ __global__ __launch_bounds__(ALL ? 256 : 512) void tensor_absmax_kernel(const vo
 // ---------------------------------------------------------------------------------------------
 // Every workgroup takes the maximum of the candidates of tensor_absmax_kernel (one load per thread, unless the matrix has
 // more than 1024 column blocks; none when the bound is static), tabulates the multipliers m(n) = fl32(qmax / (n * a')) for
-// n < 1024 in LDS (one float64 division per thread), and fills its own 1024 slots of mslot.  Workgroup 0 also writes the scale.
+// n < 256 in LDS (one float64 division per thread of four waves), and fills its own 1024 slots of mslot.  Workgroup 0 also writes the scale.
+constexpr int SCALE_TABLE = 256;
 __global__ __launch_bounds__(1024) void scale_kernel(const float* __restrict__ cand, int ncand, int K,
                                                      const int32_t* __restrict__ src,
                                                      const int32_t* __restrict__ rep, int Kpad, int qmax,
@@ -203,8 +260,15 @@ __global__ __launch_bounds__(1024) void scale_kernel(const float* __restrict__ c
                                                      float* __restrict__ scalars, uint8_t* __restrict__ gflag)
 {
     __shared__ float red[16];
-    __shared__ float table[1024];
+    __shared__ float table[SCALE_TABLE];
     const int tid = threadIdx.x;
+    // the map first: its loads, and those that depend on them, travel while a' is formed
+    const int p = blockIdx.x * 1024 + tid;
+    const bool inside = p < Kpad, counted = mode != 2;
+    const int s = inside ? src[p] : -1, n = inside ? (counted ? rep[p] : 1) : 0;
+    // (A map may have fewer slots than there are channels: channel s then has no slot s.)
+    const bool has_own = (unsigned)s < (unsigned)min((K >> 4) << 4, Kpad);
+    const int own_src = has_own ? src[s] : -1, own_n = has_own ? (counted ? rep[s] : 1) : 0;
     float a;
     if (absmax_in) {
         a = *absmax_in;
@@ -230,12 +294,7 @@ __global__ __launch_bounds__(1024) void scale_kernel(const float* __restrict__ c
             scalars[0] = a;
             scalars[2] = (a == 0.0f) ? 0.0f : (float)((double)qmax / (double)a);
         }
-        const int p = blockIdx.x * 1024 + tid;
-        if (p < Kpad) {
-            const int sp = src[p], e = rep[p];
-            const bool valid = (unsigned)sp < (unsigned)K && e >= 0;
-            mslot[p] = valid ? (float)e * T : __builtin_inff();
-        }
+        if (inside) mslot[p] = (unsigned)s < (unsigned)K && n >= 0 ? (float)n * T : __builtin_inff();      // n: the ordinal e
         return;
     }
     const double ad = (double)a;
@@ -243,39 +302,29 @@ __global__ __launch_bounds__(1024) void scale_kernel(const float* __restrict__ c
         *scale_out = (a == 0.0f) ? 1.0f : (float)(ad / (double)qmax);
         scalars[0] = a;
     }
-    table[tid] = (tid > 0 && a != 0.0f) ? (float)((double)qmax / ((double)tid * ad)) : 0.0f;
+    if (tid < SCALE_TABLE) table[tid] = (tid > 0 && a != 0.0f) ? (float)((double)qmax / ((double)tid * ad)) : 0.0f;
     __syncthreads();
-    const int p = blockIdx.x * 1024 + tid;
-    if (p < Kpad) {
-        const int s = src[p];
-        const int n = (mode == 2) ? 1 : rep[p];
+    if (inside) {
         const bool valid = (unsigned)s < (unsigned)K && n > 0 && a != 0.0f;
         float m = 0.0f;
-        if (valid) m = (n < 1024) ? table[n] : (float)((double)qmax / ((double)n * ad));
+        if (valid) m = (n < SCALE_TABLE) ? table[n] : (float)((double)qmax / ((double)n * ad));
         mslot[p] = m;
     }
     // gflag[g] = 1 when the 16 slots of group g are the 16 channels at the same indices (the head of
     // the map): such a group is read with vector loads and its quantized values can be copied by the
     // appended slots that repeat its channels
-    const bool ident = p < Kpad && p < K && src[p] == p;
+    const bool ident = inside && p < K && s == p;
     const unsigned long long bal = __ballot(ident);
     if (p < Kpad && (tid & 15) == 0) gflag[p >> 4] = (((bal >> (tid & 48)) & 0xffffull) == 0xffffull) ? 1 : 0;
     // cflag[g] = 1 when every slot of group g either holds 0 whatever the input (padding) or repeats a
     // channel j < 16 * (K / 16) whose own slot j is the identity slot with the same copy count: the
-    // slot's quantized value then equals slot j's and can be copied instead of recomputed.  (A map may have fewer slots
-    // than there are channels: channel j then has no slot j.)
-    bool copyable = false;
-    if (p < Kpad) {
-        const int j = src[p];
-        if ((unsigned)j >= (unsigned)K) copyable = true;
-        else if (j < min((K >> 4) << 4, Kpad) && src[j] == j) copyable = (mode == 2) || (rep[p] > 0 && rep[j] == rep[p]);
-    }
+    // slot's quantized value then equals slot j's and can be copied instead of recomputed.
+    const bool copyable = inside && ((unsigned)s >= (unsigned)K || (own_src == s && n > 0 && own_n == n));
     const unsigned long long balc = __ballot(copyable);
     // ... and 2 when, in addition, all 16 slots repeat the same channel (the long runs of a large
     // outlier's copies): one value then fills the group
-    const int sp = (p < Kpad) ? src[p] : -1;
-    const int s0 = __shfl(sp, (tid & 63) & ~15, 64);
-    const unsigned long long balu = __ballot(sp == s0 && (unsigned)sp < (unsigned)K);
+    const int s0 = __shfl(s, (tid & 63) & ~15, 64);
+    const unsigned long long balu = __ballot(s == s0 && (unsigned)s < (unsigned)K);
     uint8_t* cflag = gflag + ((Kpad >> 4) + 1);
     if (p < Kpad && (tid & 15) == 0) {
         const bool all_copy = ((balc >> (tid & 48)) & 0xffffull) == 0xffffull;
@@ -289,7 +338,7 @@ __global__ __launch_bounds__(1024) void scale_kernel(const float* __restrict__ c
 // ---------------------------------------------------------------------------------------------
 // LDS of flatten_quant_direct_kernel before the strip itself: the table of multipliers and the wave maxima.  A plain group's
 // copy counts are kept as bytes; MANY stands for MANY copies or more, whose count is read from the map where it matters.
-constexpr int DIRECT_TABLE = 256, DIRECT_RED = 16, MANY = 255;
+constexpr int DIRECT_TABLE = 256, DIRECT_RED = 16;
 constexpr int DIRECT_LDS_FIXED = (DIRECT_TABLE + DIRECT_RED) * 4;
 
 // PEEL = false: slot value x * m_p (equal split; m_p from mslot).  PEEL = true: the printed split of
@@ -539,7 +588,8 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
 // and has one thread per P head groups, so that a strip is one round of loads.
 //   loads      X of the first strip, the map (head and tail) and the bound or the candidates are asked for at once: what
 //              follows waits one round trip to memory for all of them.
-//   the map    thread t reads the sources and copy counts of its groups t, t + head threads, ... of the head.  A group is
+//   the map    from the absmax pass, which prepares it (PreparedMap: a byte per slot instead of eight, and no checks; 500 x 11008
+//              dynamic 9.6 -> 7.8 us, 2048 x 4096 10.8 -> 9.5); else thread t reads the sources and copy counts of its groups t, t + head threads, ... of the head.  A group is
 //              plain when its slots are the channels at the same indices with copies; the counts of plain groups are left
 //              in LDS, and from them follows which appended groups only repeat their values.  (Counts beyond the table are
 //              rare and divide once per slot.  Gathering their groups and copies element by element took 18.0 us for 1000 x
@@ -562,11 +612,13 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
                                                                     const float* __restrict__ cand, int ncand,
                                                                     float* __restrict__ scale_out,
                                                                     float* __restrict__ scalars, uint8_t* __restrict__ out,
-                                                                    int rows_each, int rows_more, int slots)
+                                                                    int rows_each, int rows_more, int slots, float* __restrict__ map)
 {
     typedef typename Elem<DT>::type T;
     constexpr int VEC = Elem<DT>::VEC, NV = 16 / VEC;
     constexpr int QMAX = (BITS == 8) ? 127 : 7;
+    // the tail of the map is asked for with the rest where that fits the registers (fp32 2000 x 4096 static, whose registers then spill: 13.6 -> 15.1 us)
+    constexpr bool TAIL_EARLY = DT != FQ_F32 && P == 1;
     const int nthr = blockDim.x, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = nthr >> 6;
     extern __shared__ __align__(16) uint8_t lds[];
@@ -630,14 +682,26 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
     float best = 0.0f;
     if (absmax_in) best = *absmax_in;
     int sv[P][16], nv[P][16];
-#pragma unroll
-    for (int p = 0; p < P; ++p)
-        if (t0 + p * head < NH) load_slots((t0 + p * head) << 4, sv[p], nv[p]);
-    // eight slots of the tail per thread and pass, the first pass now; the two threads of a group sit in adjacent lanes
     int tj[8], tn[8];
-    if (tid * 8 < NT * 16) {
-        load8(src + KQ + tid * 8, tj);
-        load_counts(KQ + tid * 8, tn);
+    uint32_t nb[P][4];                                         // copy counts of this thread's plain groups, as bytes
+    const PreparedMap pm = prepared_map(map, K, Kpad);
+    if (map) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            v4u n = {0, 0, 0, 0};
+            if (t0 + p * head < NH) n = *reinterpret_cast<const v4u*>(pm.counts + ((t0 + p * head) << 4));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) nb[p][i] = n[i];
+        }
+    } else {
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            if (t0 + p * head < NH) load_slots((t0 + p * head) << 4, sv[p], nv[p]);
+        // eight slots of the tail per thread and pass, the first pass now; the two threads of a group sit in adjacent lanes
+        if (TAIL_EARLY && tid * 8 < NT * 16) {
+            load8(src + KQ + tid * 8, tj);
+            load_counts(KQ + tid * 8, tn);
+        }
     }
     load_strip(row_begin);
     if (cand) {                                                // at most 1024 unless K is beyond 2^18: four per thread and pass
@@ -667,31 +731,44 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
     }
 
     // ---- the map ----
-    uint32_t nb[P][4];                                         // copy counts of this thread's plain groups, as bytes
     int plain = 0, many = 0;                                   // groups of this thread: plain; with a count of MANY
     bool other = false;                                        // a group that is neither plain nor copies of plain ones
+    if (map) {
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const int g = t0 + p * head;
+        for (int p = 0; p < P; ++p) {
+            if ((nb[p][0] & 0xff) == 0) continue;
+            plain |= 1 << p;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) nb[p][i] = 0;
-        if (g < NH) {
-            int differ = 0, least = nv[p][0], most = nv[p][0];
+            for (int i = 0; i < 16; ++i)
+                if (((nb[p][i >> 2] >> (8 * (i & 3))) & 0xff) == MANY) many |= 1 << p;
+        }
+        // the tail's sources and flags to LDS
+        for (int t = tid * 8; t < NT * 16; t += nthr * 8) *reinterpret_cast<v4u*>(ts + t) = *reinterpret_cast<const v4u*>(pm.sources + t);
+        for (int t = tid; t < NT; t += nthr) tf[t] = pm.copies[t];
+    } else {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                differ |= sv[p][i] ^ ((g << 4) + i);
-                least = min(least, nv[p][i]);
-                most = max(most, nv[p][i]);
+        for (int p = 0; p < P; ++p) {
+            const int g = t0 + p * head;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) nb[p][i] = 0;
+            if (g < NH) {
+                int differ = 0, least = nv[p][0], most = nv[p][0];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    differ |= sv[p][i] ^ ((g << 4) + i);
+                    least = min(least, nv[p][i]);
+                    most = max(most, nv[p][i]);
+                }
+                if (differ == 0 && least > 0) {
+                    plain |= 1 << p;
+                    if (most >= MANY) many |= 1 << p;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) nb[p][i >> 2] |= (uint32_t)min(nv[p][i], MANY) << (8 * (i & 3));
+                } else {
+                    other = true;
+                }
+                if (first) *reinterpret_cast<v4u*>(counts8 + (g << 4)) = v4u{nb[p][0], nb[p][1], nb[p][2], nb[p][3]};
             }
-            if (differ == 0 && least > 0) {
-                plain |= 1 << p;
-                if (most >= MANY) many |= 1 << p;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) nb[p][i >> 2] |= (uint32_t)min(nv[p][i], MANY) << (8 * (i & 3));
-            } else {
-                other = true;
-            }
-            if (first) *reinterpret_cast<v4u*>(counts8 + (g << 4)) = v4u{nb[p][0], nb[p][1], nb[p][2], nb[p][3]};
         }
     }
     // a' from all of X (few rows): the plain groups' part.  Rounding is monotonic, so the largest element is divided.
@@ -765,8 +842,8 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
     }
     // Sources of the phase-2 slots as 16-bit channel numbers (KQ: the slot holds 0) and, per group, whether every
     // slot holds 0 whatever the input or repeats a channel of a plain group with that channel's own copy count.
-    for (int t = tid * 8; t < NT * 16; t += nthr * 8) {
-        if (t != tid * 8) {
+    for (int t = tid * 8; !map && t < NT * 16; t += nthr * 8) {
+        if (!TAIL_EARLY || t != tid * 8) {
             load8(src + KQ + t, tj);
             load_counts(KQ + t, tn);
         }
@@ -864,7 +941,8 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
     for (int p = 0; p < P; ++p)
         if (first && t0 + p * head < NH && !((plain >> p) & 1)) slow |= 1 << p;
 
-    const int tail_waves = (NT + 63) >> 6;
+    // phase 2: a wave takes 64 groups of a row, or (few appended groups) all groups of two to eight rows
+    const int tail_waves = (NT + 63) >> 6, tail_log = NT <= 8 ? 3 : NT <= 16 ? 2 : NT <= 32 ? 1 : 0;
     for (int rs = row_begin; rs < row_end; rs += R) {
         const int nr = min(row_end - rs, R);
         // ---- phase 1: the head ----
@@ -887,15 +965,15 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
         load_strip(rs + R);
         strip_barrier();
 
-        // ---- this thread's head groups that are not plain; then phase 2, appended copies and padding: a wave takes 64
-        //      groups of a row ----
+        // ---- this thread's head groups that are not plain; then phase 2, appended copies and padding (one row per
+        //      wave whatever NT took 9000 x 300 static from 12.1 to 18.4 us) ----
         for (int k = 0; slow && k < P * nr; ++k)
             if ((slow >> (k / nr)) & 1) gather_group(t0 + (k / nr) * head, rs + k % nr);
-        for (int rr = 0, w = wave;; w += waves) {
-            for (; rr < nr && w >= tail_waves; w -= tail_waves) ++rr;
-            if (rr >= nr) break;
-            const int gt = w * 64 + lane;
-            if (gt >= NT) continue;
+        for (int rb = 0, w = wave;; w += waves) {
+            for (; rb < nr && w >= tail_waves; w -= tail_waves) rb += 1 << tail_log;
+            if (rb >= nr) break;
+            const int rr = rb + (lane >> (6 - tail_log)), gt = w * 64 + (lane & ((64 >> tail_log) - 1));
+            if (rr >= nr || gt >= NT) continue;
             if (!tf[gt]) {
                 gather_group(NH + gt, rs + rr);
                 continue;
@@ -918,7 +996,9 @@ void launch_colabsmax(const void* X, int M, int K, int ld, bool accumulate, uint
     constexpr int VEC = Elem<DT>::VEC;
     if (!accumulate) fill_u32_kernel<<<(K + 255) / 256, 256, 0, stream>>>(cmax, K, 0u);
     const AbsmaxGrid a = absmax_grid(M, K, VEC, compute_units());
-    auto kern = beyond_mib<DT>(M, K, 32) ? colabsmax_kernel<DT, true> : colabsmax_kernel<DT, false>;
+    // Streamed from 96 MiB on: smaller activations may still lie in the memory-side cache, from which the hint keeps nothing (fp32
+    // 4096 x 4096, three such in turn: 15.1 us with it, 11.4 without; bf16 8192 x 11008 29.4 and 36.9).
+    auto kern = beyond_mib<DT>(M, K, 96) ? colabsmax_kernel<DT, true> : colabsmax_kernel<DT, false>;
     kern<<<dim3((unsigned)a.blocks, (unsigned)a.strips), 256, 0, stream>>>(X, M, K, ld, a.rows_per_strip, cmax);
 }
 
@@ -926,16 +1006,16 @@ void launch_colabsmax(const void* X, int M, int K, int ld, bool accumulate, uint
 // candidate_capacity(K) floats; their number goes to *ncand.
 template <int DT>
 int launch_tensor_absmax(const void* X, int M, int K, int ld, const int32_t* src, const int32_t* rep, int Kpad,
-                         bool all_channels, float* cand, int* ncand, hipStream_t stream)
+                         bool all_channels, float* cand, int* ncand, hipStream_t stream, float* map = nullptr)
 {
     const AbsmaxGrid a = absmax_grid(M, K, Elem<DT>::VEC, compute_units());
-    const dim3 grid((unsigned)a.blocks, (unsigned)a.strips);
+    const dim3 grid((unsigned)a.blocks, (unsigned)a.strips + (map ? 1 : 0));
     // The quantizer reads X again: what the memory-side cache can hold is left there (streamed past it, the pass itself gains,
     // the call loses: 8192 x 4096 bf16 to E3M2 37.5 -> 45.9 us; 8192 x 20480 to nibbles, 335 MB, gains, 168.2 -> 162.7).
     const bool nt = beyond_mib<DT>(M, K, 224);
     auto kern = all_channels ? (nt ? tensor_absmax_kernel<DT, true, true> : tensor_absmax_kernel<DT, true, false>)
                              : (nt ? tensor_absmax_kernel<DT, false, true> : tensor_absmax_kernel<DT, false, false>);
-    kern<<<grid, all_channels ? 256 : 512, 0, stream>>>(X, M, K, ld, a.rows_per_strip, src, rep, Kpad, cand);
+    kern<<<grid, all_channels ? 256 : 512, 0, stream>>>(X, M, K, ld, a.rows_per_strip, src, rep, Kpad, cand, map);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(FQ_ERR_HIP, "absmax launch failed: %s", hipGetErrorString(e));
     *ncand = a.candidates();
@@ -943,7 +1023,7 @@ int launch_tensor_absmax(const void* X, int M, int K, int ld, const int32_t* src
 }
 
 typedef void (*direct_kernel_t)(const void*, int, int, int, const int32_t*, const int32_t*, int, const float*, const float*, int,
-                                float*, float*, uint8_t*, int, int, int);
+                                float*, float*, uint8_t*, int, int, int, float*);
 
 // Rows per strip of flatten_quant_direct_kernel: what the registers hold in flight (fp32 takes twice as many).
 template <int DT, int P> constexpr int direct_rows() { return DT == FQ_F32 ? (P == 1 ? 2 : 1) : (P == 1 ? 4 : 2); }
@@ -1013,10 +1093,12 @@ int launch_for_dtype(const void* X, int M, int K, int ld, const int32_t* src_idx
         else rc = bits == 8 ? direct_kernel<DT, 8, 2>(&kern) : bits == 6 ? direct_kernel<DT, 6, 2>(&kern) : direct_kernel<DT, 4, 2>(&kern);
         if (rc) return rc;
         int ncand = 0;
+        // the absmax pass works the map out along the way (weights have no copy counts: theirs stays with the quantizer)
+        float* map = mode == 0 && !self ? ws.mslot : nullptr;
         if (dynamic && !self)
-            if ((rc = launch_tensor_absmax<DT>(X, M, K, ld, src_idx, rep, Kpad, all_channels, cand, &ncand, stream))) return rc;
+            if ((rc = launch_tensor_absmax<DT>(X, M, K, ld, src_idx, rep, Kpad, all_channels, cand, &ncand, stream, map))) return rc;
         kern<<<(unsigned)nblk, nthr, lds, stream>>>(X, M, K, ld, src_idx, mode == 2 ? nullptr : rep, Kpad, absmax_in,
-                                                    ncand ? cand : nullptr, ncand, scale_out, ws.scalars, o8, M / nblk, M % nblk, slots);
+                                                    ncand ? cand : nullptr, ncand, scale_out, ws.scalars, o8, M / nblk, M % nblk, slots, map);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(FQ_ERR_HIP, "flatten-quantize launch failed: %s", hipGetErrorString(e));
         return FQ_OK;
