@@ -113,18 +113,15 @@ __global__ __launch_bounds__(NTHR, 4) void linear_decode_kernel(const void* __re
         a = *absmax_in;
         if (!(a >= 0.0f) || a > 3.0e38f) a = 0.0f;             // negative / NaN / Inf static bound: treated as 0
     } else {
-        // a' = max fl32(|x| / n): of several copies the largest exact quotient, compared by cross multiplication in float64
-        // (exact for n < 2^29), divided once per thread; rounding is monotonic
-        float best = 0.0f, bc = 0.0f;
+        // a' = max fl32(|x| / n): the largest exact quotient, compared by cross multiplication in float64 (exact for n <
+        // 2^29), divided once per thread; rounding is monotonic.  (A branch for n = 1: 1 x 300 x 700 7.9 us, without 7.5.)
+        float bc = 0.0f;
         int bn = 1;
         auto consider = [&](const int (&s)[16], const int (&n)[16], const float (&x)[16]) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                if ((unsigned)s[i] >= (unsigned)K || n[i] <= 0) continue;
                 const float v = fabsf(x[i]);
-                if (n[i] == 1) {
-                    best = fmaxf(best, v);
-                } else if ((double)v * (double)bn > (double)bc * (double)n[i]) {
+                if ((unsigned)s[i] < (unsigned)K && n[i] > 0 && (double)v * (double)bn > (double)bc * (double)n[i]) {
                     bc = v;
                     bn = n[i];
                 }
@@ -137,7 +134,7 @@ __global__ __launch_bounds__(NTHR, 4) void linear_decode_kernel(const void* __re
             load_x(g, s, load_slots(g, s, n), x);
             consider(s, n, x);
         }
-        best = fmaxf(best, (float)((double)bc / (double)bn));
+        float best = (float)((double)bc / (double)bn);
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
         if (lane == 0) red[wave] = best;

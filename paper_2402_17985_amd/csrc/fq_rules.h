@@ -113,7 +113,8 @@ struct FewPlan {
 //     2048 x 4096 10.6 / 9.6, but 8 x 4096 x 256 10.8 / 11.2, 16 x 4096 x 4096 12.6 / 15.5, 8 x 5120 x 4096 13.5 / 16.1.
 //   - One row, where the other choice is linear_decode_kernel: its preparation is shorter, with several workgroups per CU from more
 //     than 16 columns per CU on it repeats it.  INT8 2048 x 256 6.3 / 7.1, 2048 x 4096 7.3 / 7.4, 4096 x 256 9.4 / 8.2, 2048 x 11008 10.9 /
-//     8.4; nibbles 2048 x 4096 6.7 / 7.3, 4096 x 1024 9.2 / 8.7, 2048 x 11008 9.1 / 7.4; E3M2 4096 x 1024 9.1 / 9.2, 8192 x 1024 10.2 / 8.1.
+//     8.4; nibbles 2048 x 4096 6.7 / 7.3, 4096 x 1024 9.2 / 8.7, 2048 x 11008 9.1 / 7.4; E3M2 4096 x 1024 9.1 / 9.2, 8192 x 1024 10.2 / 8.1,
+//     1024 x 5120 6.5 / 7.6, 2048 x 11008 8.8 / 8.4.
 //     With a ragged last group (K no multiple of 16, which is gathered) 257 x 11008 8.2 / 8.5, 2005 x 11008 10.0 / 8.6, nibbles 4100 x
 //     256 8.9 / 10.0, 4100 x 11008 13.6 / 12.5; E3M2 2005 x 11008 7.9 / 8.7.
 inline bool few_plan(int M, int N, int K, int ld, int Kpad, int bits, int x_bytes, int cus, FewPlan* plan)
@@ -124,7 +125,7 @@ inline bool few_plan(int M, int N, int K, int ld, int Kpad, int bits, int x_byte
     if (e3m2 && (long long)M * K > 16384) return false;
     if (M == 1) {
         const bool wide = N > 16 * cus;
-        if (K % 16 != 0 ? !wide || K < 2000 || e3m2 : !wide && K < (e3m2 ? 8192 : 4096)) return false;
+        if (K % 16 != 0 ? !wide || K < 2000 || e3m2 : e3m2 ? K < 8192 && !(wide && K >= 2048) : !wide && K < 4096) return false;
     }
     const int head = (NH + 63) / 64 * 64, slots = std::max(1, std::min(64 * FEW_PREP_WAVES / head, M));
     if ((M + slots - 1) / slots > few_rows_held(x_bytes)) return false;
