@@ -805,7 +805,15 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
 #pragma unroll
             for (int i = 0; i < 16; ++i) mx[i] = 0.0f;
             const T* xp = X + ((t0 + p * head) << 4);
-            for (int r = slot; r < M; r += U * slots) {
+            auto take = [&](const v4u (&in)[NV]) {
+                float x[16];
+#pragma unroll
+                for (int i = 0; i < NV; ++i) widen16<DT>(in[i], x + i * VEC);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) mx[i] = fmaxf(mx[i], fabsf(x[i]));
+            };
+            int r = slot;
+            for (; r + slots < M; r += U * slots) {            // two rows or more
                 v4u in[U][NV];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -814,13 +822,13 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
                     for (int i = 0; i < NV; ++i) in[u][i] = reinterpret_cast<const v4u*>(xr)[i];
                 }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    float x[16];
+                for (int u = 0; u < U; ++u) take(in[u]);
+            }
+            if (r < M) {                                       // one left (1 x 20480 fp32, read four times: 15.4 us, once 12.9)
+                v4u in[NV];
 #pragma unroll
-                    for (int i = 0; i < NV; ++i) widen16<DT>(in[u][i], x + i * VEC);
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) mx[i] = fmaxf(mx[i], fabsf(x[i]));
-                }
+                for (int i = 0; i < NV; ++i) in[i] = reinterpret_cast<const v4u*>(xp + (size_t)r * ld)[i];
+                take(in);
             }
             int n[16];
 #pragma unroll

@@ -1,0 +1,31 @@
+"""The quantizer of a few rows with a dynamic scale, whose workgroups each take the maximum of all of X: every number of rows that is
+left over by the rounds of rows, and heads whose last group is ragged, against the CPU oracle, byte for byte."""
+import numpy as np
+import pytest
+
+import paper_2402_17985_amd as fq
+from tests.test_gpu_quant_direct import _check
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(M, K, at, copies=3):
+    """Rows whose largest element (over copies) lies at (row, channel) `at`, and a plan with a few copied channels."""
+    rng = np.random.default_rng(M + K)
+    X = rng.uniform(-1.0, 1.0, (M, K)).astype(np.float32)
+    chmax = np.ones(K, dtype=np.float32)
+    chmax[[K // 3, K // 2]] = [copies, 2]
+    X[:, K // 3] *= copies
+    X[at] = -3.25
+    src, rep, _, _ = fq.fq_flatten_plan(chmax, 1.0, 128)
+    return X, src, rep
+
+
+# One set of threads for the head and several, one head group per thread and two
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("last", [False, True])
+@pytest.mark.parametrize("dtype,M,K", [(d, M, K) for d in ("bf16", "f32") for M, K in
+                                       ((1, 256), (2, 256), (5, 256), (9, 256), (13, 1024), (17, 256), (1, 4096), (3, 4096), (5, 4096), (1, 20480), (2, 16400), (3, 20480))])
+def test_every_number_of_rows(dtype, M, K, last, bits):
+    X, src, rep = _layer(M, K, (M - 1, K - 1) if last else (M // 2, 0))
+    _check(X, dtype, src, rep, bits, None)
