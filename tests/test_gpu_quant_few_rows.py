@@ -29,3 +29,14 @@ def _layer(M, K, at, copies=3):
 def test_every_number_of_rows(dtype, M, K, last, bits):
     X, src, rep = _layer(M, K, (M - 1, K - 1) if last else (M // 2, 0))
     _check(X, dtype, src, rep, bits, None)
+
+
+# The last group gathered from global memory: the maximum in it or before it, with further groups of that kind and without
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("where", ["ragged", "head", "gathered"])
+@pytest.mark.parametrize("dtype,M,K", [("bf16", 1, 20), ("f32", 7, 300), ("bf16", 64, 1000), ("f16", 8, 2500), ("f32", 20, 2500), ("bf16", 5, 16405), ("f32", 2, 20490)])
+def test_ragged_heads(dtype, M, K, where, bits):
+    X, src, rep = _layer(M, K, (M - 1, {"ragged": K - 1, "head": 0, "gathered": 14}[where]))
+    if where == "gathered":
+        src[[14, 15]] = src[[15, 14]]
+    _check(X, dtype, src, rep, bits, None)
