@@ -681,7 +681,11 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
     // ---- the loads ----
     float best = 0.0f;
     if (absmax_in) best = *absmax_in;
-    int sv[P][16], nv[P][16];
+    // With two head groups per thread what is live at once decides whether registers go to scratch (up to 80 bytes per lane): gathered
+    // groups are taken in halves, fp32 rows two at a time for the maximum, and fp32 reads the map of its groups one after the other.
+    // Static, us, before / so: fp32 to INT8 200 x 25000 15.5 / 12.5, 300 x 30000 24.0 / 18.1; bf16 to E3M2 400 x 20480 15.5 / 12.9.
+    constexpr bool MAP_EARLY = DT != FQ_F32 || P == 1;
+    int sv[MAP_EARLY ? P : 1][16], nv[MAP_EARLY ? P : 1][16];
     int tj[8], tn[8];
     uint32_t nb[P][4];                                         // copy counts of this thread's plain groups, as bytes
     const PreparedMap pm = prepared_map(map, K, Kpad);
@@ -694,9 +698,11 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
             for (int i = 0; i < 4; ++i) nb[p][i] = n[i];
         }
     } else {
+        if constexpr (MAP_EARLY) {
 #pragma unroll
-        for (int p = 0; p < P; ++p)
-            if (t0 + p * head < NH) load_slots((t0 + p * head) << 4, sv[p], nv[p]);
+            for (int p = 0; p < P; ++p)
+                if (t0 + p * head < NH) load_slots((t0 + p * head) << 4, sv[p], nv[p]);
+        }
         // eight slots of the tail per thread and pass, the first pass now; the two threads of a group sit in adjacent lanes
         if (TAIL_EARLY && tid * 8 < NT * 16) {
             load8(src + KQ + tid * 8, tj);
@@ -752,18 +758,20 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
 #pragma unroll
             for (int i = 0; i < 4; ++i) nb[p][i] = 0;
             if (g < NH) {
-                int differ = 0, least = nv[p][0], most = nv[p][0];
+                const int e = MAP_EARLY ? p : 0;
+                if constexpr (!MAP_EARLY) load_slots(g << 4, sv[0], nv[0]);
+                int differ = 0, least = nv[e][0], most = nv[e][0];
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    differ |= sv[p][i] ^ ((g << 4) + i);
-                    least = min(least, nv[p][i]);
-                    most = max(most, nv[p][i]);
+                    differ |= sv[e][i] ^ ((g << 4) + i);
+                    least = min(least, nv[e][i]);
+                    most = max(most, nv[e][i]);
                 }
                 if (differ == 0 && least > 0) {
                     plain |= 1 << p;
                     if (most >= MANY) many |= 1 << p;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) nb[p][i >> 2] |= (uint32_t)min(nv[p][i], MANY) << (8 * (i & 3));
+                    for (int i = 0; i < 16; ++i) nb[p][i >> 2] |= (uint32_t)min(nv[e][i], MANY) << (8 * (i & 3));
                 } else {
                     other = true;
                 }
@@ -800,7 +808,7 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             if (!((plain >> p) & 1)) continue;
-            constexpr int U = 4;                               // rows in flight
+            constexpr int U = DT == FQ_F32 && P == 2 ? 2 : 4;     // rows in flight
             float mx[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) mx[i] = 0.0f;
@@ -932,18 +940,30 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
     // one group of one row in its general form: every slot's source element gathered from global memory
     auto gather_group = [&](int g, int row) {
         const T* xr = X + (size_t)row * ld;
-        int s[16], n[16];
-        float x[16], mult[16];
-        load_slots(g << 4, s, n);
+        constexpr int U = P == 1 ? 16 : 8;                     // slots at a time
+        v4u q = {0, 0, 0, 0};
+#pragma unroll 1
+        for (int h = 0; h < 16; h += U) {
+            int s[U], n[U];
+            float x[U], mult[U];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const bool in = (unsigned)s[i] < (unsigned)K;             // a slot without a channel: 0 whatever X holds
-            const float xs = Elem<DT>::widen(xr[in ? s[i] : 0]);
-            x[i] = in ? xs : 0.0f;
-            mult[i] = 0.0f;
-            if (in && n[i] > 0) mult[i] = n[i] < DIRECT_TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
+            for (int i = 0; i < U; i += 8) {
+                load8(src + (g << 4) + h + i, s + i);
+                load_counts((g << 4) + h + i, n + i);
+            }
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const bool in = (unsigned)s[i] < (unsigned)K;         // a slot without a channel: 0 whatever X holds
+                const float xs = Elem<DT>::widen(xr[in ? s[i] : 0]);
+                x[i] = in ? xs : 0.0f;
+                mult[i] = 0.0f;
+                if (in && n[i] > 0) mult[i] = n[i] < DIRECT_TABLE ? table[n[i]] : (a != 0.0f ? multiplier(n[i]) : 0.0f);
+            }
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                if (U == 16 || (w >> 1) == (h >> 3)) q[w] = quantize4<BITS>(x + 4 * w % U, mult + 4 * w % U);
         }
-        store_group<BITS>(quantize16<BITS>(x, mult), out, orow_bytes, M, row, g);
+        store_group<BITS>(q, out, orow_bytes, M, row, g);
     };
 
     // head groups of this thread that are not plain

@@ -99,18 +99,20 @@ template <int BITS> __device__ __forceinline__ uint32_t quantized_bits(float x, 
     constexpr float hi = (float)((1 << (QB - 1)) - 1), lo = -(float)(1 << (QB - 1)), ROUND = 12582912.0f;
     return __float_as_uint(__builtin_amdgcn_fmed3f(x * m, lo, hi) + ROUND);
 }
+// (quantize4: four elements, one per byte of a word)
+template <int BITS> __device__ __forceinline__ uint32_t quantize4(const float* x, const float* m)
+{
+    uint32_t t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = quantized_bits<BITS>(x[i], m[i]);
+    const uint32_t w = bytes_of(bytes_of(t[3], t[2], 0x0c0c0400u), bytes_of(t[1], t[0], 0x0c0c0400u), 0x05040100u);
+    return BITS == 6 ? e3m2_codes(w) : w;
+}
 template <int BITS> __device__ __forceinline__ v4u quantize16(const float (&x)[16], const float (&m)[16])
 {
-    uint32_t t[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) t[i] = quantized_bits<BITS>(x[i], m[i]);
     v4u w;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t p = bytes_of(t[4 * i + 1], t[4 * i], 0x0c0c0400u), q = bytes_of(t[4 * i + 3], t[4 * i + 2], 0x0c0c0400u);
-        w[i] = bytes_of(q, p, 0x05040100u);
-        if constexpr (BITS == 6) w[i] = e3m2_codes(w[i]);
-    }
+    for (int i = 0; i < 4; ++i) w[i] = quantize4<BITS>(x + 4 * i, m + 4 * i);
     return w;
 }
 

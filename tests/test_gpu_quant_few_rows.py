@@ -40,3 +40,15 @@ def test_ragged_heads(dtype, M, K, where, bits):
     if where == "gathered":
         src[[14, 15]] = src[[15, 14]]
     _check(X, dtype, src, rep, bits, None)
+
+
+# Two head groups per thread, gathered groups of which either half, or both, differ from a plain one
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("dtype,M,K", [("bf16", 3, 16400), ("f32", 3, 20480), ("f16", 70, 20490), ("f32", 300, 17000)])
+def test_gathered_groups_of_wide_layers(dtype, M, K, static, bits):
+    X, src, rep = _layer(M, K, (M - 1, 9))
+    for base in (0, K // 2 // 16 * 16, K // 16 * 16 - 16):
+        src[base + 1], src[base + 2] = base + 2, base + 1
+    src[128 + 13], rep[256 + 3], rep[256 + 12] = -1, 0, 300
+    _check(X, dtype, src, rep, bits, 3.0 if static else None)
