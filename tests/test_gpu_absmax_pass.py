@@ -39,3 +39,17 @@ def test_dynamic_scale_finds_the_maximum_wherever_it_lies(M, K, at):
     s_x = torch.zeros(1, device=DEV)
     fq.fq_flatten_quant_act(X, dev_i32(src), dev_i32(rep), 8, out, s_x, bytes_ws(fq.fq_act_workspace_bytes(K, Kpad)))
     assert np.float32(s_x.item()) == np.float32(9.25 / 127.0)
+
+
+# Columns beyond the last whole 16 bytes, whose rows are read in rounds of their own: one to seven of them, strips of several rounds
+# and of less than one; a column's largest element in the first row, the last, and between
+@pytest.mark.parametrize("dtype,M,K", [(torch.bfloat16, 4099, 1025), (torch.bfloat16, 300, 1031), (torch.float16, 9000, 4093), (torch.float32, 4500, 1022),
+                                       (torch.float32, 33, 259), (torch.bfloat16, 5, 15), (torch.float32, 8192, 4090)])
+def test_ragged_columns(dtype, M, K):
+    g = torch.Generator(device=DEV).manual_seed(M * K)
+    X = torch.randn((M, (K + 15) // 16 * 16), device=DEV, generator=g).to(dtype)[:, :K]
+    for i, r in enumerate((0, M - 1, M // 2, M // 3, M - 2, 1, M // 5)):
+        X[r, K - 1 - i] = 30.0 + i if i % 2 else -30.0 - i
+    out = torch.empty(K, device=DEV)
+    fq.fq_channel_absmax(X, out)
+    assert torch.equal(out, X.float().abs().amax(dim=0))
