@@ -1041,7 +1041,7 @@ void launch_colabsmax(const void* X, int M, int K, int ld, bool accumulate, uint
 {
     constexpr int VEC = Elem<DT>::VEC;
     if (!accumulate) fill_u32_kernel<<<(K + 255) / 256, 256, 0, stream>>>(cmax, K, 0u);
-    const AbsmaxGrid a = absmax_grid(M, K, VEC, compute_units());
+    const AbsmaxGrid a = absmax_grid(M, K, ld, VEC, compute_units());
     // Streamed from 96 MiB on: smaller activations may still lie in the memory-side cache, from which the hint keeps nothing (fp32
     // 4096 x 4096, three such in turn: 15.1 us with it, 11.4 without; bf16 8192 x 11008 29.4 and 36.9).
     auto kern = beyond_mib<DT>(M, K, 96) ? colabsmax_kernel<DT, true> : colabsmax_kernel<DT, false>;
@@ -1054,7 +1054,7 @@ template <int DT>
 int launch_tensor_absmax(const void* X, int M, int K, int ld, const int32_t* src, const int32_t* rep, int Kpad,
                          bool all_channels, float* cand, int* ncand, hipStream_t stream, float* map = nullptr)
 {
-    const AbsmaxGrid a = absmax_grid(M, K, Elem<DT>::VEC, compute_units());
+    const AbsmaxGrid a = absmax_grid(M, K, ld, Elem<DT>::VEC, compute_units());
     const dim3 grid((unsigned)a.blocks, (unsigned)a.strips + (map ? 1 : 0));
     // The quantizer reads X again: what the memory-side cache can hold is left there (streamed past it, the pass itself gains,
     // the call loses: 8192 x 4096 bf16 to E3M2 37.5 -> 45.9 us; 8192 x 20480 to nibbles, 335 MB, gains, 168.2 -> 162.7).

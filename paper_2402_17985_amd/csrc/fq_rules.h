@@ -158,15 +158,17 @@ inline long long candidate_capacity(long long K) { return std::max<long long>(MA
 
 // A workgroup's four waves read 32 rows per round, eight loads in flight each; two to four workgroups per CU (at most 1024
 // candidates), strips of whole rounds.  Of the three counts, and one round more, the one whose fullest CU has the fewest rounds, the
-// lowest on a tie.  Strips of an even number of rounds on a pitch of whole 4 KiB count for a quarter more: they start on the same
-// memory channels.  Whole quantizer call, fp32, us: 8192 x 4096 with strips of 128 rows 63.4, 256 63.6, 288 58.1, 342 59.1; 4096 x
-// 8192 256 rows 63.0, 288 60.5; bf16 8192 x 4096 256 rows 37.8, 288 34.9.  One workgroup per CU loses elsewhere: fp32 3000 x 5001
-// 42.4, with two 35.7; weights 5120 x 20480 96.6, 92.4.
+// lowest on a tie.  Strips of an even number of rounds count for a quarter more where rows are whole 4 KiB, or where they fill a stride of
+// whole 8 KiB up to its padding: they start on the same memory channels.  (Of a wider stride taken in part that is not so: fp32 1000 x
+// 7000 of 8192 6.0 us, with odd rounds 7.5; nor does it pay below 2048 rows, whole call, 1000 x 8184 of 8192 23.4, 24.2.)  Whole quantizer call, fp32, us: 8192 x 4096 with strips of 128 rows 63.4, 256 63.6, 288
+// 58.1, 342 59.1; 4096 x 8192 256 rows 63.0, 288 60.5; bf16 8192 x 4096 256 rows 37.8, 288 34.9; maxima alone, bf16 4096 x 4088 of 4096
+// 64 rows 8.2, 32 6.8.  One workgroup per CU loses elsewhere: fp32 3000 x 5001 42.4, with two 35.7; weights 5120 x 20480 96.6, 92.4.
 constexpr int ABSMAX_ROUND = 32;
-inline AbsmaxGrid absmax_grid(long long M, long long K, int vec, long long cus = 256)
+inline AbsmaxGrid absmax_grid(long long M, long long K, long long ld, int vec, long long cus = 256)
 {
     const long long bx = (K + 64 * vec - 1) / (64 * vec);
-    const long long most = (M + ABSMAX_ROUND - 1) / ABSMAX_ROUND, pitch = K * (16 / vec);
+    const long long most = (M + ABSMAX_ROUND - 1) / ABSMAX_ROUND, row = K * (16 / vec), pitch = ld * (16 / vec);
+    const bool aliased = row % 4096 == 0 || (M >= 2048 && pitch % 8192 == 0 && row > pitch - pitch / 16);
     long long rows = M, best = -1;
     for (int per_cu = 2; per_cu <= 4; ++per_cu) {
         const long long s = std::max(1LL, std::min(most, std::min<long long>(MAX_CANDIDATES, per_cu * cus) / bx));
@@ -174,7 +176,7 @@ inline AbsmaxGrid absmax_grid(long long M, long long K, int vec, long long cus =
         for (long long rounds = least; rounds <= least + 1 && rounds <= most; ++rounds) {
             const long long wgs = bx * ((most + rounds - 1) / rounds);
             long long cost = 10 * ((wgs + cus - 1) / cus) * rounds;
-            if (rounds % 2 == 0 && pitch % 4096 == 0) cost += cost / 4;
+            if (rounds % 2 == 0 && aliased) cost += cost / 4;
             if (best < 0 || cost < best) {
                 best = cost;
                 rows = rounds * ABSMAX_ROUND;

@@ -12,9 +12,9 @@ CSRC = os.path.join(ROOT, "paper_2402_17985_amd", "csrc")
 DRIVER = """
 #include "fq_rules.h"
 extern "C" long long capacity(long long K) { return fq::candidate_capacity(K); }
-extern "C" void absmax(long long M, long long K, int vec, int* out)
+extern "C" void absmax(long long M, long long K, long long ld, int vec, int* out)
 {
-    const fq::AbsmaxGrid a = fq::absmax_grid(M, K, vec);
+    const fq::AbsmaxGrid a = fq::absmax_grid(M, K, ld, vec);
     out[0] = a.blocks; out[1] = a.strips; out[2] = a.rows_per_strip;
 }
 extern "C" int skinny(long long N) { return fq::skinny_holds(N); }
@@ -57,7 +57,7 @@ def rules(tmp_path_factory):
 @pytest.mark.parametrize("M", [1, 2, 16, 64, 65, 500, 8192, 131072, 2**31 - 1])
 def test_absmax_grid_covers_the_matrix_and_fits_the_candidates(rules, vec, K, M):
     out = (ctypes.c_int * 3)()
-    rules.absmax(ctypes.c_longlong(M), ctypes.c_longlong(K), vec, out)
+    rules.absmax(ctypes.c_longlong(M), ctypes.c_longlong(K), ctypes.c_longlong(-(-K // vec) * vec), vec, out)
     blocks, strips, rows = out
     rules.capacity.restype = ctypes.c_longlong
     capacity = rules.capacity(ctypes.c_longlong(K))
@@ -67,6 +67,19 @@ def test_absmax_grid_covers_the_matrix_and_fits_the_candidates(rules, vec, K, M)
     assert blocks * strips <= 1024 or strips == 1
     # a tall matrix gets the workgroups that its height allows, however narrow it is
     assert blocks * strips >= min(256, blocks * ((M + 63) // 64)) or blocks > 1024
+
+
+def test_absmax_strips_follow_the_row_stride(rules):
+    """Strips avoid even numbers of rounds on a stride of whole 4 KiB, whatever part of the stride the columns take."""
+    def rows(M, K, ld, vec):
+        out = (ctypes.c_int * 3)()
+        rules.absmax(*(ctypes.c_longlong(v) for v in (M, K, ld)), vec, out)
+        return out[2]
+    for vec in (4, 8):
+        for M in (2048, 4096, 8192, 16384):
+            assert rows(M, 4090, 4096, vec) == rows(M, 4096, 4096, vec) == rows(M, 4096, 8192, vec)
+            assert rows(M, 4096, 4096 + vec, vec) == rows(M, 4090, 4090 + 6 + vec, vec)
+    assert rows(8192, 4096, 4096, 4) == 288 and rows(8192, 4096, 4112, 4) == 256
 
 
 @pytest.mark.parametrize("a,na,b,nb,want", [(1000, 16, 1000, 16, 1), (1000, 16, 1015, 1, 1), (1000, 16, 1016, 1, 0), (1000, 16, 999, 1, 0),
