@@ -70,16 +70,21 @@ def test_absmax_grid_covers_the_matrix_and_fits_the_candidates(rules, vec, K, M)
 
 
 def test_absmax_strips_follow_the_row_stride(rules):
-    """Strips avoid even numbers of rounds on a stride of whole 4 KiB, whatever part of the stride the columns take."""
+    """Columns that fill a stride of whole 8 KiB up to its padding get the strips of that width; a part of a wider stride, and few
+    rows, those of their own width."""
     def rows(M, K, ld, vec):
         out = (ctypes.c_int * 3)()
         rules.absmax(*(ctypes.c_longlong(v) for v in (M, K, ld)), vec, out)
         return out[2]
     for vec in (4, 8):
         for M in (2048, 4096, 8192, 16384):
-            assert rows(M, 4090, 4096, vec) == rows(M, 4096, 4096, vec) == rows(M, 4096, 8192, vec)
-            assert rows(M, 4096, 4096 + vec, vec) == rows(M, 4090, 4090 + 6 + vec, vec)
-    assert rows(8192, 4096, 4096, 4) == 288 and rows(8192, 4096, 4112, 4) == 256
+            for K in (4000, 4088, 4090):
+                assert rows(M, K, 4096, vec) == rows(M, 4096, 4096, vec)
+            for K in (2500, 3000, 3600):
+                assert rows(M, K, 4096, vec) == rows(M, K, 4100, vec)
+            assert rows(M, 4096, 4112, vec) == rows(M, 4096, 8192, vec) == rows(M, 4096, 4096, vec)
+        assert rows(2047, 8184, 8192, vec) == rows(2047, 8184, 8200, vec)
+    assert rows(8192, 4088, 4096, 4) == 288 and rows(8192, 4088, 4112, 4) == 256
 
 
 @pytest.mark.parametrize("a,na,b,nb,want", [(1000, 16, 1000, 16, 1), (1000, 16, 1015, 1, 1), (1000, 16, 1016, 1, 0), (1000, 16, 999, 1, 0),
