@@ -52,3 +52,12 @@ def test_gathered_groups_of_wide_layers(dtype, M, K, static, bits):
         src[base + 1], src[base + 2] = base + 2, base + 1
     src[128 + 13], rep[256 + 3], rep[256 + 12] = -1, 0, 300
     _check(X, dtype, src, rep, bits, 3.0 if static else None)
+
+
+# fp32: two rows left over, alone and after a round of four, by one set of threads for the head and by several
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("at", [0, 1, -2, -1])
+@pytest.mark.parametrize("M,K", [(2, 4096), (6, 4096), (10, 5001), (12, 2048), (24, 1024), (6, 8200)])
+def test_two_rows_left_over(M, K, at, bits):
+    X, src, rep = _layer(M, K, (at % M, K // 3 + 1))
+    _check(X, "f32", src, rep, bits, None)
