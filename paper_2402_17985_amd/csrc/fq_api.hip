@@ -533,7 +533,7 @@ int fq_linear_bias(const void* X, int x_dtype, int M, int K, int ldx, const int3
         const size_t x_bytes = ((size_t)(M - 1) * ldx + K) * elem_size(x_dtype);
         const bool y_apart = !overlap(Y, y_bytes, X, x_bytes) && !overlap(Y, y_bytes, src_idx, map_bytes) &&
                              !overlap(Y, y_bytes, rep, map_bytes) && !(absmax_in && overlap(Y, y_bytes, absmax_in, sizeof(float)));
-        if (y_apart && linear_few_fits(M, N, K, Kpad, bits, x_dtype))
+        if (y_apart && linear_few_fits(M, N, K, Kpad, bits, x_dtype, absmax_in == nullptr))
             return launch_linear_few(X, x_dtype, M, K, ldx, src_idx, rep, Kpad, bits, absmax_in, Wq, N, s_w, bias, Y, y_dtype, ldy, st);
         if (y_apart && linear_decode_fits(M, N, K, Kpad, bits))
             return launch_linear_decode(X, x_dtype, K, src_idx, rep, Kpad, bits, absmax_in, Wq, N, s_w, bias, Y, y_dtype, ldy, st);

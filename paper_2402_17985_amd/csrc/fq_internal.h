@@ -104,7 +104,7 @@ int launch_linear_decode(const void* X, int x_dtype, int K, const int32_t* src, 
                          int ldy, hipStream_t stream);
 
 // ... and for a few rows
-bool linear_few_fits(int M, int N, int K, int Kpad, int bits, int x_dtype);
+bool linear_few_fits(int M, int N, int K, int Kpad, int bits, int x_dtype, bool dynamic);
 int launch_linear_few(const void* X, int x_dtype, int M, int K, int ld, const int32_t* src, const int32_t* rep, int Kpad, int bits,
                       const float* absmax_in, const void* W, int N, const float* s_w, const float* bias, void* Y, int y_dtype,
                       int ldy, hipStream_t stream);

@@ -8,8 +8,8 @@
 // workgroups (two per CU) forms the absmax (dynamic scale), the multipliers and the quantized row itself, into LDS,
 // while the first weights are on their way; then it walks the 16-column tiles w, w + gridDim, ... as gemm_skinny_kernel
 // does, with the X operand out of LDS.
-// Us, this kernel / the two: INT8 20480 x 5120 39.3 / 43.5; E3M2 4096 x 4096 10.9 / 13.5; 512 x 512 11.2 / 13.3.  It serves the narrow
-// and the very wide layers; those between, and all of two to sixteen rows, go to linear_few_kernel (few_plan says which, and why).
+// Us, this kernel / the two: INT8 20480 x 5120 39.3 / 43.5; E3M2 4096 x 4096 10.9 / 13.5; 512 x 512 11.2 / 13.3.  It serves one row where
+// few_takes_one_row leaves it: short or narrow layers, INT8 layers of very many columns, ragged lengths of few columns.
 #include <algorithm>
 #include <atomic>
 

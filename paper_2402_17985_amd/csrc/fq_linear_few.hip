@@ -544,11 +544,11 @@ template <int DT> int few_kernel_for(int bits, int fn, few_kernel_t* kern)
 
 }  // namespace
 
-bool linear_few_fits(int M, int N, int K, int Kpad, int bits, int x_dtype)
+bool linear_few_fits(int M, int N, int K, int Kpad, int bits, int x_dtype, bool dynamic)
 {
     if (bits == FQ_BITS_I4_E3M2 && !quantizer_takes_e3m2(K, Kpad)) return false;
     FewPlan plan;
-    return few_plan(M, N, K, 0, Kpad, bits, elem_size(x_dtype), compute_units(), &plan);
+    return few_plan(M, N, K, 0, Kpad, bits, elem_size(x_dtype), dynamic, compute_units(), &plan);
 }
 
 int launch_linear_few(const void* X, int x_dtype, int M, int K, int ld, const int32_t* src, const int32_t* rep, int Kpad, int bits,
@@ -556,7 +556,7 @@ int launch_linear_few(const void* X, int x_dtype, int M, int K, int ld, const in
                       int ldy, hipStream_t stream)
 {
     FewPlan plan;
-    if (!few_plan(M, N, K, ld, Kpad, bits, elem_size(x_dtype), compute_units(), &plan)) return fail(FQ_ERR_RANGE, "layer not for the kernel for few rows");
+    if (!few_plan(M, N, K, ld, Kpad, bits, elem_size(x_dtype), absmax_in == nullptr, compute_units(), &plan)) return fail(FQ_ERR_RANGE, "layer not for the kernel for few rows");
     few_kernel_t kern = nullptr;
     const int rc = x_dtype == FQ_F32 ? few_kernel_for<FQ_F32>(bits, plan.fn, &kern)
                  : x_dtype == FQ_F16 ? few_kernel_for<FQ_F16>(bits, plan.fn, &kern) : few_kernel_for<FQ_BF16>(bits, plan.fn, &kern);

@@ -107,26 +107,60 @@ struct FewPlan {
     size_t lds;
 };
 
+// One row.  The other choice is linear_decode_kernel or, for 4-bit weights beyond 16384 columns, the separate kernels.  linear_decode_kernel's
+// preparation is shorter; from more than 16 columns per CU on (`wide`) it has several workgroups per CU, which repeat it, and while the
+// second ones are few (up to `full`) the two kernels are near each other.  Us, bf16, dynamic scale where it says so, the other / this:
+//   4-bit beyond 64 columns per CU   any K: nibbles 1 x 257 x 24576 12.9 / 9.7, 1803 x 24576 17.4 / 12.7, 4096 x 32000 20.8 / 18.1; E3M2 1024 x 24576 12.9 /
+//                10.7, 5001 x 50000 7 % less; nibbles 4096 x 50000 (four rounds, three quarters full) 26.6 / 27.6, 4096 x 65536 32.0 / 31.3, 4096 x
+//                100000 8 % more
+//   whole K      INT8 2048 x 4096 7.3 / 7.4, 4096 x 1024 9.2 / 8.7, 2048 x 4112 8.4 / 7.2; 4096 x 36000 4 % less, 4096 x 40000 11 % more, 5120 x 50000 56.0 /
+//                58.7, 7168 x 65536 3 % more, 3072 x 65536 7 % less, 8192 x 65536 102.2 / 101.8; nibbles 1024 x 4112 6.4 / 6.6, 1024 x 4300 6.6 / 6.5,
+//                2048 x 4112 7.6 / 7.1; E3M2 4096 x 1024 9.1 / 9.2, 8192 x 1024 10.2 / 8.1, 1024 x 6000 7.0 / 7.0, 2048 x 4112 7.3 / 7.8, 2048 x 12288 9.5 /
+//                8.9.  fp32: nibbles 1024 x 4300 6.0 / 6.6, 1024 x 12288 3-5 % less, 5120 x 2000 7.4 / 7.7, 8192 x 2000 14 % less; E3M2 2048 x 12288 static 4 %
+//                more, 3072 x 4112 6.9 / 7.5, 4096 x 4300 4 % less
+//   ragged K     (the last group is gathered, here by every CU too) dynamic: INT8 2507 x 4100 9.3 / 10.2, 2507 x 4300 10.3 / 10.1, 4090 x 4100 11.0 / 10.4, 6503 x
+//                13000 equal, x 16384 26.9 / 28.2, 4090 x 24576 equal, x 32000 7 % more, fp32 less in all of these; nibbles 2507 x 4608 9.8 / 10.2, 2507 x
+//                10000 equal, 3001 x 4608 10.6 / 10.5, 6503 x 4100 12.1 / 12.9, 8190 x 4100 16.1 / 13.0, fp32 3001 x 11008 10.7 / 11.3, 4503 x 4300 5 % less.
+//                Static: INT8 2005 x 4100 8.1 / 7.7, nibbles 2005 x 5120 8.3 / 7.7, fp32 2005 x 8192 7.4 / 7.6, 2005 x 11008 6 % less, 2507 x 4100 6.9 / 7.7
+inline bool few_takes_one_row(int N, int K, int bits, int x_bytes, bool dynamic, int cus)
+{
+    const long long n = N, per_cu = cus;
+    const bool int8 = bits == 8, e3m2 = bits != 8 && bits != 4, fp32 = x_bytes == 4;
+    const bool wide = n > 16 * per_cu, full = 2 * n > 33 * per_cu;
+    if (!int8 && n > 64 * per_cu) {
+        if (e3m2 || K < 2048) return true;
+        return n <= 320 * per_cu && !(n > 192 * per_cu && n <= 224 * per_cu && K >= 3500);
+    }
+    if (K % 16 == 0) {
+        if (e3m2) return K >= 8192 || (fp32 ? K >= 3072 && full : K >= 3072 ? wide : K >= 2048 && full);
+        if (int8 && n > 144 * per_cu && K > 3328 && K < 7680) return false;
+        if (!wide) return K >= (fp32 && !int8 ? 6144 : 4096);
+        if (fp32 && !int8) return K >= 2560 || (K >= 1536 ? full : n > 32 * per_cu);
+        return full || K >= 1536;
+    }
+    if (!wide || K < 2000 || e3m2) return false;
+    if (int8) {
+        if (!dynamic || fp32) return !dynamic || K >= 3200 || full;
+        const bool many = n > 112 * per_cu ? K >= 2400 : n > 54 * per_cu && n <= 64 * per_cu && K >= 4000 && K < 7400;
+        return !many && (K >= 3200 || full);
+    }
+    if (!dynamic) return !fp32 || K >= 3500 || (K >= 2300 ? full : n > 40 * per_cu);
+    if (fp32) return K >= 4000 && full;
+    return K >= 3000 ? full || K >= 7400 : n > 32 * per_cu;
+}
+
 // false: the layer is not for this kernel.  It takes up to 16 rows of up to 512 whole groups of 16 channels whose quantized form
 // fits LDS, where a thread's registers hold its rows (2-byte types: 16 rows up to K = 4096, 8 up to 8192).
 //   - E3M2 up to M K = 16384: its values are packed for LDS row by row.  Us, separate / this: 4 x 4096 x 4096 11.5 / 10.0, 8 x
 //     2048 x 4096 10.6 / 9.6, but 8 x 4096 x 256 10.8 / 11.2, 16 x 4096 x 4096 12.6 / 15.5, 8 x 5120 x 4096 13.5 / 16.1.
-//   - One row, where the other choice is linear_decode_kernel: its preparation is shorter, with several workgroups per CU from more
-//     than 16 columns per CU on it repeats it.  INT8 2048 x 256 6.3 / 7.1, 2048 x 4096 7.3 / 7.4, 4096 x 256 9.4 / 8.2, 2048 x 11008 10.9 /
-//     8.4; nibbles 2048 x 4096 6.7 / 7.3, 4096 x 1024 9.2 / 8.7, 2048 x 11008 9.1 / 7.4; E3M2 4096 x 1024 9.1 / 9.2, 8192 x 1024 10.2 / 8.1,
-//     1024 x 5120 6.5 / 7.6, 2048 x 11008 8.8 / 8.4.
-//     With a ragged last group (K no multiple of 16, which is gathered) 257 x 11008 8.2 / 8.5, 2005 x 11008 10.0 / 8.6, nibbles 4100 x
-//     256 8.9 / 10.0, 4100 x 11008 13.6 / 12.5; E3M2 2005 x 11008 7.9 / 8.7.
-inline bool few_plan(int M, int N, int K, int ld, int Kpad, int bits, int x_bytes, int cus, FewPlan* plan)
+//   - One row: few_takes_one_row.
+inline bool few_plan(int M, int N, int K, int ld, int Kpad, int bits, int x_bytes, bool dynamic, int cus, FewPlan* plan)
 {
     const int NH = K >> 4;
     const bool e3m2 = bits != 8 && bits != 4;
     if (M < 1 || M > FEW_ROWS || NH < 1 || NH > 64 * FEW_PREP_WAVES || Kpad < NH * 16 || Kpad >= 65536) return false;
     if (e3m2 && (long long)M * K > 16384) return false;
-    if (M == 1) {
-        const bool wide = N > 16 * cus;
-        if (K % 16 != 0 ? !wide || K < 2000 || e3m2 : e3m2 ? K < 8192 && !(wide && K >= 2048) : !wide && K < 4096) return false;
-    }
+    if (M == 1 && !few_takes_one_row(N, K, bits, x_bytes, dynamic, cus)) return false;
     const int head = (NH + 63) / 64 * 64, slots = std::max(1, std::min(64 * FEW_PREP_WAVES / head, M));
     if ((M + slots - 1) / slots > few_rows_held(x_bytes)) return false;
     // as few rounds as 64 columns per workgroup allow, all of the same width

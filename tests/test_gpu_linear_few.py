@@ -109,3 +109,16 @@ def test_output_in_the_memory_of_an_input(where, bits):
     Y = {"X": X, "second row of X": room[K:K + M * N].view(M, N) if N == K else None, "map": layer.src.view(torch.bfloat16)[:M * N].view(M, N) if N < K else None}[where]
     layer.forward(X, Y)
     assert torch.equal(Y.view(torch.int16), want.view(torch.int16))
+
+
+# One row of 4-bit values beyond 64 columns per compute unit, whatever its length: short, ragged, with a partial last round of columns
+@pytest.mark.parametrize("bits", [4, 6])
+@pytest.mark.parametrize("scale", ["static", "dynamic"])
+@pytest.mark.parametrize("dtype,K,N", [("bf16", 16, 16400), ("f32", 31, 17001), ("f16", 257, 24576), ("bf16", 1007, 33001), ("f32", 2005, 20480), ("bf16", 1024, 16385)])
+def test_one_row_of_many_columns(dtype, K, N, scale, bits):
+    rng = np.random.default_rng(K)
+    X, W, T = _x(rng, 1, K, dtype), _w(rng, N, K), 4.0
+    src, rep, _, _ = fq.fq_flatten_plan(X.float().abs().amax(dim=0).cpu().numpy(), T, 128 if bits == 6 else 32)
+    static = scalar(T) if scale == "static" else None
+    _compare(X, src, rep, W, bits, static, torch.bfloat16, None)
+    _compare(X, src, rep, W, bits, static, torch.float32, torch.from_numpy(rng.standard_normal(N, dtype=np.float32)).to(DEV), pad=3)

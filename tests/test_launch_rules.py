@@ -24,10 +24,14 @@ extern "C" void few_tiles(long long M, long long N, int rowbytes, int bits, long
     out[0] = (int)c.kernel; out[1] = c.bm; out[2] = c.bn;
 }
 extern "C" int direct(int M, int R, int cus, int resident) { return fq::direct_workgroups(M, R, cus, resident); }
+extern "C" int few_row(int N, int K, int bits, int x_bytes, int dynamic, int cus)
+{
+    return fq::few_takes_one_row(N, K, bits, x_bytes, dynamic, cus);
+}
 extern "C" int few(int M, int N, int K, int Kpad, int bits, int x_bytes, int cus, long long* out)
 {
     fq::FewPlan p;
-    if (!fq::few_plan(M, N, K, K, Kpad, bits, x_bytes, cus, &p)) return 0;
+    if (!fq::few_plan(M, N, K, K, Kpad, bits, x_bytes, true, cus, &p)) return 0;
     out[0] = p.sh.prep_waves; out[1] = p.sh.slots; out[2] = p.sh.cols; out[3] = p.fn; out[4] = p.threads; out[5] = p.grid; out[6] = p.lds;
     return 1;
 }
@@ -187,3 +191,22 @@ def test_few_rows_plan(rules, bits, x_bytes, cus):
                     assert 0 < grid <= cus and (grid == cus or (grid - 1) * cols < N <= grid * cols)
                     assert lds <= 160 * 1024
     assert taken > 0
+
+
+# One row: both sides of the lines where the kernel of the whole layer begins and ends, each where it was measured
+@pytest.mark.parametrize("bits,x_bytes,scales,K,N,want", [
+    (8, 2, "sd", 2048, 4096, 0), (8, 2, "sd", 4096, 1024, 1), (8, 2, "sd", 2048, 4112, 1), (8, 2, "sd", 4096, 36000, 1), (8, 2, "sd", 4096, 40000, 0),
+    (8, 2, "sd", 5120, 50000, 0), (8, 2, "sd", 3072, 65536, 1), (8, 2, "sd", 8192, 65536, 1), (4, 2, "sd", 1024, 4112, 0), (4, 2, "sd", 1024, 4300, 1),
+    (4, 2, "sd", 2048, 4112, 1), (4, 2, "sd", 4096, 32000, 1), (4, 2, "sd", 4096, 50000, 0), (4, 2, "sd", 4096, 65536, 1), (4, 2, "sd", 4096, 100000, 0),
+    (6, 2, "sd", 4096, 1024, 0), (6, 2, "sd", 8192, 1024, 1), (6, 2, "sd", 2048, 4112, 0), (6, 2, "sd", 2048, 12288, 1), (6, 2, "sd", 1024, 6000, 0),
+    (6, 2, "sd", 1024, 16384, 0), (6, 2, "sd", 1024, 16385, 1), (6, 2, "sd", 1007, 24576, 1), (4, 4, "sd", 1024, 4300, 0), (4, 4, "sd", 1024, 12288, 1),
+    (4, 4, "sd", 5120, 2000, 0), (4, 4, "sd", 8192, 2000, 1), (6, 4, "sd", 2048, 12288, 0), (6, 4, "sd", 3072, 4112, 0), (6, 4, "sd", 4096, 4300, 1),
+    (8, 2, "d", 2507, 4100, 0), (8, 2, "d", 2507, 4300, 1), (8, 2, "d", 4090, 4100, 1), (8, 2, "d", 6503, 13000, 1), (8, 2, "d", 6503, 16384, 0),
+    (8, 2, "d", 4090, 24576, 1), (8, 2, "d", 4090, 32000, 0), (8, 4, "d", 4090, 32000, 1), (8, 2, "s", 2005, 4100, 1), (8, 2, "s", 6503, 16384, 1),
+    (8, 2, "sd", 1803, 8192, 0), (4, 2, "d", 2507, 4608, 0), (4, 2, "d", 2507, 10000, 1), (4, 2, "d", 3001, 4608, 1), (4, 2, "d", 6503, 4100, 0),
+    (4, 2, "d", 8190, 4100, 1), (4, 2, "s", 2005, 5120, 1), (4, 4, "d", 3001, 11008, 0), (4, 4, "d", 4503, 4300, 1), (4, 4, "s", 2005, 8192, 0),
+    (4, 4, "s", 2005, 11008, 1), (4, 4, "s", 2507, 4100, 0), (4, 2, "sd", 257, 16384, 0), (4, 2, "sd", 257, 16385, 1), (6, 2, "sd", 2005, 16384, 0),
+])
+def test_one_row_lines(rules, bits, x_bytes, scales, K, N, want):
+    for scale in scales:
+        assert rules.few_row(N, K, bits, x_bytes, int(scale == "d"), 256) == want
