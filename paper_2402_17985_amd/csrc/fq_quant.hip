@@ -336,16 +336,8 @@ __global__ __launch_bounds__(1024) void scale_kernel(const float* __restrict__ c
     // slot's quantized value then equals slot j's and can be copied instead of recomputed.
     const bool copyable = inside && ((unsigned)s >= (unsigned)K || (own_src == s && n > 0 && own_n == n));
     const unsigned long long balc = __ballot(copyable);
-    // ... and 2 when, in addition, all 16 slots repeat the same channel (the long runs of a large
-    // outlier's copies): one value then fills the group
-    const int s0 = __shfl(s, (tid & 63) & ~15, 64);
-    const unsigned long long balu = __ballot(s == s0 && (unsigned)s < (unsigned)K);
     uint8_t* cflag = gflag + ((Kpad >> 4) + 1);
-    if (p < Kpad && (tid & 15) == 0) {
-        const bool all_copy = ((balc >> (tid & 48)) & 0xffffull) == 0xffffull;
-        const bool all_same = ((balu >> (tid & 48)) & 0xffffull) == 0xffffull;
-        cflag[p >> 4] = all_copy ? (all_same ? 2 : 1) : 0;
-    }
+    if (p < Kpad && (tid & 15) == 0) cflag[p >> 4] = (((balc >> (tid & 48)) & 0xffffull) == 0xffffull) ? 1 : 0;
 }
 
 // ---------------------------------------------------------------------------------------------
