@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("accumulate", [False, True])
 @pytest.mark.parametrize("dtype,M,K", [
     (torch.float32, 1, 4), (torch.bfloat16, 3, 520), (torch.float16, 31, 64), (torch.bfloat16, 33, 1000), (torch.float32, 65, 257),
-    (torch.bfloat16, 4099, 4104), (torch.float32, 2061, 4100), (torch.float16, 70000, 24),      # > 32 MiB: the first two stream
+    (torch.bfloat16, 4099, 4104), (torch.float32, 2061, 4100), (torch.float16, 70000, 24),
+    (torch.bfloat16, 12301, 4104), (torch.float32, 6203, 4101), (torch.float16, 12311, 4103),     # > 96 MiB: streamed
 ])
 def test_channel_maxima(dtype, M, K, accumulate):
     g = torch.Generator(device=DEV).manual_seed(M + K)
@@ -25,6 +26,24 @@ def test_channel_maxima(dtype, M, K, accumulate):
     fq.fq_channel_absmax(X, out, accumulate=accumulate)
     want = X.float().abs().amax(dim=0)
     assert torch.equal(out, torch.maximum(want, start) if accumulate else want)
+
+
+@pytest.mark.parametrize("dtype,M,K", [(torch.bfloat16, 14501, 8200), (torch.float16, 14501, 8203), (torch.float32, 7303, 8201)])    # > 224 MiB: streamed
+@pytest.mark.parametrize("at", ["first", "last"])
+@pytest.mark.parametrize("what", ["activation", "weights"])
+def test_scale_of_a_streamed_matrix(dtype, M, K, at, what):
+    Kpad = (K + 127) // 128 * 128
+    src, rep = np.full(Kpad, -1, np.int32), np.zeros(Kpad, np.int32)
+    src[:K], rep[:K] = np.arange(K), 1
+    X = torch.rand((M, (K + 7) // 8 * 8), device=DEV).to(dtype)[:, :K]
+    X[(0, 0) if at == "first" else (M - 1, K - 1)] = -9.25
+    out = torch.empty((M, Kpad), dtype=torch.int8, device=DEV)
+    s = torch.zeros(1, device=DEV)
+    if what == "activation":
+        fq.fq_flatten_quant_act(X, dev_i32(src), dev_i32(rep), 8, out, s, bytes_ws(fq.fq_act_workspace_bytes(K, Kpad)))
+    else:
+        fq.fq_flatten_weights(X, dev_i32(src), 8, out, s, bytes_ws(fq.fq_weights_workspace_bytes(K, Kpad)))
+    assert np.float32(s.item()) == np.float32(9.25 / 127.0)
 
 
 @pytest.mark.parametrize("M,K", [(33, 2048), (257, 11008), (4100, 1000), (14500, 8200)])       # the last beyond 224 MiB
