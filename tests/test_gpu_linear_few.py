@@ -1,5 +1,7 @@
 """The one-kernel form of the layer for a few rows against the separate kernels (a forced GEMM variant selects them; the
 other tests hold them to the oracle), bit for bit."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -7,6 +9,7 @@ import torch
 import paper_2402_17985_amd as fq
 from tests.gpu_util import DEV, scalar
 from tests.test_gpu_linear_decode import _compare, _x
+from tests.test_launch_rules import rules  # noqa: F401  (the launch rules, compiled for the host)
 
 pytestmark = pytest.mark.gpu
 
@@ -32,6 +35,39 @@ def test_planned_maps(dtype, M, K, N, scale, bits):
     _compare(X, src, rep, W, bits, static, torch.bfloat16, None)
     _compare(X, src, rep, W, bits, static, torch.float32, torch.from_numpy(rng.standard_normal(N, dtype=np.float32)).to(DEV), pad=3)
     _compare(X, src, rep, W, bits, static, torch.int32, None)
+
+
+def _plan(rules, M, N, K, Kpad, bits, dtype, dynamic):
+    """(sets of quantizing waves, rows that a thread holds, fragments of 16 columns) of the kernel that the call takes; None: another."""
+    out = (ctypes.c_longlong * 7)()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if not rules.few_scaled(M, N, K, Kpad, bits, 4 if dtype == "f32" else 2, int(dynamic), cus, out):
+        return None
+    return out[1], -(-M // out[1]), out[3]
+
+
+# The shapes above that this kernel leaves to the separate ones (E3M2 beyond 16384 elements, one row by the rule for one row) are
+# comparisons of those with themselves; here every one is taken, and by the kernel that is named: one set of quantizing waves and
+# several, as many rows per thread as its registers hold, one to four fragments, each storage and type.
+@pytest.mark.parametrize("scale", ["static", "dynamic"])
+@pytest.mark.parametrize("bits,dtype,M,K,N,want", [
+    (b, "bf16", 2, 4096, 12800, (2, 1, 4)) for b in (8, 4, 6)] + [
+    (b, "bf16", 2, 8192, 4100, (1, 2, 2)) for b in (8, 4, 6)] + [
+    (b, "f32", 4, 4096, 8300, (2, 2, 3)) for b in (8, 4, 6)] + [
+    (b, "f16", 16, 1024, 12300, (8, 2, 4)) for b in (8, 4, 6)] + [
+    (b, "bf16", 16, 4096, 11008, (2, 8, 3)) for b in (8, 4)] + [
+    (b, "bf16", 16, 4096, 40, (2, 8, 1)) for b in (8, 4)] + [
+    (b, "f16", 8, 8192, 8000, (1, 8, 2)) for b in (8, 4)] + [
+    (b, "f32", 16, 2048, 12800, (4, 4, 4)) for b in (8, 4)] + [
+    (b, "f32", 4, 8192, 8300, (1, 4, 3)) for b in (8, 4)] + [
+    (6, "f32", 2, 8192, 12300, (1, 2, 4)), (6, "bf16", 8, 2048, 8300, (4, 2, 3)), (6, "bf16", 1, 8192, 1000, (1, 1, 1)), (6, "f32", 16, 1008, 5000, (8, 2, 2))])
+def test_kernels_that_calls_take(rules, bits, dtype, M, K, N, want, scale):  # noqa: F811
+    rng = np.random.default_rng(K + M)
+    X, W, T = _x(rng, M, K, dtype), _w(rng, N, K), 4.0
+    src, rep, _, _ = fq.fq_flatten_plan(X.float().abs().amax(dim=0).cpu().numpy(), T, 128 if bits == 6 else 32)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert _plan(rules, M, N, K, len(src), bits, dtype, scale == "dynamic") == want
+    _compare(X, src, rep, W, bits, scalar(T) if scale == "static" else None, torch.bfloat16, None)
 
 
 @pytest.mark.parametrize("bits", [8, 4, 6])
@@ -83,14 +119,14 @@ def test_fewer_slots_than_channels(static):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
-@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("bits", [8, 4, 6])
 @pytest.mark.parametrize("static", [False, True])
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
 def test_what_is_not_finite(value, static, bits, dtype):
     rng = np.random.default_rng(3)
     M, K, N = 5, 500, 100
     X, W = _x(rng, M, K, dtype), _w(rng, N, K)
-    src, rep, _, _ = fq.fq_flatten_plan(X.float().abs().amax(dim=0).cpu().numpy(), 4.0, 32)
+    src, rep, _, _ = fq.fq_flatten_plan(X.float().abs().amax(dim=0).cpu().numpy(), 4.0, 128 if bits == 6 else 32)
     X[2, 7] = value
     _compare(X, src, rep, W, bits, scalar(3.0) if static else None, torch.int32, None)
 

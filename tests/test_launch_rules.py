@@ -28,12 +28,16 @@ extern "C" int few_row(int N, int K, int bits, int x_bytes, int dynamic, int cus
 {
     return fq::few_takes_one_row(N, K, bits, x_bytes, dynamic, cus);
 }
-extern "C" int few(int M, int N, int K, int Kpad, int bits, int x_bytes, int cus, long long* out)
+extern "C" int few_scaled(int M, int N, int K, int Kpad, int bits, int x_bytes, int dynamic, int cus, long long* out)
 {
     fq::FewPlan p;
-    if (!fq::few_plan(M, N, K, K, Kpad, bits, x_bytes, true, cus, &p)) return 0;
+    if (!fq::few_plan(M, N, K, K, Kpad, bits, x_bytes, dynamic, cus, &p)) return 0;
     out[0] = p.sh.prep_waves; out[1] = p.sh.slots; out[2] = p.sh.cols; out[3] = p.fn; out[4] = p.threads; out[5] = p.grid; out[6] = p.lds;
     return 1;
+}
+extern "C" int few(int M, int N, int K, int Kpad, int bits, int x_bytes, int cus, long long* out)
+{
+    return few_scaled(M, N, K, Kpad, bits, x_bytes, 1, cus, out);
 }
 extern "C" int overlap(unsigned long long a, unsigned long long na, unsigned long long b, unsigned long long nb)
 {
