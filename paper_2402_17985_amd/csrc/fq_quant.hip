@@ -127,16 +127,8 @@ __global__ __launch_bounds__(256) void colabsmax_kernel(const void* __restrict__
 }
 
 // ---------------------------------------------------------------------------------------------
-// absmax of the flattened tensor, one candidate per workgroup
+// the map, prepared for the quantizer of few rows
 // ---------------------------------------------------------------------------------------------
-// a' = max_p fl32(c_p / n_p) with c_p = max_i |X[i, src p]|.  The rounded quotient is monotonic in c, so the maximum
-// over rows may be taken after it: a workgroup that has seen the columns [c0, c0 + 64 VEC) of some rows contributes
-// max_j fl32(c_j / n_j), n_j = the smallest copy count of the valid slots that read channel j (channels that no slot reads
-// contribute nothing).  Four waves stream X; four more scan the map for n_j meanwhile.  The candidate goes to
-// cand[workgroup], and whoever needs a' takes the maximum of the candidates.
-// What this replaces: a kernel that cleared K channel maxima, atomic maxima on them, and a gather of all channel maxima
-// over the map in every workgroup of the kernel that forms the multipliers.
-// ALL: a' = max |X| over all channels, whatever the map (weights, peel split).
 // What flatten_quant_direct_kernel needs of the map, worked out once instead of in each of its workgroups: copy counts of plain
 // head groups as bytes (MANY: that many or more; 0 in other groups), sources of the tail's slots as 16-bit channel numbers (KQ:
 // the slot holds 0), and per tail group whether each slot holds 0 whatever the input or repeats a channel of a plain group with
@@ -185,6 +177,17 @@ __device__ void prepare_map(const int32_t* __restrict__ src, const int32_t* __re
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// absmax of the flattened tensor, one candidate per workgroup
+// ---------------------------------------------------------------------------------------------
+// a' = max_p fl32(c_p / n_p) with c_p = max_i |X[i, src p]|.  The rounded quotient is monotonic in c, so the maximum
+// over rows may be taken after it: a workgroup that has seen the columns [c0, c0 + 64 VEC) of some rows contributes
+// max_j fl32(c_j / n_j), n_j = the smallest copy count of the valid slots that read channel j (channels that no slot reads
+// contribute nothing).  Four waves stream X; four more scan the map for n_j meanwhile.  The candidate goes to
+// cand[workgroup], and whoever needs a' takes the maximum of the candidates.
+// What this replaces: a kernel that cleared K channel maxima, atomic maxima on them, and a gather of all channel maxima
+// over the map in every workgroup of the kernel that forms the multipliers.
+// ALL: a' = max |X| over all channels, whatever the map (weights, peel split).
 // map: when not null, the grid's first row of workgroups prepares the map there and the strips follow.
 template <int DT, bool ALL, bool NT>
 __global__ __launch_bounds__(ALL ? 256 : 512) void tensor_absmax_kernel(const void* __restrict__ Xv, int M, int K, int ld,
@@ -221,7 +224,7 @@ __global__ __launch_bounds__(ALL ? 256 : 512) void tensor_absmax_kernel(const vo
             else part[wave][lane * VEC + v] = mx[v];
         }
     } else if constexpr (!ALL) {
-// eight loads in flight; Kpad is a multiple of 32, a thread's four slots are inside or outside together
+        // eight loads in flight; Kpad is a multiple of 32, a thread's four slots are inside or outside together
         for (int p = (tid - 256) * 4; p < Kpad; p += 8 * 1024) {
             v4i s[8];
 #pragma unroll
@@ -595,12 +598,12 @@ __global__ __launch_bounds__(512) void flatten_quant_rows_kernel(const void* __r
 // and has one thread per P head groups, so that a strip is one round of loads.
 //   loads      X of the first strip, the map (head and tail) and the bound or the candidates are asked for at once: what
 //              follows waits one round trip to memory for all of them.
-//   the map    from the absmax pass, which prepares it (PreparedMap: a byte per slot instead of eight, and no checks; 500 x 11008
-//              dynamic 9.6 -> 7.8 us, 2048 x 4096 10.8 -> 9.5); else thread t reads the sources and copy counts of its groups t, t + head threads, ... of the head.  A group is
-//              plain when its slots are the channels at the same indices with copies; the counts of plain groups are left
-//              in LDS, and from them follows which appended groups only repeat their values.  (Counts beyond the table are
-//              rare and divide once per slot.  Gathering their groups and copies element by element took 18.0 us for 1000 x
-//              4096 static with one channel of 300 copies and 25.6 with 2000; this 8.7 and 11.8.)
+//   the map    with a dynamic scale from the absmax pass, which prepares it (PreparedMap: a byte per slot instead of eight, and no checks;
+//              500 x 11008 9.6 -> 7.8 us, 2048 x 4096 10.8 -> 9.5); else thread t reads the sources and copy counts of its groups t,
+//              t + head threads, ... of the head.  A group is plain when its slots are the channels at the same indices with copies;
+//              the counts of plain groups are left in LDS, and from them follows which appended groups only repeat their values.
+//              (Counts beyond the table are rare and divide once per slot.  Gathering their groups and copies element by element
+//              took 18.0 us for 1000 x 4096 static with one channel of 300 copies and 25.6 with 2000; this 8.7 and 11.8.)
 //   a'         the static bound; or the maximum of the candidates that tensor_absmax_kernel left; or (few rows) taken
 //              from all of X by every workgroup, which costs M * K reads from L2 against a launch: its threads then form
 //              several slots of head threads, each with its share of the rows, so that the reads are one round trip.
@@ -624,7 +627,8 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
     typedef typename Elem<DT>::type T;
     constexpr int VEC = Elem<DT>::VEC, NV = 16 / VEC;
     constexpr int QMAX = (BITS == 8) ? 127 : 7;
-    // the tail of the map is asked for with the rest where that fits the registers (fp32 2000 x 4096 static, whose registers then spill: 13.6 -> 15.1 us)
+    // the tail of the map is asked for with the rest where that fits the registers (fp32 2000 x 4096 static to INT8: with it, and scratch, 18.3 us;
+    // without 13.1)
     constexpr bool TAIL_EARLY = DT != FQ_F32 && P == 1;
     const int nthr = blockDim.x, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = nthr >> 6;

@@ -118,10 +118,11 @@ struct FewPlan {
 //                2048 x 4112 7.6 / 7.1; E3M2 4096 x 1024 9.1 / 9.2, 8192 x 1024 10.2 / 8.1, 1024 x 6000 7.0 / 7.0, 2048 x 4112 7.3 / 7.8, 2048 x 12288 9.5 /
 //                8.9.  fp32: nibbles 1024 x 4300 6.0 / 6.6, 1024 x 12288 3-5 % less, 5120 x 2000 7.4 / 7.7, 8192 x 2000 14 % less; E3M2 2048 x 12288 static 4 %
 //                more, 3072 x 4112 6.9 / 7.5, 4096 x 4300 4 % less
-//   ragged K     (the last group is gathered, here by every CU too) dynamic: INT8 2507 x 4100 9.3 / 10.2, 2507 x 4300 10.3 / 10.1, 4090 x 4100 11.0 / 10.4, 6503 x
-//                13000 equal, x 16384 26.9 / 28.2, 4090 x 24576 equal, x 32000 7 % more, fp32 less in all of these; nibbles 2507 x 4608 9.8 / 10.2, 2507 x
-//                10000 equal, 3001 x 4608 10.6 / 10.5, 6503 x 4100 12.1 / 12.9, 8190 x 4100 16.1 / 13.0, fp32 3001 x 11008 10.7 / 11.3, 4503 x 4300 5 % less.
-//                Static: INT8 2005 x 4100 8.1 / 7.7, nibbles 2005 x 5120 8.3 / 7.7, fp32 2005 x 8192 7.4 / 7.6, 2005 x 11008 6 % less, 2507 x 4100 6.9 / 7.7
+//   ragged K     (the last group is gathered, here by every CU too) dynamic: INT8 2507 x 4100 9.3 / 10.2, 2507 x 4300 10.3 / 10.1, 4090 x 4100 11.0 /
+//                10.4, 6503 x 13000 equal, x 16384 26.9 / 28.2, 4090 x 24576 equal, x 32000 7 % more, fp32 less in all of these; nibbles 2507 x 4608
+//                9.8 / 10.2, 2507 x 10000 equal, 3001 x 4608 10.6 / 10.5, 6503 x 4100 12.1 / 12.9, 8190 x 4100 16.1 / 13.0, fp32 3001 x 11008 10.7 /
+//                11.3, 4503 x 4300 5 % less.  Static: INT8 2005 x 4100 8.1 / 7.7, nibbles 2005 x 5120 8.3 / 7.7, fp32 2005 x 8192 7.4 / 7.6, 2005 x
+//                11008 6 % less, 2507 x 4100 6.9 / 7.7
 inline bool few_takes_one_row(int N, int K, int bits, int x_bytes, bool dynamic, int cus)
 {
     const long long n = N, per_cu = cus;
@@ -152,7 +153,8 @@ inline bool few_takes_one_row(int N, int K, int bits, int x_bytes, bool dynamic,
 // false: the layer is not for this kernel.  It takes up to 16 rows of up to 512 whole groups of 16 channels whose quantized form
 // fits LDS, where a thread's registers hold its rows (2-byte types: 16 rows up to K = 4096, 8 up to 8192).
 //   - E3M2 up to M K = 16384: its values are packed for LDS row by row.  Us, separate / this: 4 x 4096 x 4096 11.5 / 10.0, 8 x
-//     2048 x 4096 10.6 / 9.6, but 8 x 4096 x 256 10.8 / 11.2, 16 x 4096 x 4096 12.6 / 15.5, 8 x 5120 x 4096 13.5 / 16.1.
+//     2048 x 4096 10.6 / 9.6, but 8 x 4096 x 256 10.8 / 11.2, 16 x 4096 x 4096 12.6 / 15.5, 8 x 5120 x 4096 13.5 / 16.1.  (Within the line, over 2
+//     to 16 rows of 512 to 8192 by 256 to 11008 columns, dynamic, 6 to 32 % less than the separate kernels everywhere.)
 //   - One row: few_takes_one_row.
 inline bool few_plan(int M, int N, int K, int ld, int Kpad, int bits, int x_bytes, bool dynamic, int cus, FewPlan* plan)
 {
@@ -192,11 +194,12 @@ inline long long candidate_capacity(long long K) { return std::max<long long>(MA
 
 // A workgroup's four waves read 32 rows per round, eight loads in flight each; two to four workgroups per CU (at most 1024
 // candidates), strips of whole rounds.  Of the three counts, and one round more, the one whose fullest CU has the fewest rounds, the
-// lowest on a tie.  Strips of an even number of rounds count for a quarter more where rows are whole 4 KiB, or where they fill a stride of
-// whole 8 KiB up to its padding: they start on the same memory channels.  (Of a wider stride taken in part that is not so: fp32 1000 x
-// 7000 of 8192 6.0 us, with odd rounds 7.5; nor does it pay below 2048 rows, whole call, 1000 x 8184 of 8192 23.4, 24.2.)  Whole quantizer call, fp32, us: 8192 x 4096 with strips of 128 rows 63.4, 256 63.6, 288
-// 58.1, 342 59.1; 4096 x 8192 256 rows 63.0, 288 60.5; bf16 8192 x 4096 256 rows 37.8, 288 34.9; maxima alone, bf16 4096 x 4088 of 4096
-// 64 rows 8.2, 32 6.8.  One workgroup per CU loses elsewhere: fp32 3000 x 5001 42.4, with two 35.7; weights 5120 x 20480 96.6, 92.4.
+// lowest on a tie.  Strips of an even number of rounds count for a quarter more where rows are whole 4 KiB, or where they fill a
+// stride of whole 8 KiB up to its padding: they start on the same memory channels.  (Of a wider stride taken in part that is not so:
+// fp32 1000 x 7000 of 8192 6.0 us, with odd rounds 7.5; nor does it pay below 2048 rows, whole call, 1000 x 8184 of 8192 23.4, 24.2.)
+// Whole quantizer call, fp32, us: 8192 x 4096 with strips of 128 rows 63.4, 256 63.6, 288 58.1, 342 59.1; 4096 x 8192 256 rows 63.0,
+// 288 60.5; bf16 8192 x 4096 256 rows 37.8, 288 34.9; maxima alone, bf16 4096 x 4088 of 4096 64 rows 8.2, 32 6.8.  One workgroup per
+// CU loses elsewhere: fp32 3000 x 5001 42.4, with two 35.7; weights 5120 x 20480 96.6, 92.4.
 constexpr int ABSMAX_ROUND = 32;
 inline AbsmaxGrid absmax_grid(long long M, long long K, long long ld, int vec, long long cus = 256)
 {
