@@ -987,8 +987,12 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
     for (int p = 0; p < P; ++p)
         if (first && t0 + p * head < NH && !((plain >> p) & 1)) slow |= 1 << p;
 
-    // phase 2: a wave takes 64 groups of a row, or (few appended groups) all groups of two to eight rows
+    // phase 2: a wave takes 64 groups of a row, or (few appended groups) all groups of two to eight rows, a batch.  The group with the
+    // channels of a ragged head is gathered in every row.  Where waves have several batches a lane keeps what it is to gather for the
+    // strip's end, and groups move on by a lane per row so that lanes differ: one gather and not one per batch.  Nibbles, fp16, 600 x
+    // 1003 static 8.9 us, so 7.6; 4680 x 1003 11.7, 10.0; dynamic 18.5, 15.9.  With one batch per wave nothing is kept (7.0 us, 7.3).
     const int tail_waves = (NT + 63) >> 6, tail_log = NT <= 8 ? 3 : NT <= 16 ? 2 : NT <= 32 ? 1 : 0;
+    const bool later = R == 4 && KQ != K && tail_waves * (R >> min(tail_log, 2)) > waves;
     for (int rs = row_begin; rs < row_end; rs += R) {
         const int nr = min(row_end - rs, R);
         // ---- phase 1: the head ----
@@ -1015,18 +1019,21 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
         //      wave whatever NT took 9000 x 300 static from 12.1 to 18.4 us) ----
         for (int k = 0; slow && k < P * nr; ++k)
             if ((slow >> (k / nr)) & 1) gather_group(t0 + (k / nr) * head, rs + k % nr);
+        int kept = -1;                                         // group to be gathered: row << 20 | group
         for (int rb = 0, w = wave;; w += waves) {
             for (; rb < nr && w >= tail_waves; w -= tail_waves) rb += 1 << tail_log;
             if (rb >= nr) break;
-            const int rr = rb + (lane >> (6 - tail_log)), gt = w * 64 + (lane & ((64 >> tail_log) - 1));
+            const int rr = rb + (lane >> (6 - tail_log)), gt = w * 64 + ((lane + (R == 4 ? rb : 0)) & ((64 >> tail_log) - 1));
             if (rr >= nr || gt >= NT) continue;
             if (!tf[gt]) {
-                gather_group(NH + gt, rs + rr);
+                if (later && kept < 0) kept = rr << 20 | gt;
+                else gather_group(NH + gt, rs + rr);
                 continue;
             }
             const v4u* tp = reinterpret_cast<const v4u*>(ts + gt * 16);
             store_group<BITS>(gather16(qs + (size_t)rr * pitch, tp[0], tp[1]), out, orow_bytes, M, rs + rr, NH + gt);
         }
+        if (kept >= 0) gather_group(NH + (kept & 0xfffff), rs + (kept >> 20));
         strip_barrier();
     }
 }

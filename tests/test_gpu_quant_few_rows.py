@@ -1,5 +1,5 @@
-"""The quantizer of a few rows with a dynamic scale, whose workgroups each take the maximum of all of X: every number of rows that is
-left over by the rounds of rows, and heads whose last group is ragged, against the CPU oracle, byte for byte."""
+"""The quantizer of few rows, whose workgroups with a dynamic scale may each take the maximum of all of X: every number of rows that is
+left over by the rounds of rows, heads whose last group is ragged, and gathered groups, against the CPU oracle, byte for byte."""
 import numpy as np
 import pytest
 
@@ -61,3 +61,24 @@ def test_gathered_groups_of_wide_layers(dtype, M, K, static, bits):
 def test_two_rows_left_over(M, K, at, bits):
     X, src, rep = _layer(M, K, (at % M, K // 3 + 1))
     _check(X, "f32", src, rep, bits, None)
+
+
+# Groups to be gathered in every row of a strip: the one with the channels of a ragged head, and copies of those.  Fewer waves than batches
+# of appended groups, as many, and more; strips of one to four rows, several per workgroup
+@pytest.mark.parametrize("bits", [8, 4, 6])
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("copies", [{2: 30}, {2: 200, 5: 240, 8: 120, -1: 40}, {2: 250, 3: 100, 9: 250, -2: 70, 4: 254, 5: 250, 6: 250, 7: 250, -1: 9}])
+@pytest.mark.parametrize("dtype,M,K", [("f16", 1500, 1003), ("bf16", 4683, 639), ("bf16", 700, 2005), ("f16", 20011, 555), ("f32", 1501, 1003), ("bf16", 1030, 31)])
+def test_gathered_groups_of_every_row(dtype, M, K, copies, static, bits):
+    rng = np.random.default_rng(M)
+    X = rng.uniform(-1.0, 1.0, (M, K)).astype(np.float32)
+    count = np.ones(K, dtype=np.int32)
+    for c, n in copies.items():
+        count[c if c < 0 else c * K // 11] = n
+    X *= count
+    X[M - 1, K - 1] = -1.25 * count[K - 1]
+    slots = np.concatenate([np.arange(K), np.repeat(np.arange(K), count - 1)]).astype(np.int32)
+    Kpad = (len(slots) + 127) // 128 * 128
+    src, rep = np.full(Kpad, -1, np.int32), np.zeros(Kpad, np.int32)
+    src[:len(slots)], rep[:len(slots)] = slots, count[slots]
+    _check(X, dtype, src, rep, bits, 1.0 if static else None)
