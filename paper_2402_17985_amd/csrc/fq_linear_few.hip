@@ -372,8 +372,11 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void linear_few_kernel(const void* 
         const uint32_t last_w = (uint32_t)((size_t)N * rowbytes - (MODE == MODE_F6 ? 8 : 16));
         RowPieces<MODE> pw[FN], px;
         op_t w[D][FN];
+        // (turns: a mask, or all ones.  Wrapped by a comparison instead, layers of every pitch took 1-5 % longer.)
+        const uint32_t turns = (uint32_t)sh.turns, from = sw + (sh.turns < 0 ? 0u : blockIdx.x * 5 & turns);
+        auto step_of = [&](int t) -> uint32_t { return (from + (uint32_t)(t * SW)) & turns; };
         auto load = [&](int d, int t) {
-            const uint32_t s = (uint32_t)(sw + t * SW);
+            const uint32_t s = step_of(t);
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
                 w[d][j].a = *reinterpret_cast<const decltype(op_t::a)*>(W + min(pw[j].a + s * stride_w, last_w));
@@ -475,7 +478,7 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void linear_few_kernel(const void* 
 #pragma unroll
             for (int j = 0; j < FN; ++j) acc[j] = sum_t{0, 0, 0, 0};
             auto compute = [&](int d, int t) {
-                const uint32_t s = (uint32_t)(sw + t * SW);
+                const uint32_t s = step_of(t);
                 op_t x;
                 x.a = *reinterpret_cast<const decltype(op_t::a)*>(xq + (px.a + s * stride_x));
                 x.b = *reinterpret_cast<const decltype(op_t::b)*>(xq + (px.b + s * stride_x));

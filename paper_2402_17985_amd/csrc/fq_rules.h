@@ -99,6 +99,7 @@ struct FewShape {
     int M, K, ld, Kpad, N;
     int prep_waves, slots;     // waves that quantize; rows dealt over so many sets of them
     int cols;                  // columns of a workgroup and round
+    int turns;                 // steps of the reduction less 1 where workgroups begin at different ones; else -1
 };
 struct FewPlan {
     FewShape sh;
@@ -175,7 +176,11 @@ inline bool few_plan(int M, int N, int K, int ld, int Kpad, int bits, int x_byte
     plan->lds = FEW_LDS_FIXED + kq + FEW_PAD + rows * (e3m2 ? (size_t)rowbytes : few_row(rowbytes)) + (bits == 8 ? 0 : rows * (kq + FEW_PAD)) +
                 32 * nt + (nt + 15) / 16 * 16 + 2 * (((size_t)Kpad / 16 + 7) / 8 * 8) + (size_t)stream * plan->fn * 1024;
     if (plan->lds > FEW_LDS) return false;
-    plan->sh = FewShape{M, K, ld, Kpad, N, prep, slots, cols};
+    // Weight rows of 4, 8 or 16 KiB: workgroups that walk them in step meet on the same memory channels, so each begins at another step (5 w
+    // modulo their number, a power of two).  INT8, us, all at step 0 / so: 1 x 8192 x 8192 20.1 / 14.3, x 16384 31.6 / 26.7, x 24576 39.9 / 37.4,
+    // x 6144 12.3 / 12.4; nibbles 1 x 8192 x 24576 23.7 / 20.8.  On rows of 6 and 7 KiB it gave nothing or cost 1-2 %.  E3M2 rows are 96 bytes apart.
+    const bool aliased = !e3m2 && rowbytes >= 4096 && (rowbytes & (rowbytes - 1)) == 0;
+    plan->sh = FewShape{M, K, ld, Kpad, N, prep, slots, cols, aliased ? steps - 1 : -1};
     plan->threads = (prep + stream) * 64;
     plan->grid = (unsigned)std::min<long long>(((long long)N + cols - 1) / cols, cus);
     return true;

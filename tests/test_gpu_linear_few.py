@@ -158,3 +158,19 @@ def test_one_row_of_many_columns(dtype, K, N, scale, bits):
     static = scalar(T) if scale == "static" else None
     _compare(X, src, rep, W, bits, static, torch.bfloat16, None)
     _compare(X, src, rep, W, bits, static, torch.float32, torch.from_numpy(rng.standard_normal(N, dtype=np.float32)).to(DEV), pad=3)
+
+
+# Weight rows of 4, 8 and 16 KiB, whose workgroups begin at different steps of the reduction, and of 12 KiB; several rounds of columns
+@pytest.mark.parametrize("scale", ["static", "dynamic"])
+@pytest.mark.parametrize("bits,dtype,M,K,Kpad,N", [
+    (8, "bf16", 1, 8192, 8192, 8192), (8, "f16", 8, 8192, 8192, 4100), (8, "bf16", 2, 4096, 4096, 16500), (8, "f32", 3, 3001, 4096, 5000),
+    (8, "bf16", 1, 8000, 12288, 24576), (4, "bf16", 1, 8192, 8192, 8192), (4, "f16", 16, 4000, 8192, 12300), (4, "bf16", 2, 8192, 16384, 20000),
+    (8, "f32", 4, 8190, 8192, 33), (8, "bf16", 2, 8192, 16384, 8200)])
+def test_rows_of_whole_4_kib(bits, dtype, M, K, Kpad, N, scale):
+    rng = np.random.default_rng(Kpad + N)
+    X, W = _x(rng, M, K, dtype), _w(rng, N, K)
+    src, rep = np.full(Kpad, -1, np.int32), np.zeros(Kpad, np.int32)
+    src[:K], rep[:K] = np.arange(K), 1
+    more = (Kpad - K) // 2                                     # a second copy of the first channels, the rest padding
+    src[K:K + more], rep[K:K + more], rep[:more] = np.arange(more), 2, 2
+    _compare(X, src, rep, W, bits, scalar(4.0) if scale == "static" else None, torch.int32, None)

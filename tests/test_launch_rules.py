@@ -35,6 +35,11 @@ extern "C" int few_scaled(int M, int N, int K, int Kpad, int bits, int x_bytes, 
     out[0] = p.sh.prep_waves; out[1] = p.sh.slots; out[2] = p.sh.cols; out[3] = p.fn; out[4] = p.threads; out[5] = p.grid; out[6] = p.lds;
     return 1;
 }
+extern "C" int few_turns(int M, int N, int K, int Kpad, int bits, int cus)
+{
+    fq::FewPlan p;
+    return fq::few_plan(M, N, K, K, Kpad, bits, 2, true, cus, &p) ? p.sh.turns : -2;
+}
 extern "C" int few(int M, int N, int K, int Kpad, int bits, int x_bytes, int cus, long long* out)
 {
     return few_scaled(M, N, K, Kpad, bits, x_bytes, 1, cus, out);
@@ -214,3 +219,14 @@ def test_few_rows_plan(rules, bits, x_bytes, cus):
 def test_one_row_lines(rules, bits, x_bytes, scales, K, N, want):
     for scale in scales:
         assert rules.few_row(N, K, bits, x_bytes, int(scale == "d"), 256) == want
+
+
+@pytest.mark.parametrize("bits", [8, 4, 6])
+def test_few_rows_begin_at_a_step_of_the_reduction(rules, bits):
+    for Kpad in range(128, 20000, 128):
+        for M in (1, 2, 8):
+            turns = rules.few_turns(M, 12288, min(Kpad, 8192), Kpad, bits, 256)
+            if turns == -2:
+                continue
+            rowbytes = Kpad if bits == 8 else Kpad // 2
+            assert turns == (rowbytes // 128 - 1 if bits != 6 and rowbytes in (4096, 8192, 16384) else -1)
