@@ -990,7 +990,8 @@ __global__ __launch_bounds__(1024) void flatten_quant_direct_kernel(const void* 
     // phase 2: a wave takes 64 groups of a row, or (few appended groups) all groups of two to eight rows, a batch.  The group with the
     // channels of a ragged head is gathered in every row.  Where waves have several batches a lane keeps what it is to gather for the
     // strip's end, and groups move on by a lane per row so that lanes differ: one gather and not one per batch.  Nibbles, fp16, 600 x
-    // 1003 static 8.9 us, so 7.6; 4680 x 1003 11.7, 10.0; dynamic 18.5, 15.9.  With one batch per wave nothing is kept (7.0 us, 7.3).
+    // 1003 static 8.9 us, so 7.6; 4680 x 1003 11.7, 10.1; dynamic 18.5, 15.9.  With one batch per wave nothing is kept (INT8 600 x 1003 7.0,
+    // kept 7.3).
     const int tail_waves = (NT + 63) >> 6, tail_log = NT <= 8 ? 3 : NT <= 16 ? 2 : NT <= 32 ? 1 : 0;
     const bool later = R == 4 && KQ != K && tail_waves * (R >> min(tail_log, 2)) > waves;
     for (int rs = row_begin; rs < row_end; rs += R) {
